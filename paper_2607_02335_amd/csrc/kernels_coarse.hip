@@ -15,6 +15,7 @@
 // a Kronecker sum of 1D matrices, so A_0^{-1} = (Sx (x) Sy (x) Sz)
 // diag(1/(lx + ly + lz)) (Sx (x) Sy (x) Sz)^T with the 1D generalised
 // eigenvectors S (S^T M S = I) of the interior vertices.
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -42,28 +43,34 @@ struct GllNodes {
 // storage precision S), c = z (primal, S), d = corner sums
 // ([8][nblk * 64] doubles), e = two coarse vectors (2 x (n0-1)(n1-1)(n2-1)
 // doubles), fd[0..2] = per direction the coarse S ((n-1) x (n-1)) followed by
-// lambda (n-1).  Tiles are 256 cells (restriction and prolongation) or 256
-// coarse values (vertex sums and solve passes) of one problem.
+// lambda (n-1).  Tiles are one storage block (restriction and prolongation),
+// one z-plane or 32 z-columns of coarse values (plane solve), or 256 coarse
+// values (pass solve) of one problem.
 __device__ __forceinline__ int coarse_m(const ProbEntry& pe, int d) { return pe.n[d] > 1 ? pe.n[d] - 1 : 0; }
 
-// Cell -> its 8 corner sums, one thread per cell (lanes on the cells of a
-// storage block, so every load is a contiguous run); sums in FP64, streamed
-// over the z node planes.  corner[(sx + 2 sy + 4 sz) * nblk * 64 + e].
+// Cell -> its 8 corner sums, one workgroup per storage block, lanes on its 64
+// cells (every load is a contiguous run) and the z node planes dealt to the
+// four wavefronts, whose sums meet in LDS.  Bound by reading t once: one
+// thread per cell left a 24^3 mesh with 216 wavefronts, each walking its 512
+// values one plane after the other.  Sums in FP64.
+// corner[(sx + 2 sy + 4 sz) * nblk * 64 + e].
+constexpr int kRestrictLds = 4 * 8 * kLanes * (int)sizeof(double);
+
 template <int P, typename S, bool MULTI>
-__device__ __forceinline__ void restrict_cells_body(const LaunchTable& L, const GllNodes& g, int item, int items) {
+__device__ __forceinline__ void restrict_cells_body(const LaunchTable& L, const GllNodes& g, int item, int items,
+                                                    char* smem) {
     constexpr int N = P + 1, N2 = N * N, NN = N2 * N;
     const int tile = item;
-    if (tile >= L.total_tiles) return;
+    if (tile >= L.total_tiles) return;              // uniform over the workgroup
     const ProbEntry& pe = entry<MULTI>(L, tile);
-    const int stride = pe.nblk * kLanes;
-    const int e = (tile - pe.tile_begin) * 256 + threadIdx.x;
-    if (e >= stride) return;
+    const int lane = threadIdx.x % kLanes, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kLanes));
+    const int e = (tile - pe.tile_begin) * kLanes + lane;
     double out[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) out[i] = 0.0;
     if (e < pe.ncells) {
-        const S* v = static_cast<const S*>(pe.a) + (size_t)(e / kLanes) * NN * kLanes + (e % kLanes);
-        for (int c = 0; c < N; ++c) {
+        const S* v = static_cast<const S*>(pe.a) + (size_t)(e / kLanes) * NN * kLanes + lane;
+        for (int c = wv; c < N; c += 4) {
             double ux[2][N];
 #pragma unroll
             for (int b = 0; b < N; ++b) {
@@ -94,28 +101,31 @@ __device__ __forceinline__ void restrict_cells_body(const LaunchTable& L, const 
             }
         }
     }
+    double* part = reinterpret_cast<double*>(smem);             // [wavefront][corner][cell]
+#pragma unroll
+    for (int i = 0; i < 8; ++i) part[(wv * 8 + i) * kLanes + lane] = out[i];
+    __syncthreads();
+    const int stride = pe.nblk * kLanes;
     double* corner = static_cast<double*>(pe.d);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) corner[(size_t)i * stride + e] = out[i];
+    for (int h = 0; h < 2; ++h) {
+        const int i = wv + 4 * h;
+        double s = part[i * kLanes + lane];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) s += part[(w * 8 + i) * kLanes + lane];
+        corner[(size_t)i * stride + e] = s;
+    }
 }
 
 template <int P, typename S, bool MULTI>
 __global__ void __launch_bounds__(256) k_restrict_cells(LaunchTable L, GllNodes g) {
-    restrict_cells_body<P, S, MULTI>(L, g, blockIdx.x, gridDim.x);
+    __shared__ __align__(16) char smem[kRestrictLds];
+    restrict_cells_body<P, S, MULTI>(L, g, blockIdx.x, gridDim.x, smem);
 }
 
-// Corner sums -> coarse right-hand side at the interior vertices (the first
-// coarse vector), one thread per vertex, the eight cells added in ascending
-// cell order.
-template <bool MULTI>
-__global__ void __launch_bounds__(256) k_restrict_vertices(LaunchTable L) {
-    const int tile = blockIdx.x;
-    if (tile >= L.total_tiles) return;
-    const ProbEntry& pe = entry<MULTI>(L, tile);
-    const int m0 = coarse_m(pe, 0), m1 = coarse_m(pe, 1), m2 = coarse_m(pe, 2);
-    const long v = (long)(tile - pe.tile_begin) * 256 + threadIdx.x;
-    if (v >= (long)m0 * m1 * m2) return;
-    const int vi = 1 + (int)(v % m0), vj = 1 + (int)((v / m0) % m1), vk = 1 + (int)(v / ((long)m0 * m1));
+// Coarse right-hand side at interior vertex (vi, vj, vk) from the corner
+// sums: its eight cells added in ascending cell order.
+__device__ __forceinline__ double vertex_sum(const ProbEntry& pe, int vi, int vj, int vk) {
     const int n0 = pe.n[0], n1 = pe.n[1];
     const int stride = pe.nblk * kLanes;
     const double* corner = static_cast<const double*>(pe.d);
@@ -130,7 +140,138 @@ __global__ void __launch_bounds__(256) k_restrict_vertices(LaunchTable L) {
                 const int e = (vi - 1 + dx) + n0 * ((vj - 1 + dy) + n1 * (vk - 1 + dz));
                 s += corner[(size_t)((1 - dx) + 2 * (1 - dy) + 4 * (1 - dz)) * stride + e];
             }
-    static_cast<double*>(pe.e)[v] = s;
+    return s;
+}
+
+// The coarse solve in three launches where a z-plane of coarse values and the
+// bases fit in 64 KB of LDS (coarse_planes_fit): x and y forward per z-plane
+// (reading the corner sums), z forward, scaling and z backward per 32
+// columns, y and x backward per z-plane.  The work is a few MFLOP, so the
+// time is launches and dependent loads: the nine launches of the pass solve
+// with one thread per cell and per value (each sum a chain of loads from L2)
+// took 257 us for a whole correction on Q7 24^3 cells in FP32, 103 us on Q4
+// 21x13x30 and 44 us on Q2 12^3, these five launches 43, 31 and 22 us.  Every
+// sum runs over the same terms in the same order as k_coarse_pass (bitwise
+// equal).
+constexpr int kPlaneLds = 8192;                     // doubles
+constexpr int kPlaneThreads = 512;
+constexpr int kColumns = 32;
+
+static int plane_lds(const ProbEntry& e) {
+    const int m0 = e.n[0] - 1, m1 = e.n[1] - 1, mx = m0 > m1 ? m0 : m1;
+    return 2 * m0 * m1 + mx * mx;
+}
+static int column_lds(const ProbEntry& e) {
+    const int m2 = e.n[2] - 1;
+    return m2 * m2 + 2 * m2 * kColumns;
+}
+
+// out(o, r) = sum_i A(i, o) x(i, r) over a plane in LDS, i ascending; the
+// value (i, r) sits at i si + r sr, A row-major [m][m].
+__device__ __forceinline__ void plane_pass(const double* A, const double* x, double* out, int m, int rows, int si,
+                                           int sr, bool o_fastest, int tid, int nt) {
+    for (int id = tid; id < m * rows; id += nt) {
+        const int o = o_fastest ? id % m : id / rows, r = o_fastest ? id / m : id % rows;
+        const double* xr = x + r * sr;
+        double s = 0.0;
+#pragma unroll 4
+        for (int i = 0; i < m; ++i) s += A[i * m + o] * xr[i * si];
+        out[o * si + r * sr] = s;
+    }
+}
+
+// A basis into LDS, as stored (forward: S^T x) or transposed (backward: S x).
+__device__ __forceinline__ void load_basis(const double* S, double* A, int m, bool transpose, int tid, int nt) {
+    for (int id = tid; id < m * m; id += nt) {
+        if (transpose) A[(id % m) * m + id / m] = S[id];
+        else A[id] = S[id];
+    }
+}
+
+// fwd: vertex sums, x then y forward into the second coarse vector; else
+// y then x backward from the second coarse vector into the first.
+template <bool MULTI>
+__global__ void __launch_bounds__(kPlaneThreads) k_coarse_plane(LaunchTable L, int fwd) {
+    extern __shared__ double sm[];
+    const int tile = blockIdx.x;
+    if (tile >= L.total_tiles) return;
+    const ProbEntry& pe = entry<MULTI>(L, tile);
+    const int m0 = pe.n[0] - 1, m1 = pe.n[1] - 1, m2 = pe.n[2] - 1, np = m0 * m1;
+    const int k = tile - pe.tile_begin, tid = threadIdx.x;
+    double* x = sm;
+    double* w = sm + np;
+    double* A = sm + 2 * np;
+    double* cv = static_cast<double*>(pe.e);
+    double* half1 = cv + (size_t)np * m2 + (size_t)k * np;
+    const double* Sx = static_cast<const double*>(pe.fd[0]);
+    const double* Sy = static_cast<const double*>(pe.fd[1]);
+    for (int id = tid; id < np; id += kPlaneThreads)
+        x[id] = fwd ? vertex_sum(pe, 1 + id % m0, 1 + id / m0, 1 + k) : half1[id];
+    if (fwd) load_basis(Sx, A, m0, false, tid, kPlaneThreads);
+    else load_basis(Sy, A, m1, true, tid, kPlaneThreads);
+    __syncthreads();
+    if (fwd) plane_pass(A, x, w, m0, m1, 1, m0, true, tid, kPlaneThreads);
+    else plane_pass(A, x, w, m1, m0, m0, 1, false, tid, kPlaneThreads);
+    __syncthreads();
+    if (fwd) load_basis(Sy, A, m1, false, tid, kPlaneThreads);
+    else load_basis(Sx, A, m0, true, tid, kPlaneThreads);
+    __syncthreads();
+    if (fwd) plane_pass(A, w, half1, m1, m0, m0, 1, false, tid, kPlaneThreads);
+    else plane_pass(A, w, cv + (size_t)k * np, m0, m1, 1, m0, true, tid, kPlaneThreads);
+}
+
+// z forward, division by lx + ly + lz, z backward of 32 columns of the
+// second coarse vector, in place.
+template <bool MULTI>
+__global__ void __launch_bounds__(256) k_coarse_columns(LaunchTable L) {
+    extern __shared__ double sm[];
+    const int tile = blockIdx.x;
+    if (tile >= L.total_tiles) return;
+    const ProbEntry& pe = entry<MULTI>(L, tile);
+    const int m0 = pe.n[0] - 1, m1 = pe.n[1] - 1, m2 = pe.n[2] - 1, np = m0 * m1;
+    const int tid = threadIdx.x, c = tid % kColumns;
+    const int col = (tile - pe.tile_begin) * kColumns + c;
+    const bool ok = col < np;
+    double* A = sm;
+    double* x = sm + m2 * m2;
+    double* w = x + m2 * kColumns;
+    double* v = static_cast<double*>(pe.e) + (size_t)np * m2 + (ok ? col : 0);
+    const double* Sz = static_cast<const double*>(pe.fd[2]);
+    load_basis(Sz, A, m2, false, tid, 256);
+    for (int k = tid / kColumns; k < m2; k += 256 / kColumns) x[k * kColumns + c] = ok ? v[(size_t)k * np] : 0.0;
+    __syncthreads();
+    const double* lx = static_cast<const double*>(pe.fd[0]) + (size_t)m0 * m0;
+    const double* ly = static_cast<const double*>(pe.fd[1]) + (size_t)m1 * m1;
+    const double* lz = Sz + (size_t)m2 * m2;
+    const double lxy = ok ? lx[col % m0] + ly[col / m0] : 1.0;
+    for (int o = tid / kColumns; o < m2; o += 256 / kColumns) {
+        double s = 0.0;
+#pragma unroll 4
+        for (int i = 0; i < m2; ++i) s += A[i * m2 + o] * x[i * kColumns + c];
+        s /= lxy + lz[o];
+        w[o * kColumns + c] = s;
+    }
+    __syncthreads();
+    for (int o = tid / kColumns; o < m2; o += 256 / kColumns) {
+        double s = 0.0;
+#pragma unroll 4
+        for (int j = 0; j < m2; ++j) s += A[o * m2 + j] * w[j * kColumns + c];
+        if (ok) v[(size_t)o * np] = s;
+    }
+}
+
+// Corner sums -> coarse right-hand side at the interior vertices (the first
+// coarse vector), one thread per vertex.
+template <bool MULTI>
+__global__ void __launch_bounds__(256) k_restrict_vertices(LaunchTable L) {
+    const int tile = blockIdx.x;
+    if (tile >= L.total_tiles) return;
+    const ProbEntry& pe = entry<MULTI>(L, tile);
+    const int m0 = coarse_m(pe, 0), m1 = coarse_m(pe, 1), m2 = coarse_m(pe, 2);
+    const long v = (long)(tile - pe.tile_begin) * 256 + threadIdx.x;
+    if (v >= (long)m0 * m1 * m2) return;
+    static_cast<double*>(pe.e)[v] =
+        vertex_sum(pe, 1 + (int)(v % m0), 1 + (int)((v / m0) % m1), 1 + (int)(v / ((long)m0 * m1)));
 }
 
 // One 1D pass of the coarse fast-diagonalisation solve along `axis` (0 = x)
@@ -169,11 +310,21 @@ __global__ void __launch_bounds__(256) k_coarse_pass(LaunchTable L, int axis, in
     dst[id] = s;
 }
 
+// (1 - xi) e0 + xi e1 at node a of N = P + 1 along one direction; the end
+// nodes take their vertex value itself.
+template <int P>
+__device__ __forceinline__ double between(double e0, double e1, int a, double xi) {
+    const double m = (1.0 - xi) * e0 + xi * e1;
+    return a == 0 ? e0 : a == P ? e1 : m;
+}
+
 // z += P_0 e: trilinear interpolation of the coarse correction (the first
-// coarse vector) at the cell nodes, one thread per cell.  Only corners with
-// a nonzero weight at a node are summed, in (sz, sy, sx) order, so the
-// copies of a node shared by several cells add the same terms in the same
-// order (bitwise continuous).
+// coarse vector) at the cell nodes, along z, then y, then x.  One workgroup
+// per storage block, lanes on its cells, the z node planes dealt to the four
+// wavefronts (as the restriction).  A node shared by several cells is an end
+// node along the shared directions, so every copy takes the same vertex
+// values with the same weights (bitwise continuous).  Bound by reading and
+// writing z once.
 template <int P, typename S, bool MULTI>
 __device__ __forceinline__ void prolong_add_body(const LaunchTable& L, const GllNodes& g, int item, int items) {
     using C = typename Prec<S>::C;
@@ -181,7 +332,8 @@ __device__ __forceinline__ void prolong_add_body(const LaunchTable& L, const Gll
     const int tile = item;
     if (tile >= L.total_tiles) return;
     const ProbEntry& pe = entry<MULTI>(L, tile);
-    const int e = (tile - pe.tile_begin) * 256 + threadIdx.x;
+    const int lane = threadIdx.x % kLanes, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kLanes));
+    const int e = (tile - pe.tile_begin) * kLanes + lane;
     if (e >= pe.ncells) return;
     const int n0 = pe.n[0], n1 = pe.n[1], n2 = pe.n[2];
     const int m0 = coarse_m(pe, 0), m1 = coarse_m(pe, 1);
@@ -198,30 +350,19 @@ __device__ __forceinline__ void prolong_add_body(const LaunchTable& L, const Gll
                 const bool in = vi >= 1 && vi <= n0 - 1 && vj >= 1 && vj <= n1 - 1 && vk >= 1 && vk <= n2 - 1;
                 cv[sx + 2 * sy + 4 * sz] = in ? ev[(vi - 1) + (long)m0 * ((vj - 1) + (long)m1 * (vk - 1))] : 0.0;
             }
-    S* out = static_cast<S*>(pe.c) + (size_t)(e / kLanes) * NN * kLanes + (e % kLanes);
-    for (int c = 0; c < N; ++c) {
-        const double wz[2] = {1.0 - g.xi[c], g.xi[c]};
+    S* out = static_cast<S*>(pe.c) + (size_t)(e / kLanes) * NN * kLanes + lane;
+    for (int c = wv; c < N; c += 4) {
+        double p[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) p[q] = between<P>(cv[q], cv[q + 4], c, g.xi[c]);
+        S* row = out + (size_t)c * N2 * kLanes;
+#pragma unroll
         for (int b = 0; b < N; ++b) {
-            const double wy[2] = {1.0 - g.xi[b], g.xi[b]};
+            const double l0 = between<P>(p[0], p[2], b, g.xi[b]), l1 = between<P>(p[1], p[3], b, g.xi[b]);
 #pragma unroll
             for (int a = 0; a < N; ++a) {
-                const double wx[2] = {1.0 - g.xi[a], g.xi[a]};
-                double s = 0.0;
-#pragma unroll
-                for (int sz = 0; sz < 2; ++sz) {
-                    if (wz[sz] == 0.0) continue;
-#pragma unroll
-                    for (int sy = 0; sy < 2; ++sy) {
-                        if (wy[sy] == 0.0) continue;
-#pragma unroll
-                        for (int sx = 0; sx < 2; ++sx) {
-                            if (wx[sx] == 0.0) continue;
-                            s += cv[sx + 2 * sy + 4 * sz] * (wx[sx] * wy[sy] * wz[sz]);
-                        }
-                    }
-                }
-                S* dst = out + (size_t)(a + N * b + N2 * c) * kLanes;
-                store_from(dst, (C)(load_as<double>(dst) + s));
+                S* dst = row + (size_t)(a + N * b) * kLanes;
+                store_from(dst, (C)(load_as<double>(dst) + between<P>(l0, l1, a, g.xi[a])));
             }
         }
     }
@@ -242,11 +383,71 @@ static hipError_t by_prec(int prec, F&& f) {
     }
 }
 
-// Tiles of the cell kernels (256 cells each); a problem without interior
-// vertices has no coarse space and takes no correction.
-static int coarse_cell_tiles(const ProbEntry& e) {
-    const bool any = e.n[0] > 1 && e.n[1] > 1 && e.n[2] > 1;
-    return any ? (e.nblk * kLanes + 255) / 256 : 0;
+static bool has_coarse(const ProbEntry& e) { return e.n[0] > 1 && e.n[1] > 1 && e.n[2] > 1; }
+
+// Tiles of the cell kernels (one storage block each); a problem without
+// interior vertices has no coarse space and takes no correction.
+static int coarse_cell_tiles(const ProbEntry& e) { return has_coarse(e) ? e.nblk : 0; }
+
+// Fill the tile ranges of `ents` by `tiles` and stage the table.
+template <typename F>
+static hipError_t coarse_table(LaunchTable& L, ProbEntry* ents, int nprob, TableStager* st, hipStream_t s, F&& tiles) {
+    int t = 0;
+    for (int i = 0; i < nprob; ++i) {
+        ents[i].tile_begin = t;
+        ents[i].ntiles = has_coarse(ents[i]) ? tiles(ents[i]) : 0;
+        t += ents[i].ntiles;
+    }
+    L.nprob = nprob;
+    L.total_tiles = t;
+    return stage_table(L, ents, nprob, st, s);
+}
+
+// The coarse solve's tables: plane and column tiles where every problem of
+// the launch fits k_coarse_plane and k_coarse_columns, else tiles of 256
+// coarse values for the passes.
+struct CoarseSolve {
+    bool planes = true;
+    int lds_plane = 0, lds_column = 0;
+    LaunchTable Lp{}, Lc{}, Lv{};
+    bool empty() const { return planes ? Lp.total_tiles == 0 : Lv.total_tiles == 0; }
+};
+
+static hipError_t coarse_solve_tables(CoarseSolve& cs, ProbEntry* ents, int nprob, TableStager* st, hipStream_t s) {
+    for (int i = 0; i < nprob; ++i) {
+        if (!has_coarse(ents[i])) continue;
+        cs.lds_plane = std::max(cs.lds_plane, plane_lds(ents[i]));
+        cs.lds_column = std::max(cs.lds_column, column_lds(ents[i]));
+    }
+    cs.planes = cs.lds_plane <= kPlaneLds && cs.lds_column <= kPlaneLds;
+    if (!cs.planes)
+        return coarse_table(cs.Lv, ents, nprob, st, s, [](const ProbEntry& e) {
+            return (int)(((long)(e.n[0] - 1) * (e.n[1] - 1) * (e.n[2] - 1) + 255) / 256);
+        });
+    hipError_t err = coarse_table(cs.Lp, ents, nprob, st, s, [](const ProbEntry& e) { return e.n[2] - 1; });
+    if (err != hipSuccess) return err;
+    return coarse_table(cs.Lc, ents, nprob, st, s, [](const ProbEntry& e) {
+        return ((e.n[0] - 1) * (e.n[1] - 1) + kColumns - 1) / kColumns;
+    });
+}
+
+// Corner sums -> the coarse correction in the first coarse vector.
+template <bool MULTI>
+static void launch_coarse_solve(const CoarseSolve& cs, hipStream_t s) {
+    if (cs.planes) {
+        const int lp = cs.lds_plane * (int)sizeof(double), lc = cs.lds_column * (int)sizeof(double);
+        hipLaunchKernelGGL(k_coarse_plane<MULTI>, dim3(cs.Lp.total_tiles), dim3(kPlaneThreads), lp, s, cs.Lp, 1);
+        hipLaunchKernelGGL(k_coarse_columns<MULTI>, dim3(cs.Lc.total_tiles), dim3(256), lc, s, cs.Lc);
+        hipLaunchKernelGGL(k_coarse_plane<MULTI>, dim3(cs.Lp.total_tiles), dim3(kPlaneThreads), lp, s, cs.Lp, 0);
+        return;
+    }
+    const dim3 grid(cs.Lv.total_tiles), block(256);
+    hipLaunchKernelGGL(k_restrict_vertices<MULTI>, grid, block, 0, s, cs.Lv);
+    // x, y, z forward (then the eigenvalue scaling), z, y, x backward;
+    // vector 0 -> 1 -> 0 -> 1 -> 0 -> 1 -> 0
+    const int axis[6] = {0, 1, 2, 2, 1, 0}, fwd[6] = {1, 1, 1, 0, 0, 0};
+    for (int k = 0; k < 6; ++k)
+        hipLaunchKernelGGL(k_coarse_pass<MULTI>, grid, block, 0, s, cs.Lv, axis[k], fwd[k], k % 2, k == 2 ? 1 : 0);
 }
 
 template <int P>
@@ -254,63 +455,39 @@ static hipError_t coarse_p(int prec, ProbEntry* ents, int nprob, TableStager* st
     GllNodes g{};
     const std::vector<double>& xi = gll_cached(P);
     for (int a = 0; a <= P; ++a) g.xi[a] = xi[a];
-    const bool multi = nprob > 1;
-    // cell-based tables (restriction, prolongation)
     LaunchTable Lc{};
-    int tc = 0;
-    for (int i = 0; i < nprob; ++i) {
-        ents[i].tile_begin = tc;
-        ents[i].ntiles = coarse_cell_tiles(ents[i]);
-        tc += ents[i].ntiles;
-    }
-    Lc.nprob = nprob;
-    Lc.total_tiles = tc;
-    hipError_t err = stage_table(Lc, ents, nprob, st, s);
+    hipError_t err = coarse_table(Lc, ents, nprob, st, s, coarse_cell_tiles);
     if (err != hipSuccess) return err;
-    // coarse-value tables (vertex sums, solve passes)
-    LaunchTable Lv{};
-    int tv = 0;
-    for (int i = 0; i < nprob; ++i) {
-        long nv = 1;
-        for (int d = 0; d < 3; ++d) nv *= ents[i].n[d] > 1 ? ents[i].n[d] - 1 : 0;
-        ents[i].tile_begin = tv;
-        ents[i].ntiles = (int)((nv + 255) / 256);
-        tv += ents[i].ntiles;
-    }
-    Lv.nprob = nprob;
-    Lv.total_tiles = tv;
-    if (tv == 0) return hipSuccess;                 // no interior vertex anywhere: no coarse space
-    err = stage_table(Lv, ents, nprob, st, s);
+    if (Lc.total_tiles == 0) return hipSuccess;     // no interior vertex anywhere: no coarse space
+    CoarseSolve cs;
+    err = coarse_solve_tables(cs, ents, nprob, st, s);
     if (err != hipSuccess) return err;
+    const dim3 grid(Lc.total_tiles), block(256);
     return by_prec(prec, [&](auto tag) {
         using S = decltype(tag);
         TraceSpan ts("coarse_correction", P, Prec<S>::id, s);
-        if (multi) hipLaunchKernelGGL((k_restrict_cells<P, S, true>), dim3(tc), dim3(256), 0, s, Lc, g);
-        else hipLaunchKernelGGL((k_restrict_cells<P, S, false>), dim3(tc), dim3(256), 0, s, Lc, g);
-        if (multi) hipLaunchKernelGGL(k_restrict_vertices<true>, dim3(tv), dim3(256), 0, s, Lv);
-        else hipLaunchKernelGGL(k_restrict_vertices<false>, dim3(tv), dim3(256), 0, s, Lv);
-        // x, y, z forward (then the eigenvalue scaling), z, y, x backward;
-        // vector 0 -> 1 -> 0 -> 1 -> 0 -> 1 -> 0
-        const int axis[6] = {0, 1, 2, 2, 1, 0}, fwd[6] = {1, 1, 1, 0, 0, 0};
-        for (int k = 0; k < 6; ++k) {
-            if (multi) hipLaunchKernelGGL(k_coarse_pass<true>, dim3(tv), dim3(256), 0, s, Lv, axis[k], fwd[k], k % 2, k == 2 ? 1 : 0);
-            else hipLaunchKernelGGL(k_coarse_pass<false>, dim3(tv), dim3(256), 0, s, Lv, axis[k], fwd[k], k % 2, k == 2 ? 1 : 0);
+        if (nprob > 1) {
+            hipLaunchKernelGGL((k_restrict_cells<P, S, true>), grid, block, 0, s, Lc, g);
+            launch_coarse_solve<true>(cs, s);
+            hipLaunchKernelGGL((k_prolong_add<P, S, true>), grid, block, 0, s, Lc, g);
+        } else {
+            hipLaunchKernelGGL((k_restrict_cells<P, S, false>), grid, block, 0, s, Lc, g);
+            launch_coarse_solve<false>(cs, s);
+            hipLaunchKernelGGL((k_prolong_add<P, S, false>), grid, block, 0, s, Lc, g);
         }
-        if (multi) hipLaunchKernelGGL((k_prolong_add<P, S, true>), dim3(tc), dim3(256), 0, s, Lc, g);
-        else hipLaunchKernelGGL((k_prolong_add<P, S, false>), dim3(tc), dim3(256), 0, s, Lc, g);
         return hipGetLastError();
     });
 }
 
 // Mixed-degree coarse correction: restriction and prolongation as mixed
-// launches (cell tiles of the degrees 7, 3, 2), the vertex sums and the six
-// solve passes (the same for every degree) over all problems at once.
+// launches (cell tiles of the degrees 7, 3, 2), the coarse solve (the same for
+// every degree) over all problems at once.
 template <int P, typename S>
 struct RestrictBody {
     using Arg = GllNodes;
-    static constexpr int kLds = 0;
-    __device__ static __forceinline__ void run(const LaunchTable& L, const GllNodes& g, int item, int items, char*) {
-        restrict_cells_body<P, S, true>(L, g, item, items);
+    static constexpr int kLds = kRestrictLds;
+    __device__ static __forceinline__ void run(const LaunchTable& L, const GllNodes& g, int item, int items, char* smem) {
+        restrict_cells_body<P, S, true>(L, g, item, items, smem);
     }
 };
 
@@ -332,21 +509,10 @@ static GllNodes gll_arg(int p) {
 
 static hipError_t coarse_mixed(int prec, ProbEntry* ents, int nprob, TableStager* st, hipStream_t s) {
     static_assert(mix_degree(0) == 7 && mix_degree(1) == 3 && mix_degree(2) == 2, "segment degrees");
-    // coarse-value tables (vertex sums, solve passes) over all problems
-    LaunchTable Lv{};
-    int tv = 0;
-    for (int i = 0; i < nprob; ++i) {
-        long nv = 1;
-        for (int d = 0; d < 3; ++d) nv *= ents[i].n[d] > 1 ? ents[i].n[d] - 1 : 0;
-        ents[i].tile_begin = tv;
-        ents[i].ntiles = (int)((nv + 255) / 256);
-        tv += ents[i].ntiles;
-    }
-    Lv.nprob = nprob;
-    Lv.total_tiles = tv;
-    if (tv == 0) return hipSuccess;                 // no interior vertex anywhere: no coarse space
-    hipError_t err = stage_table(Lv, ents, nprob, st, s);
+    CoarseSolve cs;
+    hipError_t err = coarse_solve_tables(cs, ents, nprob, st, s);
     if (err != hipSuccess) return err;
+    if (cs.empty()) return hipSuccess;              // no interior vertex anywhere: no coarse space
     MixTable T{};
     int grid = 0;
     auto tiles = [](int, const ProbEntry& e) { return coarse_cell_tiles(e); };
@@ -354,20 +520,13 @@ static hipError_t coarse_mixed(int prec, ProbEntry* ents, int nprob, TableStager
     err = mix_build(ents, nprob, st, s, tiles, items, T, grid);
     if (err != hipSuccess) return err;
     const GllNodes g7 = gll_arg(7), g3 = gll_arg(3), g2 = gll_arg(2);
-    const bool multi = nprob > 1;
     return by_prec(prec, [&](auto tag) {
         using S = decltype(tag);
         TraceSpan ts("coarse_correction", 0, Prec<S>::id, s);
         if (grid > 0)
             hipLaunchKernelGGL((k_mixed<RestrictBody<7, S>, RestrictBody<3, S>, RestrictBody<2, S>>), dim3(grid),
                                dim3(256), 0, s, T, g7, g3, g2);
-        if (multi) hipLaunchKernelGGL(k_restrict_vertices<true>, dim3(tv), dim3(256), 0, s, Lv);
-        else hipLaunchKernelGGL(k_restrict_vertices<false>, dim3(tv), dim3(256), 0, s, Lv);
-        const int axis[6] = {0, 1, 2, 2, 1, 0}, fwd[6] = {1, 1, 1, 0, 0, 0};
-        for (int k = 0; k < 6; ++k) {
-            if (multi) hipLaunchKernelGGL(k_coarse_pass<true>, dim3(tv), dim3(256), 0, s, Lv, axis[k], fwd[k], k % 2, k == 2 ? 1 : 0);
-            else hipLaunchKernelGGL(k_coarse_pass<false>, dim3(tv), dim3(256), 0, s, Lv, axis[k], fwd[k], k % 2, k == 2 ? 1 : 0);
-        }
+        launch_coarse_solve<true>(cs, s);
         if (grid > 0)
             hipLaunchKernelGGL((k_mixed<ProlongBody<7, S>, ProlongBody<3, S>, ProlongBody<2, S>>), dim3(grid),
                                dim3(256), 0, s, T, g7, g3, g2);
