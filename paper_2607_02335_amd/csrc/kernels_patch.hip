@@ -21,6 +21,7 @@
 //   the output is continuous exactly, not just to rounding.
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "fem_internal.h"
 #include "launch.h"
@@ -2303,53 +2304,11 @@ __global__ void __launch_bounds__(256) k_pi_combine_rows(LaunchTable L) {
 }
 
 // ---------------------------------------------------------------------------
-// High-degree variant (4 <= p <= 7): the six 1D contractions of a patch are
-// dense products of a (2p-1)x(2p-1) eigenbasis with the (2p-1) x (2p-1)^2
-// matrix of the patch's lines, so they run on the matrix cores: 16x16x4
-// MFMA tiles (FP64 or FP32), the basis zero-padded to 16x16 as the register
-// A operand and 16 patch lines per tile as the B operand read from LDS.
-// One or two wavefronts own one patch (mfma_waves_per_patch); the residual
-// is first assembled into a global-node array (k_assemble_nodes), so a patch
-// reads its (2p-1)^3 box without summing copies, and the results go to a
-// patch-major buffer (one contiguous run per patch) for k_pi_combine_pm.
-// out(j, line) = sum_i Op(j, i) v(i, line) in place over all lines of the
-// patch; Op's 16x4 slices for the four k-steps are in `a`.  The patch's WPP
-// wavefronts (sub = this one's index) take every WPP-th 16-line tile.
-// Branch-free: the B operand of k >= 2p-1 is read from the clamped index
-// (the A slice is zero there, so it adds exact zeros), the tail lines of the
-// last tile read the last line, and every result row that is not part of the
-// patch is stored to the wavefront's dump slot instead.
-template <typename C, int nP, int DIR, int WPP>
-__device__ __forceinline__ void mfma_pass(C* pv, C* dump, const C (&a)[4], int lane, int sub) {
-    using M = Mfma<C>;
-    constexpr int NL = nP * nP, NT = (NL + 15) / 16;
-    // element (i, line) of the pass's lines sits at base(line) + STRIDE * i
-    constexpr int STRIDE = DIR == 2 ? NL : DIR == 1 ? nP : 1;
-    const int col = lane % 16, g = lane / 16;
-    int koff[4], joff[4];
-    bool jok[4];
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) koff[ks] = STRIDE * min(4 * ks + g, nP - 1);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int j = M::row(lane, r);
-        jok[r] = j < nP;
-        joff[r] = STRIDE * (jok[r] ? j : 0);
-    }
-    for (int t = sub; t < NT; t += WPP) {
-        const int line = 16 * t + col;
-        const bool lok = line < NL;
-        const int lc = lok ? line : NL - 1;
-        const int base = DIR == 2 ? lc : DIR == 1 ? (lc % nP) + NL * (lc / nP) : nP * lc;
-        typename M::V acc = {0, 0, 0, 0};
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) acc = M::mma(a[ks], pv[base + koff[ks]], acc);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) *((lok && jok[r]) ? pv + base + joff[r] : dump + lane) = acc[r];
-    }
-    if (WPP == 1) wave_sync();
-    else __syncthreads();
-}
+// High-degree variant (4 <= p <= 7): the residual is first assembled into a
+// global-node array (k_assemble_nodes), so a patch reads its (2p-1)^3 box
+// without summing copies, one wavefront solves a patch (k_pi_solve_l), and the
+// results go to a patch-major buffer (one contiguous run per patch) for the
+// combine.
 
 // Combine from a patch-major buffer (p >= 4): a workgroup takes one storage
 // block (64 cells) at one node plane c.  Each wavefront walks 16 of the
@@ -2569,165 +2528,210 @@ __global__ void __launch_bounds__(256) k_pi_combine_nr(LaunchTable L) {
     pi_combine_nr_body<P, S, ACC, MULTI>(L, blockIdx.x, gridDim.x, smem);
 }
 
-// The x pair (forward product, scaling by 1/(lambda_x+lambda_y+lambda_z),
-// backward product) of every 16-line tile chained in registers: the
-// forward product's accumulators are the backward product's B operand.  A
-// lane holds accumulator rows row(lane, 0..3), so the backward k-steps take
-// k = row(lane, ks) for lane group g = lane/16; `ab` holds the backward
-// basis slices in that order (A[m][row(16 g + m, ks)]).  Branch-free as
-// mfma_pass; a lane's four lambda_x values are loaded once.
-template <typename C, int nP, int WPP>
-__device__ __forceinline__ void mfma_pass_x2(C* pv, C* dump, const C (&af)[4], const C (&ab)[4], int lane, int sub,
-                                             const C* lx, const C* ly, const C* lz) {
-    using M = Mfma<C>;
-    constexpr int NL = nP * nP, NT = (NL + 15) / 16;
-    const int col = lane % 16, g = lane / 16;
-    int koff[4], jr[4];
-    bool jok[4];
-    C lxr[4];
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) koff[ks] = min(4 * ks + g, nP - 1);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int j = M::row(lane, r);
-        jok[r] = j < nP;
-        jr[r] = jok[r] ? j : 0;
-        lxr[r] = lx[jr[r]];
-    }
-    for (int t = sub; t < NT; t += WPP) {
-        const int line = 16 * t + col;
-        const bool lok = line < NL;
-        const int lc = lok ? line : NL - 1;
-        const int qy = lc % nP, qz = lc / nP;
-        const C* src = pv + nP * lc;
-        typename M::V acc = {0, 0, 0, 0};
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) acc = M::mma(af[ks], src[koff[ks]], acc);
-        const C lyz = ly[qy] + lz[qz];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] = jok[r] ? acc[r] * recip(lxr[r] + lyz) : (C)0;
-        typename M::V out = {0, 0, 0, 0};
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) out = M::mma(ab[ks], acc[ks], out);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) *((lok && jok[r]) ? pv + nP * lc + jr[r] : dump + lane) = out[r];
-    }
-    if (WPP == 1) wave_sync();
-    else __syncthreads();
+// The p >= 4 patch solves: one wavefront per patch, lanes on the patch's 1D
+// lines (up to three per lane), the eigenbases in scalar registers.  A pass
+// over one direction reads a lane's lines into registers, streams the rows of
+// the basis through scalar loads and multiplies them in; the basis is the same
+// for every lane, so an FMA takes it as its scalar operand and the vector side
+// holds nothing but patch values:
+//   z forward   straight from the assembled residual   -> [z][y][x] in LDS
+//   y forward   in place
+//   x forward, the scaling by 1/(lambda_x + lambda_y + lambda_z), x backward
+//               in registers, in place
+//   y backward  in place
+//   z backward  straight to the patch buffer
+// Loads of the residual and stores to the buffer have lanes on consecutive
+// nodes; no workgroup barrier.  Bound by the scalar loads of the bases and the
+// FMA rate: 6 (2p-1)^2 FMAs per 64 lines, with 169 lines in 192 lanes at
+// p = 7.  Measured on 24^3 cells at p = 7: 129 us in FP64 and 82 us in FP32
+// (without the scalar loads 94 and 57); dense products on 16x16x4 MFMA tiles
+// took 174 and 105 us, where 2p-1 = 13 pads to 16 rows, columns and terms, and
+// with two contractions chained in registers per LDS pass 143 and 82 us.  At
+// p = 4 on 21x13x30 cells in FP32 12 against 24 us.  The basis as a DPP
+// broadcast operand instead of a scalar one: 10% slower.
+template <int P, typename C> constexpr int solve_l_lds() {
+    return 4 * (2 * P - 1) * (2 * P - 1) * (2 * P - 1) * (int)sizeof(C);
 }
 
-// Wavefronts that share one patch: the larger patches split their 16-line
-// tiles over the whole workgroup for more waves in flight per LDS byte.
-template <int P> constexpr int mfma_waves_per_patch() { return P >= 6 ? 2 : 1; }
+// A basis in the constant address space (written before the launch only), so
+// that wavefront-uniform reads become scalar loads.
+template <typename C> using ScalarPtr = const C __attribute__((address_space(4)))*;
 
-template <int P, typename C> constexpr int mfma_lds() {
-    return ((4 / mfma_waves_per_patch<P>()) * (2 * P - 1) * (2 * P - 1) * (2 * P - 1) + 4 * 64) * (int)sizeof(C);
+// The same pointer, unknown to the compiler: rows that a later pass reads again
+// are loaded again instead of kept (a basis is more than the scalar registers
+// hold).
+template <typename C> __device__ __forceinline__ ScalarPtr<C> reread(ScalarPtr<C> f) {
+    const uint64_t a = (uint64_t)f;
+    uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    asm volatile("" : "+s"(lo), "+s"(hi));
+    return (ScalarPtr<C>)((uint64_t)hi << 32 | lo);
+}
+
+// f(i, row i) for every row of a basis; the next row is loaded while the
+// current one is multiplied in (two rows fill half of the scalar registers;
+// groups of two or three rows measured the same).
+template <int N, typename C> struct BasisRow { C v[N]; };
+
+template <int N, typename C, class F>
+__device__ __forceinline__ void each_row(ScalarPtr<C> S0, F&& f) {
+    const ScalarPtr<C> S = reread<C>(S0);
+    BasisRow<N, C> row[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) row[0].v[j] = S[j];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (i + 1 < N) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) row[i + 1].v[j] = S[(i + 1) * N + j];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        f(i, row[i].v);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// o(l, j) = sum_i S(i, j) v(l, i) for a lane's LN lines
+template <int N, int LN, typename C>
+__device__ __forceinline__ void lines_forward(ScalarPtr<C> S, const C (&v)[LN][N], C (&o)[LN][N]) {
+    each_row<N, C>(S, [&](int i, const C (&r)[N]) {
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+#pragma unroll
+            for (int l = 0; l < LN; ++l) o[l][j] = i == 0 ? r[j] * v[l][i] : o[l][j] + r[j] * v[l][i];
+    });
+}
+
+// sum_j S(i, j) v(l, j), handed to put(l, i, sum)
+template <int N, int LN, typename C, class F>
+__device__ __forceinline__ void lines_backward(ScalarPtr<C> S, const C (&v)[LN][N], F&& put) {
+    each_row<N, C>(S, [&](int i, const C (&r)[N]) {
+        C s[LN];
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+#pragma unroll
+            for (int l = 0; l < LN; ++l) s[l] = j == 0 ? r[j] * v[l][j] : s[l] + r[j] * v[l][j];
+#pragma unroll
+        for (int l = 0; l < LN; ++l) put(l, i, s[l]);
+    });
 }
 
 // pe: e = assembled global residual (C), d = patch buffer (C), fd = FD data (C)
 template <int P, typename S, typename C, bool MULTI>
-__device__ __forceinline__ void pi_solve_mfma_body(const LaunchTable& L, int item, int items, char* smem) {
-    constexpr int nP = 2 * P - 1, nP2 = nP * nP, nP3 = nP2 * nP;
+__device__ __forceinline__ void pi_solve_l_body(const LaunchTable& L, int item, int items, char* smem) {
+    constexpr int N = 2 * P - 1, N2 = N * N, N3 = N2 * N;
     constexpr int REC = fd_record(P);
-    constexpr int WPP = mfma_waves_per_patch<P>();   // wavefronts per patch
-    constexpr int PPW = 4 / WPP;                      // patches per workgroup
-    static_assert(nP <= 16, "one MFMA tile per contraction");
-    C (*spv)[nP3] = reinterpret_cast<C (*)[nP3]>(smem);
-    C (*sdump)[64] = reinterpret_cast<C (*)[64]>(smem + sizeof(C) * PPW * nP3);   // per-wavefront sink for rows outside the patch
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int slot = wv / WPP, sub = wv % WPP;
-    // a workgroup's patches are consecutive tiles.  A slot past the last
-    // patch (the tail of an odd patch count) solves the last patch again in
-    // its own LDS slot and stores nothing, so every wavefront of the
-    // workgroup reaches every barrier
-    const int tile_raw = item * PPW + slot;
-    const bool active = tile_raw < L.total_tiles;
-    const int tile = active ? tile_raw : L.total_tiles - 1;
+    constexpr int LN = (N2 + 63) / 64;                // lines per lane
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int tile = xcd_tile(item, items) * 4 + wv;  // neighbouring patches on one XCD
+    if (tile >= L.total_tiles) return;                // per wavefront: no workgroup barrier follows
     const ProbEntry& pe = entry<MULTI>(L, tile);
     const int pidx = tile - pe.tile_begin;
     const int npx = pe.n[0] - 1, npy = pe.n[1] - 1;
     const int vi = 1 + pidx % npx, vj = 1 + (pidx / npx) % npy, vk = 1 + pidx / (npx * npy);
-    const C* fx = static_cast<const C*>(pe.fd[0]) + (size_t)(vi - 1) * REC;
-    const C* fy = static_cast<const C*>(pe.fd[1]) + (size_t)(vj - 1) * REC;
-    const C* fz = static_cast<const C*>(pe.fd[2]) + (size_t)(vk - 1) * REC;
-    // A operands: forward uses S^T (A[j][i] = S[i][j]), backward uses S;
-    // each pass's slices are loaded while the previous pass runs
-    auto loadA = [&](const C* f, bool fwd, C (&a)[4]) {
+    const ScalarPtr<C> fx = (ScalarPtr<C>)(static_cast<const C*>(pe.fd[0]) + (size_t)(vi - 1) * REC);
+    const ScalarPtr<C> fy = (ScalarPtr<C>)(static_cast<const C*>(pe.fd[1]) + (size_t)(vj - 1) * REC);
+    const ScalarPtr<C> fz = (ScalarPtr<C>)(static_cast<const C*>(pe.fd[2]) + (size_t)(vk - 1) * REC);
+    C* const W = reinterpret_cast<C*>(smem) + wv * N3;
+    // a lane's lines; lanes past the last line repeat it (the same values to
+    // the same words)
+    int ln[LN], lh[LN], ll[LN];
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const int rr = lane % 16, kk = 4 * ks + lane / 16;
-            const bool ok = rr < nP && kk < nP;
-            a[ks] = ok ? (fwd ? f[kk * nP + rr] : f[rr * nP + kk]) : (C)0;
-        }
-    };
-    C a0[4], a1[4];
-    loadA(fz, true, a0);
-    C* pv = spv[slot];
-    const int t64 = sub * 64 + lane;                  // thread index within the patch's wavefronts
-    // restrict: the patch's box of the assembled residual
+    for (int l = 0; l < LN; ++l) {
+        ln[l] = min(lane + 64 * l, N2 - 1);
+        lh[l] = ln[l] / N;
+        ll[l] = ln[l] % N;
+    }
+    C v[LN][N], o[LN][N];
     {
         const size_t G0 = (size_t)pe.n[0] * P + 1, G1 = (size_t)pe.n[1] * P + 1;
         const size_t I0 = (size_t)(vi - 1) * P + 1, J0 = (size_t)(vj - 1) * P + 1, K0 = (size_t)(vk - 1) * P + 1;
-        // the box origin is uniform over the patch's wavefronts; offsets
-        // within the box stay below G0 G1 nP < 2^32 (checked at set-up)
-        const C* g = static_cast<const C*>(pe.e) + (I0 + G0 * (J0 + G1 * K0));
-        // element q = qx + nP qy + nP^2 qz; the thread's (qx, qy, qz) advance
-        // by the fixed stride without divisions, and all loads are issued
-        // before the first LDS store
-        constexpr int STEP = 64 * WPP, NIT = (nP3 + STEP - 1) / STEP;
-        constexpr int DX = STEP % nP, DY = (STEP / nP) % nP, DZ = STEP / nP2;
-        int qx = t64 % nP, qy = (t64 / nP) % nP;
-        const uint32_t g0 = (uint32_t)G0, g1 = (uint32_t)G1;
-        uint32_t off = qx + g0 * (qy + g1 * (uint32_t)(t64 / nP2));
-        const uint32_t dstep = DX + g0 * (DY + g1 * DZ);            // uniform node-offset steps
-        const uint32_t cx = g0 - nP, cy = g0 * (g1 - nP);           // carries into y and z
-        C vals[NIT];
+        // the plane origin is uniform; byte offsets within the plane's box
+        // stay below 8 G0 (2p-1) < 2^32 (G0 G1 (2p-1) < 2^32 is checked at
+        // set-up, and G1 > 8 at p >= 4)
+        const char* box = reinterpret_cast<const char*>(static_cast<const C*>(pe.e) + (I0 + G0 * (J0 + G1 * K0)));
+        const size_t plane = G0 * G1 * sizeof(C);
+        uint32_t off[LN];
 #pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-            vals[it] = t64 + STEP * it < nP3 ? g[off] : (C)0;
-            qx += DX;
-            qy += DY;
-            off += dstep;
-            if (qx >= nP) { qx -= nP; ++qy; off += cx; }
-            if (qy >= nP) { qy -= nP; off += cy; }
-        }
+        for (int l = 0; l < LN; ++l) off[l] = (ll[l] + (uint32_t)G0 * lh[l]) * (uint32_t)sizeof(C);
 #pragma unroll
-        for (int it = 0; it < NIT; ++it)
-            if (t64 + STEP * it < nP3) pv[t64 + STEP * it] = vals[it];
+        for (int z = 0; z < N; ++z)
+#pragma unroll
+            for (int l = 0; l < LN; ++l) v[l][z] = *reinterpret_cast<const C*>(box + z * plane + off[l]);
     }
-    if (WPP == 1) wave_sync();
-    else __syncthreads();
-    const C* lx = fx + nP2;
-    const C* ly = fy + nP2;
-    const C* lz = fz + nP2;
-    C* dump = sdump[wv];
-    loadA(fy, true, a1);
-    mfma_pass<C, nP, 2, WPP>(pv, dump, a0, lane, sub);
-    loadA(fx, true, a0);
-    mfma_pass<C, nP, 1, WPP>(pv, dump, a1, lane, sub);
+    // z forward: lines (y, x)
+    lines_forward(fz, v, o);
+    C* w[LN];
+#pragma unroll
+    for (int l = 0; l < LN; ++l) w[l] = W + ln[l];
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+#pragma unroll
+        for (int l = 0; l < LN; ++l) w[l][j * N2] = o[l][j];
+    wave_sync();
+    // y forward: lines (z, x)
+#pragma unroll
+    for (int l = 0; l < LN; ++l) w[l] = W + lh[l] * N2 + ll[l];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int l = 0; l < LN; ++l) v[l][i] = w[l][i * N];
+    lines_forward(fy, v, o);
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+#pragma unroll
+        for (int l = 0; l < LN; ++l) w[l][j * N] = o[l][j];
+    wave_sync();
+    // x forward, scaling, x backward: lines (z, y)
     {
-        // backward x basis in the accumulator row order of the forward product
+        C* u[LN];
+        C lyz[LN];
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const int rr = lane % 16, kk = Mfma<C>::row(lane, ks);
-            a1[ks] = (rr < nP && kk < nP) ? fx[rr * nP + kk] : (C)0;
+        for (int l = 0; l < LN; ++l) {
+            u[l] = W + ln[l] * N;
+            lyz[l] = fy[N2 + ll[l]] + fz[N2 + lh[l]];
         }
-        mfma_pass_x2<C, nP, WPP>(pv, dump, a0, a1, lane, sub, lx, ly, lz);
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int l = 0; l < LN; ++l) v[l][i] = u[l][i];
+        lines_forward(fx, v, o);
+        C lx[N];
+        {
+            const ScalarPtr<C> f = reread<C>(fx + N2);
+#pragma unroll
+            for (int j = 0; j < N; ++j) lx[j] = f[j];
+        }
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+#pragma unroll
+            for (int l = 0; l < LN; ++l) o[l][j] *= recip(lx[j] + lyz[l]);
+        lines_backward(fx, o, [&](int l, int i, C s) { u[l][i] = s; });
     }
-    loadA(fy, false, a0);
-    loadA(fz, false, a1);
-    mfma_pass<C, nP, 1, WPP>(pv, dump, a0, lane, sub);
-    mfma_pass<C, nP, 2, WPP>(pv, dump, a1, lane, sub);
-    // patch-major buffer: each patch's values are one contiguous run
-    C* out = static_cast<C*>(pe.d) + (size_t)pidx * nP3;
-    if (active)
-        for (int q = t64; q < nP3; q += 64 * WPP) out[q] = pv[q];
+    wave_sync();
+    // y backward
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+#pragma unroll
+        for (int l = 0; l < LN; ++l) v[l][j] = w[l][j * N];
+    lines_backward(fy, v, [&](int l, int i, C s) { w[l][i * N] = s; });
+    wave_sync();
+    // z backward to the patch-major buffer (each patch's values are one
+    // contiguous run)
+#pragma unroll
+    for (int l = 0; l < LN; ++l) w[l] = W + ln[l];
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+#pragma unroll
+        for (int l = 0; l < LN; ++l) v[l][j] = w[l][j * N2];
+    C* out = static_cast<C*>(pe.d) + (size_t)pidx * N3;
+    lines_backward(fz, v, [&](int l, int i, C s) { (out + i * N2)[(uint32_t)ln[l]] = s; });
 }
 
 template <int P, typename S, typename C, bool MULTI>
-__global__ void __launch_bounds__(256) k_pi_solve_mfma(LaunchTable L) {
-    __shared__ __align__(16) char smem[mfma_lds<P, C>()];
-    pi_solve_mfma_body<P, S, C, MULTI>(L, blockIdx.x, gridDim.x, smem);
+__global__ void __launch_bounds__(256) k_pi_solve_l(LaunchTable L) {
+    __shared__ __align__(16) char smem[solve_l_lds<P, C>()];
+    pi_solve_l_body<P, S, C, MULTI>(L, blockIdx.x, gridDim.x, smem);
 }
 
 template <int P, typename S>
@@ -2741,7 +2745,7 @@ static hipError_t launch_assemble(ProbEntry* ents, int nprob, TableStager* d_tab
 
 
 template <int P, typename S>
-static hipError_t launch_pi_mfma(int accumulate, ProbEntry* ents, int nprob, TableStager* d_tab, hipStream_t s,
+static hipError_t launch_pi_lines(int accumulate, ProbEntry* ents, int nprob, TableStager* d_tab, hipStream_t s,
                                  int gcap) {
     using C = typename Prec<S>::C;
     // 1. assemble r into each problem's global-node array
@@ -2761,11 +2765,10 @@ static hipError_t launch_pi_mfma(int accumulate, ProbEntry* ents, int nprob, Tab
     err = stage_table(L1, ents, nprob, d_tab, s);
     if (err != hipSuccess) return err;
     if (tiles > 0) {
-        constexpr int PPW = 4 / mfma_waves_per_patch<P>();
-        const int grid = (tiles + PPW - 1) / PPW;
+        const int grid = ((tiles + 3) / 4 + 7) / 8 * 8;
         TraceSpan ts("pi_solve", P, Prec<S>::id, s);
-        if (nprob > 1) hipLaunchKernelGGL((k_pi_solve_mfma<P, S, C, true>), dim3(grid), dim3(256), 0, s, L1);
-        else hipLaunchKernelGGL((k_pi_solve_mfma<P, S, C, false>), dim3(grid), dim3(256), 0, s, L1);
+        if (nprob > 1) hipLaunchKernelGGL((k_pi_solve_l<P, S, C, true>), dim3(grid), dim3(256), 0, s, L1);
+        else hipLaunchKernelGGL((k_pi_solve_l<P, S, C, false>), dim3(grid), dim3(256), 0, s, L1);
         err = hipGetLastError();
         if (err != hipSuccess) return err;
     }
@@ -2949,7 +2952,7 @@ static hipError_t launch_pi_t(int accumulate, ProbEntry* ents, int nprob, TableS
     if constexpr (P >= 4) {
         const int gf = g_pi_fused.load(std::memory_order_relaxed);
         const int mode = cfg.pi_fused >= 0 ? cfg.pi_fused : gf >= 0 ? gf : 0;
-        if (mode != 2) return launch_pi_mfma<P, S>(accumulate, ents, nprob, d_tab, s, gcap);
+        if (mode != 2) return launch_pi_lines<P, S>(accumulate, ents, nprob, d_tab, s, gcap);
     }
     using C = typename Prec<S>::C;
     constexpr int CBP = pi_patches_per_tile<P, C>();
@@ -3123,7 +3126,7 @@ static hipError_t launch_pi_p(int prec, int acc, ProbEntry* e, int n, TableStage
 // ---------------------------------------------------------------------------
 // Mixed-degree patch inverse: every degree's default variant (p = 2, 3:
 // solves with the in-tile x-combine in FP64, solves through the patch buffer
-// in FP32/BF16; p = 7: MFMA solves), each of its three phases (assembly,
+// in FP32/BF16; p = 7: wavefront-per-patch solves), each of its three phases (assembly,
 // solves, combine) one persistent launch over all degrees.
 // (the assembly with lanes over nodes: the same sums as the long-row variant
 // with lanes over cells, whose registers would bound the whole launch)
@@ -3141,11 +3144,11 @@ struct SolveBody {
     using C = typename Prec<S>::C;
     using Arg = NoArg;
     static constexpr int CBP = solve_g_tile<P>();
-    static constexpr int kLds = P >= 4 ? mfma_lds<P, C>()
+    static constexpr int kLds = P >= 4 ? solve_l_lds<P, C>()
                               : pi_wave_default<P, S>() ? solve_w_lds<P, C>()
                               : pi_xcomb_default<P, S>() ? solve_x_lds<P, C, CBP>() : solve_g_lds<P, C, CBP>();
     __device__ static __forceinline__ void run(const LaunchTable& L, const NoArg&, int item, int items, char* smem) {
-        if constexpr (P >= 4) pi_solve_mfma_body<P, S, C, true>(L, item, items, smem);
+        if constexpr (P >= 4) pi_solve_l_body<P, S, C, true>(L, item, items, smem);
         else if constexpr (pi_wave_default<P, S>()) pi_solve_w_body<P, S, true>(L, item, items, smem);
         else if constexpr (pi_xcomb_default<P, S>()) pi_solve_x_body<P, S, CBP, true>(L, item, items, smem);
         else pi_solve_g_body<P, S, CBP, true>(L, item, items, smem);
@@ -3174,7 +3177,7 @@ template <int P, typename S> static int pi_solve_tiles(const ProbEntry& e) {
     else return ((npx + solve_g_tile<P>() - 1) / solve_g_tile<P>()) * npy * npz;
 }
 template <int P, typename S> static int pi_solve_items(int t) {
-    if constexpr (P >= 4) return (t + 4 / mfma_waves_per_patch<P>() - 1) / (4 / mfma_waves_per_patch<P>());
+    if constexpr (P >= 4) return (t + 3) / 4;                   // four patches per workgroup
     else if constexpr (pi_wave_default<P, S>()) return (t + 3) / 4;     // four tiles per workgroup
     else return t;
 }
