@@ -1566,147 +1566,111 @@ __global__ void __launch_bounds__(256) k_pi_combine_x(LaunchTable L) {
     pi_combine_x_body<P, S, CBP, ACC, MULTI>(L, blockIdx.x, gridDim.x);
 }
 
-// Assembly into the global-node array: one wavefront per node row (Y, Z),
-// its lanes walking X, so writes are contiguous and the row's y/z copy
-// structure is uniform over the wavefront.  Each node sums its copies in
-// ascending cell order along z, y, x, the same order for every node.
-// pe: a = r (S), e = global array (C); ntiles = ceil(rows / 4).
-template <int P, typename S, typename C, bool MULTI>
-__device__ __forceinline__ void assemble_nodes_body(const LaunchTable& L, int item, int items) {
-    constexpr int N = P + 1, NN = N * N * N;
-    const int tile = item;
-    if (tile >= L.total_tiles) return;
-    const ProbEntry& pe = entry<MULTI>(L, tile);
-    const int n0 = pe.n[0], n1 = pe.n[1], n2 = pe.n[2];
-    const int G0 = n0 * P + 1, G1 = n1 * P + 1, G2 = n2 * P + 1;
-    const int row = (tile - pe.tile_begin) * 4 + (int)(threadIdx.x / 64);
-    if (row >= G1 * G2) return;
-    const int lane = threadIdx.x % 64;
-    const int J = row % G1, K = row / G1;
-    // copies along y and z (uniform): lower cell first
-    const int qy = J / P, ry = J - qy * P, qz = K / P, rz = K - qz * P;
-    const int ny = (ry == 0 && qy >= 1 && qy <= n1 - 1) ? 2 : 1;
-    const int nz = (rz == 0 && qz >= 1 && qz <= n2 - 1) ? 2 : 1;
-    const int cy0 = (ry == 0 && qy >= 1) ? qy - 1 : qy, by0 = (ry == 0 && qy >= 1) ? P : ry;
-    const int cz0 = (rz == 0 && qz >= 1) ? qz - 1 : qz, bz0 = (rz == 0 && qz >= 1) ? P : rz;
-    const S* v = static_cast<const S*>(pe.a);
-    C* out = static_cast<C*>(pe.e) + (size_t)row * G0;
-    for (int I = lane; I < G0; I += 64) {
-        const int qx = I / P, rx = I - qx * P;
-        const bool two = rx == 0 && qx >= 1 && qx <= n0 - 1;        // a second copy along x
-        const int cx0 = (rx == 0 && qx >= 1) ? qx - 1 : qx, ax0 = (rx == 0 && qx >= 1) ? P : rx;
-        // copies along y/z in uniform branches, the x pair loaded together
-        // (the second from the first's address when absent) and selected
-        double val[2][2][2];
-#pragma unroll
-        for (int z = 0; z < 2; ++z)
-#pragma unroll
-            for (int y = 0; y < 2; ++y) {
-                val[z][y][0] = val[z][y][1] = 0.0;
-                if (z < nz && y < ny) {
-                    const int e = cx0 + n0 * ((cy0 + y) + n1 * (cz0 + z));
-                    const int lyz = N * ((y ? 0 : by0) + N * (z ? 0 : bz0));
-                    val[z][y][0] = load_as<double>(v + cell_offset(e, ax0 + lyz, NN));
-                    val[z][y][1] = load_as<double>(v + (two ? cell_offset(e + 1, lyz, NN) : cell_offset(e, ax0 + lyz, NN)));
-                }
-            }
-        double s = 0.0;
-#pragma unroll
-        for (int z = 0; z < 2; ++z)
-#pragma unroll
-            for (int y = 0; y < 2; ++y) {
-                if (z >= nz || y >= ny) continue;
-                s += val[z][y][0];
-                s = two ? s + val[z][y][1] : s;
-            }
-        out[I] = (C)s;
-    }
+// Assembly into the global-node array: one wavefront per (storage block, node
+// row (b, c)) of cells, lanes on the block's 64 cells.  A lane owns its cell's
+// nodes a < P of the row (a = P too in the last cell along x; rows b = P and
+// c = P only in the last cells along y and z), and adds to them the copies of
+// its lower neighbours: along x by a lane shuffle, along y and z by loading the
+// neighbours' rows (again runs of consecutive cells).  So every load is a run
+// of consecutive cells of a storage block and every value of r is read about
+// once, whatever the length of the mesh rows.  Each node sums its copies in
+// ascending cell order along z, y, x, the same order for every node.  Bound by
+// reading r and writing the nodes once: Q7 24^3 FP32 11 us (4.2 TB/s), FP64
+// 20 us (4.7 TB/s), Q3 64^3 FP64 30 us, Q2 96^3 FP64 46 us; lanes on the nodes
+// of a mesh row, each load 64 different lines of r, took 26, 26, 34 and 61 us.
+// For 8-byte nodes at p >= 3 the row's runs go through LDS and leave with lanes
+// on consecutive nodes (stores 8 p bytes apart: 25 us at Q7 24^3 against 20, 32
+// at Q3 64^3 against 30; 4-byte nodes and p = 2 measured 3-8% faster without).
+// At p >= 4 neighbouring blocks run on one XCD (5-8% faster; at p <= 3 5-15%
+// slower).
+// pe: a = r (S), e = global array (C); tiles of four wavefronts.
+__host__ __device__ inline int assemble_waves(const ProbEntry& e, int P) {
+    const int top = e.nblk - e.n[0] * e.n[1] * (e.n[2] - 1) / kLanes;      // blocks with cells of the last layer
+    return (P + 1) * (e.nblk * P + top);
+}
+
+template <int P, typename C> constexpr bool assemble_staged() { return P >= 3 && sizeof(C) == 8; }
+template <int P, typename C> constexpr int assemble_lds() {
+    return assemble_staged<P, C>() ? 4 * 64 * (P + 1) * 8 : 16;      // per wavefront: P nodes and an address per lane
 }
 
 template <int P, typename S, typename C, bool MULTI>
-__global__ void __launch_bounds__(256) k_assemble_nodes(LaunchTable L) {
-    assemble_nodes_body<P, S, C, MULTI>(L, blockIdx.x, gridDim.x);
-}
-
-// The same assembly for long rows: one wavefront per node row (Y, Z) with
-// lane i on cell column i (64 cells per pass along x).  For each of the
-// row's y/z copies (uniform over the wavefront) a lane loads its cell's p+1
-// nodes along x, so every load is a run of consecutive cells of a storage
-// block; the node a cell shares with its left neighbour takes the
-// neighbour's last node through a lane shuffle.  Terms are added in the same
-// order as k_assemble_nodes (ascending cell order along z, y, x), so the two
-// kernels give identical results.
-template <int P, typename S, typename C, bool MULTI>
-__device__ __forceinline__ void assemble_cells_body(const LaunchTable& L, int item, int items) {
+__device__ __forceinline__ void assemble_body(const LaunchTable& L, int item, int items, char* smem) {
     constexpr int N = P + 1, NN = N * N * N;
-    const int tile = item;
+    const int tile = P >= 4 ? xcd_tile(item, items) : item;
     if (tile >= L.total_tiles) return;
     const ProbEntry& pe = entry<MULTI>(L, tile);
-    const int n0 = pe.n[0], n1 = pe.n[1], n2 = pe.n[2];
-    const int G0 = n0 * P + 1, G1 = n1 * P + 1, G2 = n2 * P + 1;
-    const int row = (tile - pe.tile_begin) * 4 + (int)(threadIdx.x / 64);
-    if (row >= G1 * G2) return;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
+    const int wave = (tile - pe.tile_begin) * 4 + wv;
+    if (wave >= assemble_waves(pe, P)) return;
     const int lane = threadIdx.x % 64;
-    const int J = row % G1, K = row / G1;
-    const int qy = J / P, ry = J - qy * P, qz = K / P, rz = K - qz * P;
-    const int ny = (ry == 0 && qy >= 1 && qy <= n1 - 1) ? 2 : 1;
-    const int nz = (rz == 0 && qz >= 1 && qz <= n2 - 1) ? 2 : 1;
-    const int cy0 = (ry == 0 && qy >= 1) ? qy - 1 : qy, by0 = (ry == 0 && qy >= 1) ? P : ry;
-    const int cz0 = (rz == 0 && qz >= 1) ? qz - 1 : qz, bz0 = (rz == 0 && qz >= 1) ? P : rz;
+    const int n0 = pe.n[0], n1 = pe.n[1], n2 = pe.n[2];
+    // wavefronts: row b fastest, then plane c < P, then block; after all
+    // blocks the planes c = P of the blocks holding cells of the last layer
+    const int b = wave % N, w = wave / N;
+    const bool top = w >= pe.nblk * P;
+    const int blk = top ? n0 * n1 * (n2 - 1) / kLanes + w - pe.nblk * P : w / P, c = top ? P : w % P;
+    const int e = blk * kLanes + lane;
+    const int i = e % n0, j = (e / n0) % n1, k = e / (n0 * n1);
+    const bool own = e < pe.ncells && (b < P || j == n1 - 1) && (c < P || k == n2 - 1);
+    if (__ballot(own) == 0) return;
     const S* v = static_cast<const S*>(pe.a);
-    C* out = static_cast<C*>(pe.e) + (size_t)row * G0;
-    for (int i0 = 0; i0 < n0; i0 += 64) {
-        const int i = i0 + lane;
-        const bool in = i < n0;
-        double val[2][2][N], left[2][2];
+    double acc[N];
 #pragma unroll
-        for (int z = 0; z < 2; ++z)
+    for (int a = 0; a < N; ++a) acc[a] = 0.0;
 #pragma unroll
-            for (int y = 0; y < 2; ++y) {
+    for (int z = 1; z >= 0; --z)
 #pragma unroll
-                for (int a = 0; a < N; ++a) val[z][y][a] = 0.0;
-                left[z][y] = 0.0;
-                if (z < nz && y < ny) {                        // uniform
-                    const int e = i + n0 * ((cy0 + y) + n1 * (cz0 + z));
-                    const int lyz = N * ((y ? 0 : by0) + N * (z ? 0 : bz0));
-                    if (in) {
+        for (int y = 1; y >= 0; --y) {
+            if ((z && c != 0) || (y && b != 0)) continue;      // uniform: no lower copy of this row
+            const bool ok = own && (!z || k > 0) && (!y || j > 0);
+            const int ee = e - (z ? n0 * n1 : 0) - (y ? n0 : 0);
+            const int lyz = N * ((y ? P : b) + N * (z ? P : c));
+            double val[N];
 #pragma unroll
-                        for (int a = 0; a < N; ++a) val[z][y][a] = load_stream<double>(v + cell_offset(e, a + lyz, NN));
-                    }
-                    left[z][y] = __shfl_up(val[z][y][P], 1, 64);
-                    if (lane == 0 && i0 > 0) left[z][y] = load_as<double>(v + cell_offset(e - 1, P + lyz, NN));
-                }
+            for (int a = 0; a < N; ++a) val[a] = 0.0;
+            if (ok) {
+                const S* src = v + cell_offset(ee, lyz, NN);
+#pragma unroll
+                for (int a = 0; a < N; ++a) val[a] = P >= 4 ? load_as<double>(src + a * kLanes) : load_stream<double>(src + a * kLanes);
             }
-        if (in) {
+            double left = __shfl_up(val[P], 1, 64);
+            if (lane == 0 && ok && i > 0) left = load_as<double>(v + cell_offset(ee - 1, P + lyz, NN));
+            if (ok && i > 0) acc[0] += left;                   // lower cell first
+            if (ok) {
 #pragma unroll
-            for (int a = 0; a < P; ++a) {
-                double s = 0.0;
-#pragma unroll
-                for (int z = 0; z < 2; ++z)
-#pragma unroll
-                    for (int y = 0; y < 2; ++y) {
-                        if (z >= nz || y >= ny) continue;
-                        if (a == 0 && i >= 1) s += left[z][y];    // lower cell first
-                        s += val[z][y][a];
-                    }
-                out[i * P + a] = (C)s;
-            }
-            if (i == n0 - 1) {
-                double s = 0.0;
-#pragma unroll
-                for (int z = 0; z < 2; ++z)
-#pragma unroll
-                    for (int y = 0; y < 2; ++y)
-                        if (z < nz && y < ny) s += val[z][y][P];
-                out[n0 * P] = (C)s;
+                for (int a = 0; a < N; ++a) acc[a] += val[a];
             }
         }
+    const size_t G0 = (size_t)n0 * P + 1, G1 = (size_t)n1 * P + 1;
+    C* out = own ? static_cast<C*>(pe.e) + ((size_t)(i * P) + G0 * ((size_t)(j * P + b) + G1 * (size_t)(k * P + c)))
+                 : nullptr;
+    if constexpr (assemble_staged<P, C>()) {
+        // lane t of pass q stores node (64 q + t) % P of lane (64 q + t) / P
+        C* nodes = reinterpret_cast<C*>(smem) + wv * 64 * P;
+        C** row = reinterpret_cast<C**>(smem + 4 * 64 * P * sizeof(C)) + wv * 64;
+        row[lane] = out;
+#pragma unroll
+        for (int a = 0; a < P; ++a) nodes[lane * P + a] = (C)acc[a];
+        if (own && i == n0 - 1) out[P] = (C)acc[P];
+        wave_sync();
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            const int t = 64 * q + lane;
+            C* dst = row[t / P];
+            if (dst) dst[t % P] = nodes[t];
+        }
+    } else if (own) {
+#pragma unroll
+        for (int a = 0; a < P; ++a) out[a] = (C)acc[a];
+        if (i == n0 - 1) out[P] = (C)acc[P];
     }
 }
 
 template <int P, typename S, typename C, bool MULTI>
-__global__ void __launch_bounds__(256) k_assemble_cells(LaunchTable L) {
-    assemble_cells_body<P, S, C, MULTI>(L, blockIdx.x, gridDim.x);
+__global__ void __launch_bounds__(256) k_assemble(LaunchTable L) {
+    __shared__ __align__(16) char smem[assemble_lds<P, C>()];
+    assemble_body<P, S, C, MULTI>(L, blockIdx.x, gridDim.x, smem);
 }
 
 // Fused sweep from the assembled residual (p <= 3): like k_pi_sweep, but the
@@ -1968,13 +1932,12 @@ __global__ void __launch_bounds__(256) k_pi_sweep_g(LaunchTable L) {
 }
 
 template <int P, typename S>
-static hipError_t launch_assemble_nodes(ProbEntry* ents, int nprob, TableStager* d_tab, hipStream_t s) {
+static hipError_t launch_assemble(ProbEntry* ents, int nprob, TableStager* d_tab, hipStream_t s) {
     using C = typename Prec<S>::C;
     int tiles = 0;
     for (int i = 0; i < nprob; ++i) {
-        const int rows = (ents[i].n[1] * P + 1) * (ents[i].n[2] * P + 1);
         ents[i].tile_begin = tiles;
-        ents[i].ntiles = (rows + 3) / 4;
+        ents[i].ntiles = (assemble_waves(ents[i], P) + 3) / 4;
         tiles += ents[i].ntiles;
     }
     LaunchTable L{};
@@ -1982,18 +1945,10 @@ static hipError_t launch_assemble_nodes(ProbEntry* ents, int nprob, TableStager*
     L.total_tiles = tiles;
     hipError_t err = stage_table(L, ents, nprob, d_tab, s);
     if (err != hipSuccess || tiles == 0) return err;
+    const int grid = (tiles + 7) / 8 * 8;
     TraceSpan ts("pi_assemble", P, Prec<S>::id, s);
-    // lanes over cells when every row is long (coalesced loads, no idle
-    // tail pass), lanes over nodes otherwise; identical results either way
-    bool long_rows = true;
-    for (int i = 0; i < nprob; ++i) long_rows = long_rows && ents[i].n[0] >= 48;
-    if (long_rows) {
-        if (nprob > 1) hipLaunchKernelGGL((k_assemble_cells<P, S, C, true>), dim3(tiles), dim3(256), 0, s, L);
-        else hipLaunchKernelGGL((k_assemble_cells<P, S, C, false>), dim3(tiles), dim3(256), 0, s, L);
-    } else {
-        if (nprob > 1) hipLaunchKernelGGL((k_assemble_nodes<P, S, C, true>), dim3(tiles), dim3(256), 0, s, L);
-        else hipLaunchKernelGGL((k_assemble_nodes<P, S, C, false>), dim3(tiles), dim3(256), 0, s, L);
-    }
+    if (nprob > 1) hipLaunchKernelGGL((k_assemble<P, S, C, true>), dim3(grid), dim3(256), 0, s, L);
+    else hipLaunchKernelGGL((k_assemble<P, S, C, false>), dim3(grid), dim3(256), 0, s, L);
     return hipGetLastError();
 }
 
@@ -2008,7 +1963,7 @@ template <typename S> struct SweepGShape<3, S> { static constexpr int TX = 8, TY
 template <int P, typename S>
 static hipError_t launch_pi_sweep_g(int accumulate, ProbEntry* ents, int nprob, TableStager* d_tab, hipStream_t s) {
     constexpr int TX = SweepGShape<P, S>::TX, TY = SweepGShape<P, S>::TY;
-    hipError_t err = launch_assemble_nodes<P, S>(ents, nprob, d_tab, s);
+    hipError_t err = launch_assemble<P, S>(ents, nprob, d_tab, s);
     if (err != hipSuccess) return err;
     LaunchTable L{};
     int tiles = 0;
@@ -2305,7 +2260,7 @@ __global__ void __launch_bounds__(256) k_pi_combine_rows(LaunchTable L) {
 
 // ---------------------------------------------------------------------------
 // High-degree variant (4 <= p <= 7): the residual is first assembled into a
-// global-node array (k_assemble_nodes), so a patch reads its (2p-1)^3 box
+// global-node array (k_assemble), so a patch reads its (2p-1)^3 box
 // without summing copies, one wavefront solves a patch (k_pi_solve_l), and the
 // results go to a patch-major buffer (one contiguous run per patch) for the
 // combine.
@@ -2735,21 +2690,11 @@ __global__ void __launch_bounds__(256) k_pi_solve_l(LaunchTable L) {
 }
 
 template <int P, typename S>
-static hipError_t launch_assemble_nodes(ProbEntry* ents, int nprob, TableStager* d_tab, hipStream_t s);
-
-template <int P, typename S>
-static hipError_t launch_assemble(ProbEntry* ents, int nprob, TableStager* d_tab, hipStream_t s, int gcap) {
-    (void)gcap;
-    return launch_assemble_nodes<P, S>(ents, nprob, d_tab, s);
-}
-
-
-template <int P, typename S>
 static hipError_t launch_pi_lines(int accumulate, ProbEntry* ents, int nprob, TableStager* d_tab, hipStream_t s,
                                  int gcap) {
     using C = typename Prec<S>::C;
     // 1. assemble r into each problem's global-node array
-    hipError_t err = launch_assemble<P, S>(ents, nprob, d_tab, s, gcap);
+    hipError_t err = launch_assemble<P, S>(ents, nprob, d_tab, s);
     if (err != hipSuccess) return err;
     int tiles = 0;
     // 2. one wavefront per patch
@@ -2819,7 +2764,7 @@ template <int P, typename S>
 static hipError_t launch_pi_slabs(int accumulate, ProbEntry e, hipStream_t s, int nslab, int gcap) {
     constexpr int CBP = solve_g_tile<P>();
     constexpr int N = P + 1;
-    hipError_t err = launch_assemble<P, S>(&e, 1, nullptr, s, gcap);
+    hipError_t err = launch_assemble<P, S>(&e, 1, nullptr, s);
     if (err != hipSuccess) return err;
     const int npx = e.n[0] - 1, npy = e.n[1] - 1, npz = e.n[2] - 1;
     const int tpr = (npx + CBP - 1) / CBP;
@@ -2864,7 +2809,7 @@ template <int P, typename S, bool WAVE>
 static hipError_t launch_pi_xcomb(int accumulate, ProbEntry* ents, int nprob, TableStager* d_tab, hipStream_t s,
                                   int gcap) {
     constexpr int CBP = WAVE ? solve_w_tile<P>() : solve_g_tile<P>();
-    hipError_t err = launch_assemble<P, S>(ents, nprob, d_tab, s, gcap);
+    hipError_t err = launch_assemble<P, S>(ents, nprob, d_tab, s);
     if (err != hipSuccess) return err;
     int t1 = 0;
     for (int i = 0; i < nprob; ++i) {
@@ -2989,7 +2934,7 @@ static hipError_t launch_pi_t(int accumulate, ProbEntry* ents, int nprob, TableS
                 if (nprob > 1) hipLaunchKernelGGL((k_pi_solve_r<P, S, CBP, true>), dim3(grid), dim3(256), 0, s, L);
                 else hipLaunchKernelGGL((k_pi_solve_r<P, S, CBP, false>), dim3(grid), dim3(256), 0, s, L);
             } else {
-                err = launch_assemble<P, S>(ents, nprob, d_tab, s, gcap);
+                err = launch_assemble<P, S>(ents, nprob, d_tab, s);
                 if (err != hipSuccess) return err;
                 int t1 = 0;
                 for (int i = 0; i < nprob; ++i) {
@@ -3128,14 +3073,12 @@ static hipError_t launch_pi_p(int prec, int acc, ProbEntry* e, int n, TableStage
 // solves with the in-tile x-combine in FP64, solves through the patch buffer
 // in FP32/BF16; p = 7: wavefront-per-patch solves), each of its three phases (assembly,
 // solves, combine) one persistent launch over all degrees.
-// (the assembly with lanes over nodes: the same sums as the long-row variant
-// with lanes over cells, whose registers would bound the whole launch)
 template <int P, typename S>
 struct AssembleBody {
     using Arg = NoArg;
-    static constexpr int kLds = 0;
-    __device__ static __forceinline__ void run(const LaunchTable& L, const NoArg&, int item, int items, char*) {
-        assemble_nodes_body<P, S, typename Prec<S>::C, true>(L, item, items);
+    static constexpr int kLds = assemble_lds<P, typename Prec<S>::C>();
+    __device__ static __forceinline__ void run(const LaunchTable& L, const NoArg&, int item, int items, char* smem) {
+        assemble_body<P, S, typename Prec<S>::C, true>(L, item, items, smem);
     }
 };
 
@@ -3198,7 +3141,7 @@ static hipError_t launch_pi_mixed_t(ProbEntry* ents, int nprob, TableStager* st,
     MixTable T{};
     int grid = 0;
     // 1. assembly into each problem's global-node array
-    auto rows4 = [](int p, const ProbEntry& e) { return ((e.n[1] * p + 1) * (e.n[2] * p + 1) + 3) / 4; };
+    auto rows4 = [](int p, const ProbEntry& e) { return (assemble_waves(e, p) + 3) / 4; };
     auto same = [](int, int t) { return t; };
     hipError_t err = mix_build(ents, nprob, st, s, rows4, same, T, grid);
     if (err != hipSuccess) return err;
