@@ -49,11 +49,13 @@ __global__ void __launch_bounds__(256) k_dot(LaunchTable L, int group) {
     }
 }
 
-// slots[slot] = sum of the group's tile partials (one workgroup per problem)
+// slots[slot] = sum of the group's tile partials (one workgroup per problem;
+// a second row of workgroups takes group2 into slot2)
 template <bool MULTI>
-__global__ void __launch_bounds__(256) k_red_final(LaunchTable L, int group, int slot) {
+__global__ void __launch_bounds__(256) k_red_final(LaunchTable L, int group1, int slot1, int group2, int slot2) {
     __shared__ double sh[4];
     const int i = blockIdx.x;
+    const int group = blockIdx.y ? group2 : group1, slot = blockIdx.y ? slot2 : slot1;
     const ProbEntry& pe = entry_at<MULTI>(L, i);
     double acc = 0.0;
     for (int t = threadIdx.x; t < pe.ntiles_red; t += 256) acc += pe.red[group * kRedParts + t];
@@ -61,21 +63,59 @@ __global__ void __launch_bounds__(256) k_red_final(LaunchTable L, int group, int
     if (threadIdx.x == 0) red_slots(pe.red)[slot] = s;
 }
 
+// ------------------------------------------------------ copies of a node
+// The copies of local node (a, b, c) of cell (i, j, k), (a, b, c) uniform over
+// the wavefront, visited in ascending cell order along z, y, x:
+// f(cell, local node, cell indices) for each; returns how many.  A direction has a second
+// copy only at its end nodes, so all but the end nodes skip the neighbours in
+// uniform branches (a loop over per-lane lists of copies kept the lists in
+// scratch memory and issued the loads one after the other).
+struct NodeAt { int a, b, c, i, j, k, n0, n1, n2; };
+
+template <int P, class F>
+__device__ __forceinline__ int node_copies(const NodeAt& t, F&& f) {
+    constexpr int N = P + 1, N2 = N * N;
+    const int e = t.i + t.n0 * (t.j + t.n1 * t.k);
+    const int nn01 = t.n0 * t.n1;
+    // per direction: is there a lower / an upper neighbour sharing the node
+    const bool xl = t.a == 0 && t.i > 0, xu = t.a == P && t.i < t.n0 - 1;
+    const bool yl = t.b == 0 && t.j > 0, yu = t.b == P && t.j < t.n1 - 1;
+    const bool zl = t.c == 0 && t.k > 0, zu = t.c == P && t.k < t.n2 - 1;
+    const bool xend = t.a == 0 || t.a == P, yend = t.b == 0 || t.b == P, zend = t.c == 0 || t.c == P;     // uniform
+#pragma unroll
+    for (int z = 0; z < 2; ++z) {
+        if (z && !zend) break;
+        if (z && !(zl || zu)) break;
+        const int dz = z ? (zu ? 1 : 0) : (zl ? -1 : 0), lz = N2 * (z ? (zu ? 0 : t.c) : (zl ? P : t.c));
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+            if (y && !yend) break;
+            if (y && !(yl || yu)) break;
+            const int dy = y ? (yu ? 1 : 0) : (yl ? -1 : 0), ly = N * (y ? (yu ? 0 : t.b) : (yl ? P : t.b));
+            const int ee = e + dz * nn01 + dy * t.n0, dx = xl ? -1 : 0, dx2 = xu ? 1 : 0;
+            f(ee + dx, lz + ly + (xl ? P : t.a), t.i + dx, t.j + dy, t.k + dz);
+            if (xend && (xl || xu)) f(ee + dx2, lz + ly + (xu ? 0 : t.a), t.i + dx2, t.j + dy, t.k + dz);
+        }
+    }
+    return (xl || xu ? 2 : 1) * (yl || yu ? 2 : 1) * (zl || zu ? 2 : 1);
+}
+
 // -------------------------------------------------- assembled norm ||G^T r||^2
-// Each global node is owned by its copy in the lowest-numbered cell along
+// Each global node is owned by its copy in the highest-numbered cell along
 // every direction; the owner sums all copies (fixed order) and squares.
 template <int P, typename S, bool MULTI>
 __device__ __forceinline__ void anorm_body(const LaunchTable& L, int group, int item, int items, char* smem) {
     constexpr int N = P + 1, N2 = N * N, NN = N2 * N;
     double* sh = reinterpret_cast<double*>(smem);
-    const int lane = threadIdx.x % kLanes, lq = threadIdx.x / kLanes;
+    const int lane = threadIdx.x % kLanes, lq = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kLanes));
     for (int tile = item; tile < L.total_tiles; tile += items) {
         const ProbEntry& pe = entry<MULTI>(L, tile);
         const int t = tile - pe.tile_begin;
         size_t lo, hi;
         red_range(pe, t, lo, hi);
         const S* v = static_cast<const S*>(pe.a);
-        const int n0 = pe.n[0], n1 = pe.n[1], n2 = pe.n[2];
+        NodeAt at;
+        at.n0 = pe.n[0], at.n1 = pe.n[1], at.n2 = pe.n[2];
         double acc = 0.0;
         // walk the range block by block: a thread keeps its cell (lane) within a block
         for (size_t base = lo - lo % ((size_t)NN * kLanes); base < hi; base += (size_t)NN * kLanes) {
@@ -84,21 +124,13 @@ __device__ __forceinline__ void anorm_body(const LaunchTable& L, int group, int 
             if (e >= pe.ncells) continue;
             const int lb = base < lo ? (int)((lo - base) / kLanes) : 0;
             const int le = base + (size_t)NN * kLanes > hi ? (int)((hi - base) / kLanes) : NN;
-            const int i = e % n0, j = (e / n0) % n1, k = e / (n0 * n1);
+            at.i = e % at.n0, at.j = (e / at.n0) % at.n1, at.k = e / (at.n0 * at.n1);
             for (int l = lb + lq; l < le; l += 4) {
-                const int a = l % N, b = (l / N) % N, c = l / N2;
-                if ((a == P && i < n0 - 1) || (b == P && j < n1 - 1) || (c == P && k < n2 - 1)) continue;
-                const int cx = (a == 0 && i > 0) ? 2 : 1;
-                const int cy = (b == 0 && j > 0) ? 2 : 1;
-                const int cz = (c == 0 && k > 0) ? 2 : 1;
+                at.a = l % N, at.b = (l / N) % N, at.c = l / N2;
+                if ((at.a == P && at.i < at.n0 - 1) || (at.b == P && at.j < at.n1 - 1) ||
+                    (at.c == P && at.k < at.n2 - 1)) continue;
                 double s = 0.0;
-                for (int sz = 0; sz < cz; ++sz)
-                    for (int sy = 0; sy < cy; ++sy)
-                        for (int sx = 0; sx < cx; ++sx) {
-                            const int ee = (i - sx) + n0 * ((j - sy) + n1 * (k - sz));
-                            const int ll = (sx ? P : a) + N * ((sy ? P : b) + N * (sz ? P : c));
-                            s += load_as<double>(v + cell_offset(ee, ll, NN));
-                        }
+                node_copies<P>(at, [&](int ee, int ll, int, int, int) { s += load_as<double>(v + cell_offset(ee, ll, NN)); });
                 acc += s * s;
             }
         }
@@ -168,7 +200,7 @@ __device__ __forceinline__ void distribute_body(const LaunchTable& L, int group,
                                                 char* smem) {
     constexpr int N = P + 1, N2 = N * N, NN = N2 * N;
     double* sh = reinterpret_cast<double*>(smem);
-    const int lane = threadIdx.x % kLanes, lq = threadIdx.x / kLanes;
+    const int lane = threadIdx.x % kLanes, lq = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kLanes));
     for (int tile = item; tile < L.total_tiles; tile += items) {
         const ProbEntry& pe = entry<MULTI>(L, tile);
         const int t = tile - pe.tile_begin;
@@ -176,7 +208,8 @@ __device__ __forceinline__ void distribute_body(const LaunchTable& L, int group,
         red_range(pe, t, lo, hi);
         const double* v = static_cast<const double*>(pe.a);
         RS* out = static_cast<RS*>(pe.c);
-        const int n0 = pe.n[0], n1 = pe.n[1], n2 = pe.n[2];
+        NodeAt at;
+        at.n0 = pe.n[0], at.n1 = pe.n[1], at.n2 = pe.n[2];
         double os = 1.0;                     // scale of the stored copies
         if constexpr (Prec<RS>::id == FEM_F16) os = f16_residual_scale(pe);
         double acc = 0.0;
@@ -189,48 +222,33 @@ __device__ __forceinline__ void distribute_body(const LaunchTable& L, int group,
                 for (int l = lb + lq; l < le; l += 4) store_from(out + base + (size_t)l * kLanes + lane, (typename Prec<RS>::C)0);
                 continue;
             }
-            const int i = e % n0, j = (e / n0) % n1, k = e / (n0 * n1);
+            at.i = e % at.n0, at.j = (e / at.n0) % at.n1, at.k = e / (at.n0 * at.n1);
             for (int l = lb + lq; l < le; l += 4) {
-                const int a = l % N, b = (l / N) % N, c = l / N2;
-                // sharing cells per direction: (cell, local index), ascending cell
-                int ci[2], ai[2], nx, cj[2], bj[2], ny, ck[2], ck_l[2], nz;
-                if (a == 0 && i > 0) { ci[0] = i - 1; ai[0] = P; ci[1] = i; ai[1] = 0; nx = 2; }
-                else if (a == P && i < n0 - 1) { ci[0] = i; ai[0] = P; ci[1] = i + 1; ai[1] = 0; nx = 2; }
-                else { ci[0] = i; ai[0] = a; nx = 1; }
-                if (b == 0 && j > 0) { cj[0] = j - 1; bj[0] = P; cj[1] = j; bj[1] = 0; ny = 2; }
-                else if (b == P && j < n1 - 1) { cj[0] = j; bj[0] = P; cj[1] = j + 1; bj[1] = 0; ny = 2; }
-                else { cj[0] = j; bj[0] = b; ny = 1; }
-                if (c == 0 && k > 0) { ck[0] = k - 1; ck_l[0] = P; ck[1] = k; ck_l[1] = 0; nz = 2; }
-                else if (c == P && k < n2 - 1) { ck[0] = k; ck_l[0] = P; ck[1] = k + 1; ck_l[1] = 0; nz = 2; }
-                else { ck[0] = k; ck_l[0] = c; nz = 1; }
+                at.a = l % N, at.b = (l / N) % N, at.c = l / N2;
                 double s = 0.0, d = 0.0;
-                for (int z = 0; z < nz; ++z)
-                    for (int y = 0; y < ny; ++y)
-                        for (int x = 0; x < nx; ++x) {
-                            const int ee = ci[x] + n0 * (cj[y] + n1 * ck[z]);
-                            const int ll = ai[x] + N * (bj[y] + N * ck_l[z]);
-                            s += v[cell_offset(ee, ll, NN)];
-                            if (MODE == kDistJacobi) {
-                                const double hx = pe.h[0][ci[x]], hy = pe.h[1][cj[y]], hz = pe.h[2][ck[z]];
-                                const int ax = ai[x], by = bj[y], cz = ck_l[z];
-                                d += (hy * hz / hx) * dg.k[ax] * dg.m[by] * dg.m[cz] +
-                                     (hx * hz / hy) * dg.m[ax] * dg.k[by] * dg.m[cz] +
-                                     (hx * hy / hz) * dg.m[ax] * dg.m[by] * dg.k[cz];
-                            }
-                        }
+                const int copies = node_copies<P>(at, [&](int ee, int ll, int ci, int cj, int ck) {
+                    s += v[cell_offset(ee, ll, NN)];
+                    if (MODE == kDistJacobi) {
+                        const double hx = pe.h[0][ci], hy = pe.h[1][cj], hz = pe.h[2][ck];
+                        const int ax = ll % N, by = (ll / N) % N, cz = ll / N2;
+                        d += (hy * hz / hx) * dg.k[ax] * dg.m[by] * dg.m[cz] +
+                             (hx * hz / hy) * dg.m[ax] * dg.k[by] * dg.m[cz] +
+                             (hx * hy / hz) * dg.m[ax] * dg.m[by] * dg.k[cz];
+                    }
+                });
                 double o;
                 if (MODE == kDistMean) {
-                    o = s / (double)(nx * ny * nz);
+                    o = s / (double)copies;
                 } else {
-                    const bool bnd = pe.dirichlet && ((a == 0 && i == 0) || (a == P && i == n0 - 1) ||
-                                                      (b == 0 && j == 0) || (b == P && j == n1 - 1) ||
-                                                      (c == 0 && k == 0) || (c == P && k == n2 - 1));
+                    const bool bnd = pe.dirichlet && ((at.a == 0 && at.i == 0) || (at.a == P && at.i == at.n0 - 1) ||
+                                                      (at.b == 0 && at.j == 0) || (at.b == P && at.j == at.n1 - 1) ||
+                                                      (at.c == 0 && at.k == 0) || (at.c == P && at.k == at.n2 - 1));
                     o = bnd ? 0.0 : (MODE == kDistJacobi ? s / d : s);
                 }
                 if constexpr (Prec<RS>::id == FEM_F16) o *= os;
                 store_from(out + base + (size_t)l * kLanes + lane, (typename Prec<RS>::C)o);
                 // owner copy: lowest cell along every direction
-                if (ci[0] == i && cj[0] == j && ck[0] == k) acc += s * s;
+                if (!((at.a == 0 && at.i > 0) || (at.b == 0 && at.j > 0) || (at.c == 0 && at.k > 0))) acc += s * s;
             }
         }
         const double r = block_sum(acc, sh);
@@ -576,9 +594,10 @@ ProbEntry entry_of(const fem_problem* P) {
     e.h[1] = P->d_h + P->n[0];
     e.h[2] = P->d_h + P->n[0] + P->n[1];
     e.red = P->d_red;
-    // tiles of about 8192 elements (a few per thread of a 256-thread
-    // workgroup), at most kRedParts; fixed by the problem's own sizes
-    constexpr size_t kTileElems = 8192;
+    // tiles of about 512 elements (two per thread of a 256-thread workgroup),
+    // at most kRedParts; fixed by the problem's own sizes.  (With 8192 a Q2
+    // 12^3 problem had six tiles: 54 us for the distribute pass, 13 for a dot.)
+    constexpr size_t kTileElems = 512;
     const int nn = (P->p + 1) * (P->p + 1) * (P->p + 1);
     size_t want = (P->cell_len + kTileElems - 1) / kTileElems;
     if (want < 1) want = 1;
@@ -716,11 +735,13 @@ hipError_t run_dss_axis(fem_problem* P, void* v, int axis, int prec) {
     return run_dss_axis_entry(P->p, e, axis, prec, P->stream);
 }
 
-static hipError_t finish_reduction(fem_problem* P, const ProbEntry& e, int group, int slot) {
+static hipError_t finish_reduction(fem_problem* P, const ProbEntry& e, int group, int slot, int group2 = -1,
+                                   int slot2 = -1) {
     LaunchTable L{};
     L.nprob = 1;
     L.one = e;
-    hipLaunchKernelGGL(k_red_final<false>, dim3(1), dim3(256), 0, P->stream, L, group, slot);
+    hipLaunchKernelGGL(k_red_final<false>, dim3(1, group2 < 0 ? 1 : 2), dim3(256), 0, P->stream, L, group, slot, group2,
+                       slot2);
     return hipGetLastError();
 }
 
@@ -903,9 +924,7 @@ hipError_t run_dot_qz_rz(fem_problem* P, const double* q, const double* r, const
         return hipGetLastError();
     });
     if (err != hipSuccess) return err;
-    err = finish_reduction(P, e, 0, kSlotQZ);
-    if (err != hipSuccess) return err;
-    return finish_reduction(P, e, 3, kSlotRZ);
+    return finish_reduction(P, e, 0, kSlotQZ, 3, kSlotRZ);
 }
 
 hipError_t run_slot_copy(fem_problem* P, int dst, int src) {
@@ -927,9 +946,10 @@ static int tiles_red(ProbEntry* ents, int nprob) {
     return t;
 }
 
-static hipError_t final_multi(LaunchTable& L, hipStream_t s, int group, int slot) {
-    if (L.nprob > 1) hipLaunchKernelGGL(k_red_final<true>, dim3(L.nprob), dim3(256), 0, s, L, group, slot);
-    else hipLaunchKernelGGL(k_red_final<false>, dim3(1), dim3(256), 0, s, L, group, slot);
+static hipError_t final_multi(LaunchTable& L, hipStream_t s, int group, int slot, int group2 = -1, int slot2 = -1) {
+    const dim3 grid(L.nprob, group2 < 0 ? 1 : 2);
+    if (L.nprob > 1) hipLaunchKernelGGL(k_red_final<true>, grid, dim3(256), 0, s, L, group, slot, group2, slot2);
+    else hipLaunchKernelGGL(k_red_final<false>, grid, dim3(256), 0, s, L, group, slot, group2, slot2);
     return hipGetLastError();
 }
 
@@ -1132,9 +1152,7 @@ hipError_t launch_dot_qz_rz(int zprec, ProbEntry* ents, int nprob, TableStager* 
         return hipGetLastError();
     });
     if (err != hipSuccess) return err;
-    err = final_multi(L, s, 0, kSlotQZ);
-    if (err != hipSuccess) return err;
-    return final_multi(L, s, 3, kSlotRZ);
+    return final_multi(L, s, 0, kSlotQZ, 3, kSlotRZ);
 }
 
 hipError_t launch_slot_copy(ProbEntry* ents, int nprob, TableStager* st, hipStream_t s, int dst, int src) {
