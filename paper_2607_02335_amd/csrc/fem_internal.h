@@ -190,6 +190,7 @@ struct fem_problem {
     void* d_solve;         // pcg_solve vectors, allocated on first use
     size_t solve_bytes;
     double* h_red;         // pinned host mirror of the scalar slots (null for arena problems)
+    hipEvent_t ev_read;    // after a read-back into h_red (null for arena problems)
     bool external_mem;     // buffers carved from caller memory (freed with it)
     // coarse (Q1 on the interior vertices) level of the two-level preconditioner
     int cm[3];             // interior vertices per direction (n - 1)
