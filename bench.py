@@ -143,7 +143,7 @@ def measure_workload(fem, torch, p, n, seed, steps, warmup, prec=0):
 
 # Launch-trace label -> the operation of the hot path it belongs to.
 OP_OF = {"apply": "apply", "mass": "mass", "pi_assemble": "patch_inverse", "pi_solve": "patch_inverse",
-         "pi_combine": "patch_inverse", "pi_sweep": "patch_inverse", "dss_axis": "dss"}
+         "pi_combine": "patch_inverse", "pi_sweep": "patch_inverse", "dss": "dss", "dss_axis": "dss"}
 
 
 def op_bytes(op, p, n, esize=8):

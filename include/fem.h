@@ -167,7 +167,7 @@ fem_status fe_apply(fem_problem* P, const void* x_cell, void* y_cell, int prec);
  * (P_I M), so fe_mass_apply(G f) is the load vector of nodal values f. */
 fem_status fe_mass_apply(fem_problem* P, const void* x_cell, void* y_cell, int prec);
 /* s = G G^T v: every copy receives the sum of all copies of its node
- * (Section 3.3), computed by three axis passes z, y, x (Algorithm
+ * (Section 3.3), by the three axis passes z, y, x in one kernel (Algorithm
  * "Dimensionally-Split Structured Summation").  s may equal v (in place). */
 fem_status fem_dss(fem_problem* P, const void* v, void* s, int prec);
 /* One in-place axis pass of that cascade (axis 0 = x, 1 = y, 2 = z): each
@@ -347,7 +347,7 @@ size_t fem_mb_block_offset(const fem_mb_plan* M, int block);
 fem_status fem_mb_pack(fem_mb_plan* M, const double* canon, void* v_cell, int prec);
 fem_status fem_mb_unpack(fem_mb_plan* M, const void* v_cell, double* canon, int prec);
 /* v <- S v in place, S = G G^T of the multi-block mesh: stage 1 (stages & 1)
- * the structured cascade inside every block (three axis passes per block),
+ * the structured cascade inside every block (one launch per block),
  * stage 2 (stages & 2) the inter-block skeleton in three launches on
  * disjoint copies: cell-face interiors (one pairwise exchange per node, the
  * index on the far side computed from the face orientation bits), cell-edge

@@ -414,7 +414,7 @@ extern "C" fem_status fem_dss(fem_problem* P, const void* v, void* s, int prec) 
     if (v != s)
         FEM_HIP(hipMemcpyAsync(s, v, P->cell_len * prec_bytes(prec), hipMemcpyDeviceToDevice, P->stream),
                 "fem_dss copy");
-    for (int axis = 2; axis >= 0; --axis) FEM_HIP(run_dss_axis(P, s, axis, prec), "fem_dss");
+    FEM_HIP(run_dss(P, s, prec), "fem_dss");
     return FEM_OK;
 }
 

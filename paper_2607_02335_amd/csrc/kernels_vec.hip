@@ -9,6 +9,7 @@
 // in a fixed order (thread-strided sums, a fixed shuffle tree, four wave
 // partials), and a final kernel adds the tile partials in index order.
 #include <cstring>
+#include <type_traits>
 
 #include "fem_internal.h"
 #include "launch.h"
@@ -315,6 +316,86 @@ __global__ void __launch_bounds__(256) k_dss_axis(ProbEntry pe, int axis, long t
     const C s = load_as<C>(pL) + load_as<C>(pR);
     store_from(pL, s);
     store_from(pR, s);
+}
+
+// ------------------------------------------------------------- whole DSS
+// The three axis passes z, y, x of the cascade in one, in place: every shared
+// node is summed and written back by one lane.  One wavefront per (storage
+// block, node row (b, c)), lanes on its cells: a lane sums its cell's nodes of
+// the row with the copies of the lower z and y neighbours (loads of runs of
+// consecutive cells), takes the x neighbour's sum by a shuffle, and writes its
+// cell's row and the lower neighbours' copies of it; only the x copies across a
+// block's edge are read and written by the next block's first lane.  Rows with
+// 0 < b, c hold x-shared nodes alone.  Each node adds in the cascade's own
+// order (bitwise equal to the three passes in FP64 and FP32; 2-byte storage
+// rounds once instead of after every pass).  Bound by reading and writing the
+// (p+1)^3 - (p-1)^3 surface copies of a cell once, where the passes move 3 x 2
+// (p+1)^2 of them: 139 us for 793 MB at Q3 96^3 FP64 (5.7 TB/s), three passes
+// 221 us.
+template <int P, typename S>
+__global__ void __launch_bounds__(256) k_dss(ProbEntry pe, int waves) {
+    using C = typename Prec<S>::C;
+    constexpr int N = P + 1, NN = N * N * N, AP = P * kLanes;
+    const int wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
+    if (wave >= waves) return;
+    const BlockRow br = block_row<P>(pe, wave);
+    const int lane = threadIdx.x % 64, b = br.b, c = br.c;
+    const int n0 = pe.n[0], n1 = pe.n[1], n2 = pe.n[2];
+    const int e = br.blk * kLanes + lane;
+    const int i = e % n0, j = (e / n0) % n1, k = e / (n0 * n1);
+    const bool own = e < pe.ncells && (b < P || j == n1 - 1) && (c < P || k == n2 - 1);
+    if (__ballot(own) == 0) return;
+    const bool all = b == 0 || c == 0;                       // uniform: every node of the row may be shared
+    const bool y2 = own && b == 0 && j > 0, z2 = own && c == 0 && k > 0;
+    S* v = static_cast<S*>(pe.c);
+    // the row's copies in cell column ee: own, lower y, lower z, lower y and z
+    auto copy = [&](int ee, int y, int z) -> S* {
+        return v + cell_offset(ee - (y ? n0 : 0) - (z ? n0 * n1 : 0), N * ((y ? P : b) + N * (z ? P : c)), NN);
+    };
+    // z and y passes of node offset o of column ee
+    auto column = [&](int ee, int o) -> C {
+        C s = load_as<C>(copy(ee, 0, 0) + o);
+        if (z2) s = load_as<C>(copy(ee, 0, 1) + o) + s;
+        if (y2) {
+            C t = load_as<C>(copy(ee, 1, 0) + o);
+            if (z2) t = load_as<C>(copy(ee, 1, 1) + o) + t;
+            s = t + s;
+        }
+        return s;
+    };
+    C sum[N];
+#pragma unroll
+    for (int a = 0; a < N; ++a) sum[a] = (C)0;
+    if (own) {
+#pragma unroll
+        for (int a = 0; a < N; ++a)
+            if (all || a == 0 || a == P) sum[a] = column(e, a * kLanes);
+    }
+    // x pass
+    C left = __shfl_up(sum[P], 1, 64);
+    const bool edge = own && lane == 0 && i > 0;             // the left copies lie in the previous block
+    if (edge) left = column(e - 1, AP);
+    if (own && i > 0) sum[0] = left + sum[0];
+    const C right = __shfl_down(sum[0], 1, 64);
+    if (!own) return;
+    auto put = [&](int y, int z) {
+        S* p = copy(e, y, z);
+        if (all || i > 0) store_from(p, sum[0]);
+        if (all) {
+#pragma unroll
+            for (int a = 1; a < P; ++a) store_from(p + a * kLanes, sum[a]);
+        }
+        if (i == n0 - 1) {
+            if (all) store_from(p + AP, sum[P]);
+        } else if (lane < 63) {
+            store_from(p + AP, right);
+        }
+        if (edge) store_from(copy(e - 1, y, z) + AP, sum[0]);
+    };
+    put(0, 0);
+    if (y2) put(1, 0);
+    if (z2) put(0, 1);
+    if (y2 && z2) put(1, 1);
 }
 
 // ------------------------------------------------------------ converters
@@ -706,33 +787,51 @@ static void launch_dss_axis(const ProbEntry& e, int axis, long total, hipStream_
     hipLaunchKernelGGL((k_dss_axis<P_, S>), dim3((total + 255) / 256), dim3(256), 0, s, e, axis, total);
 }
 
-hipError_t run_dss_axis_entry(int p, const ProbEntry& e, int axis, int prec, hipStream_t st) {
-    const int N = p + 1;
+// f<P>() for degree p
+template <typename F>
+static hipError_t by_degree(int p, F&& f) {
+    switch (p) {
+        case 1: f(std::integral_constant<int, 1>{}); break;
+        case 2: f(std::integral_constant<int, 2>{}); break;
+        case 3: f(std::integral_constant<int, 3>{}); break;
+        case 4: f(std::integral_constant<int, 4>{}); break;
+        case 5: f(std::integral_constant<int, 5>{}); break;
+        case 6: f(std::integral_constant<int, 6>{}); break;
+        case 7: f(std::integral_constant<int, 7>{}); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t run_dss_axis(fem_problem* P, void* v, int axis, int prec) {
+    ProbEntry e = entry_of(P);
+    e.c = v;
+    const int N = P->p + 1;
     long total;
     if (axis == 0) total = (long)(e.n[0] - 1) * e.n[1] * e.n[2] * N * N;
     else if (axis == 1) total = (long)e.n[0] * (e.n[1] - 1) * e.n[2] * N * N;
     else total = (long)e.n[0] * e.n[1] * (e.n[2] - 1) * N * N;
     if (total <= 0) return hipSuccess;
     return dispatch_prec(prec, [&](auto tag) {
-        using S = decltype(tag);
-        switch (p) {
-            case 1: launch_dss_axis<1, S>(e, axis, total, st); break;
-            case 2: launch_dss_axis<2, S>(e, axis, total, st); break;
-            case 3: launch_dss_axis<3, S>(e, axis, total, st); break;
-            case 4: launch_dss_axis<4, S>(e, axis, total, st); break;
-            case 5: launch_dss_axis<5, S>(e, axis, total, st); break;
-            case 6: launch_dss_axis<6, S>(e, axis, total, st); break;
-            case 7: launch_dss_axis<7, S>(e, axis, total, st); break;
-            default: return hipErrorInvalidValue;
-        }
-        return hipGetLastError();
+        return by_degree(P->p, [&](auto d) { launch_dss_axis<decltype(d)::value, decltype(tag)>(e, axis, total, P->stream); });
     });
 }
 
-hipError_t run_dss_axis(fem_problem* P, void* v, int axis, int prec) {
+hipError_t run_dss_entry(int p, const ProbEntry& e, int prec, hipStream_t st) {
+    const int waves = block_rows(e, p);
+    return dispatch_prec(prec, [&](auto tag) {
+        using S = decltype(tag);
+        return by_degree(p, [&](auto d) {
+            TraceSpan ts("dss", p, Prec<S>::id, st);
+            hipLaunchKernelGGL((k_dss<decltype(d)::value, S>), dim3((waves + 3) / 4), dim3(256), 0, st, e, waves);
+        });
+    });
+}
+
+hipError_t run_dss(fem_problem* P, void* v, int prec) {
     ProbEntry e = entry_of(P);
     e.c = v;
-    return run_dss_axis_entry(P->p, e, axis, prec, P->stream);
+    return run_dss_entry(P->p, e, prec, P->stream);
 }
 
 static hipError_t finish_reduction(fem_problem* P, const ProbEntry& e, int group, int slot, int group2 = -1,

@@ -55,6 +55,21 @@ __host__ __device__ inline void red_range(const ProbEntry& pe, int t, size_t& lo
     if (lo > hi) lo = hi;
 }
 
+// Wavefronts of a kernel that gives every (storage block, node row (b, c)) one
+// wavefront, lanes on the block's cells, each owning the nodes below P of its
+// cell: rows b = 0..P of the planes c < P of every block, then of the plane
+// c = P of the blocks holding cells of the last layer.
+struct BlockRow { int blk, b, c; };
+__host__ __device__ inline int block_rows(const ProbEntry& e, int P) {
+    const int top = e.nblk - e.n[0] * e.n[1] * (e.n[2] - 1) / kLanes;
+    return (P + 1) * (e.nblk * P + top);
+}
+template <int P> __device__ __forceinline__ BlockRow block_row(const ProbEntry& e, int wave) {
+    const int w = wave / (P + 1);
+    const bool top = w >= e.nblk * P;
+    return {top ? e.n[0] * e.n[1] * (e.n[2] - 1) / kLanes + w - e.nblk * P : w / P, wave % (P + 1), top ? P : w % P};
+}
+
 // 1D reference matrices of degree p on [0,1] (row-major, (p+1)^2), built on
 // the host once per process.
 const double* ref_mass(int p);
@@ -172,8 +187,10 @@ ProbEntry coarse_entry(fem_problem* P, const void* t, void* z);
 // Single-problem helpers (problem handle in, stream of the handle).
 ProbEntry entry_of(const fem_problem* P);
 hipError_t run_dss_axis(fem_problem* P, void* v, int axis, int prec);
-// The same axis pass on the mesh of an entry (e.n, e.c = vector).
-hipError_t run_dss_axis_entry(int p, const ProbEntry& e, int axis, int prec, hipStream_t s);
+// All three axis passes in one, in place, on the mesh of an entry (e.n, e.nblk,
+// e.ncells, e.c = vector).
+hipError_t run_dss_entry(int p, const ProbEntry& e, int prec, hipStream_t s);
+hipError_t run_dss(fem_problem* P, void* v, int prec);
 hipError_t run_gather(fem_problem* P, const double* xg, void* xc, int prec);
 hipError_t run_scatter(fem_problem* P, const void* yc, double* yg, int prec);
 hipError_t run_extract(fem_problem* P, const void* uc, double* ug, int prec);

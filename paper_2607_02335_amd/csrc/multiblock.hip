@@ -484,8 +484,9 @@ extern "C" fem_status fem_mb_dss(fem_mb_plan* M, void* v, int prec, int stages) 
             for (int d = 0; d < 3; ++d) e.n[d] = M->n[b][d];
             e.p = M->p;
             e.c = static_cast<char*>(v) + (size_t)M->off[b] * es;
-            for (int axis = 2; axis >= 0; --axis)
-                FEM_HIP(run_dss_axis_entry(M->p, e, axis, prec, M->stream), "fem_mb_dss structured");
+            e.ncells = e.n[0] * e.n[1] * e.n[2];
+            e.nblk = (e.ncells + kLanes - 1) / kLanes;
+            FEM_HIP(run_dss_entry(M->p, e, prec, M->stream), "fem_mb_dss structured");
         }
     }
     if (stages & 2) {

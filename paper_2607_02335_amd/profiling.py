@@ -37,6 +37,7 @@ _LABELS = [
     ("k_pi_combine", "pi_combine"),
     ("k_pi_sweep", "pi_sweep"),
     ("k_dss_axis", "dss_axis"),
+    ("k_dss", "dss"),
     ("k_dot", "dot"),
     ("k_anorm", "assembled_norm"),
     ("k_distribute", "distribute"),
