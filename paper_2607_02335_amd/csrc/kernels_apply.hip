@@ -75,14 +75,18 @@ __device__ __forceinline__ bool on_boundary(const CellGeom<C>& g, int a, int b, 
 // cells) per wavefront.
 // The kernel body takes the workgroup index and the grid size as arguments
 // (here and below), so that a mixed-degree launch can run it on its items.
-template <int P, typename S, int MODE, bool MULTI>
+// SPLIT: one workgroup per block instead, each wavefront producing one output
+// plane from the whole input cell (the same sums): meshes of few blocks leave
+// most SIMDs without a second wavefront otherwise (split_tiles).
+template <int P, typename S, int MODE, bool MULTI, bool SPLIT = false>
 __device__ __forceinline__ void apply_reg_body(const LaunchTable& L, const RefMats<P, typename Prec<S>::C>& R,
                                                int item, int items) {
     using C = typename Prec<S>::C;
     constexpr int N = P + 1, N2 = N * N, NN = N2 * N;
     const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    for (int tile = item * 4 + wv; tile < L.total_tiles; tile += items * 4) {
+    const int wv = SPLIT ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : threadIdx.x >> 6;
+    if (SPLIT && wv >= N) return;
+    for (int tile = SPLIT ? item : item * 4 + wv; tile < L.total_tiles; tile += SPLIT ? items : items * 4) {
         const ProbEntry& pe = entry<MULTI>(L, tile);
         const int blk = tile - pe.tile_begin;
         const int e = blk * kLanes + lane;
@@ -90,7 +94,7 @@ __device__ __forceinline__ void apply_reg_body(const LaunchTable& L, const RefMa
         const S* __restrict__ x = static_cast<const S*>(pe.a) + base;
         S* __restrict__ y = static_cast<S*>(pe.c) + base;
         if (e >= pe.ncells) {
-            for (int l = 0; l < NN; ++l) store_from(y + l * kLanes, (C)0);
+            for (int l = SPLIT ? wv * N2 : 0; l < (SPLIT ? (wv + 1) * N2 : NN); ++l) store_from(y + l * kLanes, (C)0);
             continue;
         }
         const CellGeom<C> g = cell_geom<C>(pe, e);
@@ -110,8 +114,7 @@ __device__ __forceinline__ void apply_reg_body(const LaunchTable& L, const RefMa
         const S* __restrict__ rres = (MODE == kApplyResidual)
             ? static_cast<const S*>(pe.b) + base : nullptr;
 
-#pragma unroll
-        for (int cz = 0; cz < N; ++cz) {
+        auto plane = [&](int cz) {
             C out[N2];
             if (MODE == kApplyMass) {
                 C A[N2], Bp[N2];
@@ -194,14 +197,33 @@ __device__ __forceinline__ void apply_reg_body(const LaunchTable& L, const RefMa
                     if (on_boundary<P>(g, a, b, cz)) v = (C)0;
                     store_from(y + l * kLanes, v);
                 }
+        };
+        if constexpr (SPLIT) {
+            plane(wv);
+        } else {
+#pragma unroll
+            for (int cz = 0; cz < N; ++cz) plane(cz);
         }
     }
 }
 
-template <int P, typename S, int MODE, bool MULTI>
+template <int P, typename S, int MODE, bool MULTI, bool SPLIT>
 __global__ void __launch_bounds__(256)
 k_apply_reg(LaunchTable L, RefMats<P, typename Prec<S>::C> R) {
-    apply_reg_body<P, S, MODE, MULTI>(L, R, blockIdx.x, gridDim.x);
+    apply_reg_body<P, S, MODE, MULTI, SPLIT>(L, R, blockIdx.x, gridDim.x);
+}
+
+// Blocks up to which the register apply gives every output plane a wavefront
+// (p = 2, 3): the whole-cell form runs a block per wavefront, so below a few
+// blocks per SIMD it waits on one wavefront's loads and sums; the plane form
+// loads a cell once per plane, which costs more once the chip is full, and
+// earlier in FP64, where the cell's registers leave few wavefronts.  Whole ->
+// planes at p = 3, n^3 cells (n^3 / 64 blocks), us: residual FP32 n = 8 16 -> 8,
+// 32 26 -> 12, 48 31 -> 23, 56 36 -> 33; FP64 8 21 -> 11, 32 29 -> 23, 40 32 -> 40;
+// apply FP32 8 10 -> 7, 40 13 -> 12, 48 19 -> 19; FP64 8 12 -> 9, 24 13 -> 14,
+// 40 19 -> 31.
+template <int MODE, typename C> constexpr int split_tiles() {
+    return MODE == kApplyResidual ? (sizeof(C) == 8 ? 512 : 3072) : (sizeof(C) == 8 ? 128 : 1024);
 }
 
 // ---------------------------------------------------------------------------
@@ -787,9 +809,14 @@ static hipError_t launch_apply_t(ProbEntry* ents, int nprob, TableStager* d_tab,
                  Prec<S>::id, s);
     if constexpr (P <= 3) {
         if (use_reg) {
+            if (P >= 2 && tiles <= split_tiles<MODE, C>()) {
+                if (nprob > 1) hipLaunchKernelGGL((k_apply_reg<P, S, MODE, true, P >= 2>), dim3(tiles), dim3(256), 0, s, L, R);
+                else hipLaunchKernelGGL((k_apply_reg<P, S, MODE, false, P >= 2>), dim3(tiles), dim3(256), 0, s, L, R);
+                return hipGetLastError();
+            }
             const int grid = (tiles + 3) / 4 < gcap ? (tiles + 3) / 4 : gcap;
-            if (nprob > 1) hipLaunchKernelGGL((k_apply_reg<P, S, MODE, true>), dim3(grid), dim3(256), 0, s, L, R);
-            else hipLaunchKernelGGL((k_apply_reg<P, S, MODE, false>), dim3(grid), dim3(256), 0, s, L, R);
+            if (nprob > 1) hipLaunchKernelGGL((k_apply_reg<P, S, MODE, true, false>), dim3(grid), dim3(256), 0, s, L, R);
+            else hipLaunchKernelGGL((k_apply_reg<P, S, MODE, false, false>), dim3(grid), dim3(256), 0, s, L, R);
             return hipGetLastError();
         }
     }
