@@ -1584,9 +1584,13 @@ __global__ void __launch_bounds__(256) k_pi_combine_x(LaunchTable L) {
 // At p >= 4 neighbouring blocks run on one XCD (5-8% faster; at p <= 3 5-15%
 // slower).
 // pe: a = r (S), e = global array (C); tiles of four wavefronts.
-__host__ __device__ inline int assemble_waves(const ProbEntry& e, int P) {
-    const int top = e.nblk - e.n[0] * e.n[1] * (e.n[2] - 1) / kLanes;      // blocks with cells of the last layer
-    return (P + 1) * (e.nblk * P + top);
+// Rows per wavefront: launches over several problems search the entry table
+// once per wavefront, a chain of dependent loads as long as a row's own work
+// (the assembly of a 256-problem batch: 622 us with one row, 589 with four).
+template <bool MULTI> __host__ __device__ constexpr int wave_rows() { return MULTI ? 4 : 1; }
+static inline int row_tiles(int rows, bool multi) {
+    const int per = 4 * (multi ? wave_rows<true>() : wave_rows<false>());
+    return (rows + per - 1) / per;
 }
 
 template <int P, typename C> constexpr bool assemble_staged() { return P >= 3 && sizeof(C) == 8; }
@@ -1601,69 +1605,70 @@ __device__ __forceinline__ void assemble_body(const LaunchTable& L, int item, in
     if (tile >= L.total_tiles) return;
     const ProbEntry& pe = entry<MULTI>(L, tile);
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
-    const int wave = (tile - pe.tile_begin) * 4 + wv;
-    if (wave >= assemble_waves(pe, P)) return;
-    const int lane = threadIdx.x % 64;
-    const int n0 = pe.n[0], n1 = pe.n[1], n2 = pe.n[2];
-    // wavefronts: row b fastest, then plane c < P, then block; after all
-    // blocks the planes c = P of the blocks holding cells of the last layer
-    const int b = wave % N, w = wave / N;
-    const bool top = w >= pe.nblk * P;
-    const int blk = top ? n0 * n1 * (n2 - 1) / kLanes + w - pe.nblk * P : w / P, c = top ? P : w % P;
-    const int e = blk * kLanes + lane;
-    const int i = e % n0, j = (e / n0) % n1, k = e / (n0 * n1);
-    const bool own = e < pe.ncells && (b < P || j == n1 - 1) && (c < P || k == n2 - 1);
-    if (__ballot(own) == 0) return;
-    const S* v = static_cast<const S*>(pe.a);
-    double acc[N];
+    const int lane = threadIdx.x % 64, waves = block_rows(pe, P);
+#pragma unroll 1
+    for (int rr = 0; rr < wave_rows<MULTI>(); ++rr) {
+        const int wave = ((tile - pe.tile_begin) * wave_rows<MULTI>() + rr) * 4 + wv;
+        if (wave >= waves) return;
+        const int n0 = pe.n[0], n1 = pe.n[1], n2 = pe.n[2];
+        const BlockRow br = block_row<P>(pe, wave);
+        const int b = br.b, c = br.c;
+        const int e = br.blk * kLanes + lane;
+        const int i = e % n0, j = (e / n0) % n1, k = e / (n0 * n1);
+        const bool own = e < pe.ncells && (b < P || j == n1 - 1) && (c < P || k == n2 - 1);
+        if (__ballot(own) == 0) continue;
+        const S* v = static_cast<const S*>(pe.a);
+        double acc[N];
 #pragma unroll
-    for (int a = 0; a < N; ++a) acc[a] = 0.0;
+        for (int a = 0; a < N; ++a) acc[a] = 0.0;
 #pragma unroll
-    for (int z = 1; z >= 0; --z)
+        for (int z = 1; z >= 0; --z)
 #pragma unroll
-        for (int y = 1; y >= 0; --y) {
-            if ((z && c != 0) || (y && b != 0)) continue;      // uniform: no lower copy of this row
-            const bool ok = own && (!z || k > 0) && (!y || j > 0);
-            const int ee = e - (z ? n0 * n1 : 0) - (y ? n0 : 0);
-            const int lyz = N * ((y ? P : b) + N * (z ? P : c));
-            double val[N];
+            for (int y = 1; y >= 0; --y) {
+                if ((z && c != 0) || (y && b != 0)) continue;      // uniform: no lower copy of this row
+                const bool ok = own && (!z || k > 0) && (!y || j > 0);
+                const int ee = e - (z ? n0 * n1 : 0) - (y ? n0 : 0);
+                const int lyz = N * ((y ? P : b) + N * (z ? P : c));
+                double val[N];
 #pragma unroll
-            for (int a = 0; a < N; ++a) val[a] = 0.0;
-            if (ok) {
-                const S* src = v + cell_offset(ee, lyz, NN);
+                for (int a = 0; a < N; ++a) val[a] = 0.0;
+                if (ok) {
+                    const S* src = v + cell_offset(ee, lyz, NN);
 #pragma unroll
-                for (int a = 0; a < N; ++a) val[a] = P >= 4 ? load_as<double>(src + a * kLanes) : load_stream<double>(src + a * kLanes);
+                    for (int a = 0; a < N; ++a) val[a] = P >= 4 ? load_as<double>(src + a * kLanes) : load_stream<double>(src + a * kLanes);
+                }
+                double left = __shfl_up(val[P], 1, 64);
+                if (lane == 0 && ok && i > 0) left = load_as<double>(v + cell_offset(ee - 1, P + lyz, NN));
+                if (ok && i > 0) acc[0] += left;                   // lower cell first
+                if (ok) {
+#pragma unroll
+                    for (int a = 0; a < N; ++a) acc[a] += val[a];
+                }
             }
-            double left = __shfl_up(val[P], 1, 64);
-            if (lane == 0 && ok && i > 0) left = load_as<double>(v + cell_offset(ee - 1, P + lyz, NN));
-            if (ok && i > 0) acc[0] += left;                   // lower cell first
-            if (ok) {
+        const size_t G0 = (size_t)n0 * P + 1, G1 = (size_t)n1 * P + 1;
+        C* out = own ? static_cast<C*>(pe.e) + ((size_t)(i * P) + G0 * ((size_t)(j * P + b) + G1 * (size_t)(k * P + c)))
+                     : nullptr;
+        if constexpr (assemble_staged<P, C>()) {
+            // lane t of pass q stores node (64 q + t) % P of lane (64 q + t) / P
+            C* nodes = reinterpret_cast<C*>(smem) + wv * 64 * P;
+            C** row = reinterpret_cast<C**>(smem + 4 * 64 * P * sizeof(C)) + wv * 64;
+            row[lane] = out;
 #pragma unroll
-                for (int a = 0; a < N; ++a) acc[a] += val[a];
+            for (int a = 0; a < P; ++a) nodes[lane * P + a] = (C)acc[a];
+            if (own && i == n0 - 1) out[P] = (C)acc[P];
+            wave_sync();
+#pragma unroll
+            for (int q = 0; q < P; ++q) {
+                const int t = 64 * q + lane;
+                C* dst = row[t / P];
+                if (dst) dst[t % P] = nodes[t];
             }
+            wave_sync();
+        } else if (own) {
+#pragma unroll
+            for (int a = 0; a < P; ++a) out[a] = (C)acc[a];
+            if (i == n0 - 1) out[P] = (C)acc[P];
         }
-    const size_t G0 = (size_t)n0 * P + 1, G1 = (size_t)n1 * P + 1;
-    C* out = own ? static_cast<C*>(pe.e) + ((size_t)(i * P) + G0 * ((size_t)(j * P + b) + G1 * (size_t)(k * P + c)))
-                 : nullptr;
-    if constexpr (assemble_staged<P, C>()) {
-        // lane t of pass q stores node (64 q + t) % P of lane (64 q + t) / P
-        C* nodes = reinterpret_cast<C*>(smem) + wv * 64 * P;
-        C** row = reinterpret_cast<C**>(smem + 4 * 64 * P * sizeof(C)) + wv * 64;
-        row[lane] = out;
-#pragma unroll
-        for (int a = 0; a < P; ++a) nodes[lane * P + a] = (C)acc[a];
-        if (own && i == n0 - 1) out[P] = (C)acc[P];
-        wave_sync();
-#pragma unroll
-        for (int q = 0; q < P; ++q) {
-            const int t = 64 * q + lane;
-            C* dst = row[t / P];
-            if (dst) dst[t % P] = nodes[t];
-        }
-    } else if (own) {
-#pragma unroll
-        for (int a = 0; a < P; ++a) out[a] = (C)acc[a];
-        if (i == n0 - 1) out[P] = (C)acc[P];
     }
 }
 
@@ -1937,7 +1942,7 @@ static hipError_t launch_assemble(ProbEntry* ents, int nprob, TableStager* d_tab
     int tiles = 0;
     for (int i = 0; i < nprob; ++i) {
         ents[i].tile_begin = tiles;
-        ents[i].ntiles = (assemble_waves(ents[i], P) + 3) / 4;
+        ents[i].ntiles = row_tiles(block_rows(ents[i], P), nprob > 1);
         tiles += ents[i].ntiles;
     }
     LaunchTable L{};
@@ -2320,6 +2325,7 @@ __device__ __forceinline__ void pi_combine_pm_body(const LaunchTable& L, int ite
                         const int vy = j + sy;
                         const bool yok = zok && !((sy == 0 && b == P) || (sy == 1 && b == 0)) && vy >= 1 && vy <= npy;
                         const int qy = sy == 0 ? P - 1 + b : b - 1;
+                        C xs = 0;
 #pragma unroll
                         for (int sx = 0; sx < 2; ++sx) {
                             const int vx = i + sx;
@@ -2329,8 +2335,9 @@ __device__ __forceinline__ void pi_combine_pm_body(const LaunchTable& L, int ite
                                                         qx + nP * qy + nP2 * qzs[t < nz ? t : 0]
                                                   : 0;
                             const C v = pbuf[off];
-                            sum = ok ? sum + v : sum;
+                            xs = ok ? xs + v : xs;
                         }
+                        sum = yok ? sum + xs : sum;
                     }
                 }
                 sz[ab * RS + cl] = sum;
@@ -2365,9 +2372,6 @@ __global__ void __launch_bounds__(256) k_pi_combine_pm(LaunchTable L) {
 // Bitwise equal to k_pi_combine_pm.  The first row of a problem zeroes the
 // padding cells of its last storage block.
 constexpr int kNrCells = 32;
-// default p >= 4 combine by precision only: node rows for FP64 (measured
-// faster there), per (block, plane) for 4- and 2-byte values
-template <typename S> constexpr bool pm_rows_default() { return Prec<S>::id == FEM_F64; }
 template <int P, typename C> constexpr int nr_lds() { return (kNrCells * P + 1) * (int)sizeof(C); }
 
 template <int P, typename S, int ACC, bool MULTI>
@@ -2440,7 +2444,8 @@ __device__ __forceinline__ void pi_combine_nr_body(const LaunchTable& L, int ite
 #pragma unroll
             for (int tz = 0; tz < 2; ++tz)
 #pragma unroll
-                for (int ty = 0; ty < 2; ++ty)
+                for (int ty = 0; ty < 2; ++ty) {
+                    C xs = 0;
 #pragma unroll
                     for (int tx = 0; tx < 2; ++tx) {
                         const bool ok = tz < nzp && ty < nyp && tx < nxp;
@@ -2449,8 +2454,10 @@ __device__ __forceinline__ void pi_combine_nr_body(const LaunchTable& L, int ite
                                      nP * qyp[ty] + nP2 * qzp[tz]
                                : 0;
                         const C v = pbuf[off];
-                        sum = ok ? sum + v : sum;
+                        xs = ok ? xs + v : xs;
                     }
+                    sum = tz < nzp && ty < nyp ? sum + xs : sum;
+                }
             sx[tid] = sum;
         }
         __syncthreads();
@@ -2571,23 +2578,16 @@ __device__ __forceinline__ void lines_backward(ScalarPtr<C> S, const C (&v)[LN][
     });
 }
 
-// pe: e = assembled global residual (C), d = patch buffer (C), fd = FD data (C)
-template <int P, typename S, typename C, bool MULTI>
-__device__ __forceinline__ void pi_solve_l_body(const LaunchTable& L, int item, int items, char* smem) {
-    constexpr int N = 2 * P - 1, N2 = N * N, N3 = N2 * N;
+// The solve of patch (vi, vj, vk) by one wavefront; W = its (2p-1)^3 words of
+// LDS, out = its (2p-1)^3 results.
+template <int P, typename C>
+__device__ __forceinline__ void solve_lines(const ProbEntry& pe, int vi, int vj, int vk, int lane, C* W, C* out) {
+    constexpr int N = 2 * P - 1, N2 = N * N;
     constexpr int REC = fd_record(P);
     constexpr int LN = (N2 + 63) / 64;                // lines per lane
-    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int tile = xcd_tile(item, items) * 4 + wv;  // neighbouring patches on one XCD
-    if (tile >= L.total_tiles) return;                // per wavefront: no workgroup barrier follows
-    const ProbEntry& pe = entry<MULTI>(L, tile);
-    const int pidx = tile - pe.tile_begin;
-    const int npx = pe.n[0] - 1, npy = pe.n[1] - 1;
-    const int vi = 1 + pidx % npx, vj = 1 + (pidx / npx) % npy, vk = 1 + pidx / (npx * npy);
     const ScalarPtr<C> fx = (ScalarPtr<C>)(static_cast<const C*>(pe.fd[0]) + (size_t)(vi - 1) * REC);
     const ScalarPtr<C> fy = (ScalarPtr<C>)(static_cast<const C*>(pe.fd[1]) + (size_t)(vj - 1) * REC);
     const ScalarPtr<C> fz = (ScalarPtr<C>)(static_cast<const C*>(pe.fd[2]) + (size_t)(vk - 1) * REC);
-    C* const W = reinterpret_cast<C*>(smem) + wv * N3;
     // a lane's lines; lanes past the last line repeat it (the same values to
     // the same words)
     int ln[LN], lh[LN], ll[LN];
@@ -2671,33 +2671,199 @@ __device__ __forceinline__ void pi_solve_l_body(const LaunchTable& L, int item, 
         for (int l = 0; l < LN; ++l) v[l][j] = w[l][j * N];
     lines_backward(fy, v, [&](int l, int i, C s) { w[l][i * N] = s; });
     wave_sync();
-    // z backward to the patch-major buffer (each patch's values are one
-    // contiguous run)
+    // z backward
 #pragma unroll
     for (int l = 0; l < LN; ++l) w[l] = W + ln[l];
 #pragma unroll
     for (int j = 0; j < N; ++j)
 #pragma unroll
         for (int l = 0; l < LN; ++l) v[l][j] = w[l][j * N2];
-    C* out = static_cast<C*>(pe.d) + (size_t)pidx * N3;
     lines_backward(fz, v, [&](int l, int i, C s) { (out + i * N2)[(uint32_t)ln[l]] = s; });
 }
 
-template <int P, typename S, typename C, bool MULTI>
-__global__ void __launch_bounds__(256) k_pi_solve_l(LaunchTable L) {
-    __shared__ __align__(16) char smem[solve_l_lds<P, C>()];
-    pi_solve_l_body<P, S, C, MULTI>(L, blockIdx.x, gridDim.x, smem);
+// The patch-major buffer: each patch's values are one contiguous run.  (Adding
+// the x-overlaps of four patches in LDS and writing runs of global nodes, a
+// third less to write and read back, cost the solves more than it saved the
+// combine: 129 -> 150 us against 70 -> 49 in FP64, 82 -> 93 against 47 -> 35 in
+// FP32.)
+// pe: e = assembled global residual (C), d = patch buffer (C), fd = FD data (C)
+template <int P, typename C, bool MULTI>
+__device__ __forceinline__ void pi_solve_l_body(const LaunchTable& L, int item, int items, char* smem) {
+    constexpr int N = 2 * P - 1, N2 = N * N, N3 = N2 * N;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int tile = xcd_tile(item, items) * 4 + wv;  // neighbouring patches on one XCD
+    if (tile >= L.total_tiles) return;                // per wavefront: no workgroup barrier follows
+    const ProbEntry& pe = entry<MULTI>(L, tile);
+    const int pidx = tile - pe.tile_begin;
+    const int npx = pe.n[0] - 1, npy = pe.n[1] - 1;
+    C* out = static_cast<C*>(pe.d) + (size_t)pidx * N3;
+    solve_lines<P, C>(pe, 1 + pidx % npx, 1 + (pidx / npx) % npy, 1 + pidx / (npx * npy), lane,
+                      reinterpret_cast<C*>(smem) + wv * N3, out);
 }
 
+template <int P, typename C, bool MULTI>
+__global__ void __launch_bounds__(256) k_pi_solve_l(LaunchTable L) {
+    __shared__ __align__(16) char smem[solve_l_lds<P, C>()];
+    pi_solve_l_body<P, C, MULTI>(L, blockIdx.x, gridDim.x, smem);
+}
+
+// The combine of the patch-major buffer by default: one wavefront per global
+// node row (Y, Z) in chunks of 32 cells along x.  Its lanes first take the
+// nodes of the chunk and add the z-patches (ascending vertex), within each the
+// y-patches, within each the sum of the x-patches; the sums go through LDS and
+// leave with lanes on (node a, cell), a store covering up to 32 consecutive
+// cells of a storage block.  No workgroup barrier, and every value of the
+// buffer is read once, in runs of p - 1 and p nodes.  Bitwise equal to
+// k_pi_combine_pm and k_pi_combine_nr.  Bound by reading the buffer and writing
+// z once: p = 7 on 24^3 cells 42 us in FP32 (3.2 TB/s; a workgroup per node row
+// 47, per block and node plane 50) and 65 in FP64 (63, 71), on 12^3 cells in
+// FP32 8 (13, 16), p = 4 on 20^3 cells 8 (12, 19).
+// pe: d = patch buffer, c = z (S), alpha = damping; tiles of wave_rows per
+// wavefront.
+template <int P, typename C> constexpr int wr_lds() { return 4 * (kNrCells * P + 1) * (int)sizeof(C); }
+
+template <int P, typename S, int ACC, bool MULTI>
+__device__ __forceinline__ void pi_combine_wr_body(const LaunchTable& L, int item, int items, char* smem) {
+    using C = typename Prec<S>::C;
+    constexpr int N = P + 1, N2 = N * N, NN = N2 * N;
+    constexpr int nP = 2 * P - 1, nP2 = nP * nP, nP3 = nP2 * nP;
+    constexpr int CC = kNrCells;
+    const int tile = xcd_tile(item, items);      // neighbouring rows on one XCD
+    if (tile >= L.total_tiles) return;
+    const ProbEntry& pe = entry<MULTI>(L, tile);
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64)), lane = threadIdx.x % 64;
+    const int n0 = pe.n[0], n1 = pe.n[1], n2 = pe.n[2];
+    const int npx = n0 - 1, npy = n1 - 1;
+    const int G1 = n1 * P + 1, rows = G1 * (n2 * P + 1);
+    C* const sx = reinterpret_cast<C*>(smem) + wv * (CC * P + 1);
+    const C* pbuf = static_cast<const C*>(pe.d);
+    S* z = static_cast<S*>(pe.c);
+    const C alpha = (C)pe.alpha;
+#pragma unroll 1
+    for (int rr = 0; rr < wave_rows<MULTI>(); ++rr) {
+        const int row = ((tile - pe.tile_begin) * wave_rows<MULTI>() + rr) * 4 + wv;
+        if (row >= rows) return;                     // per wavefront: no workgroup barrier follows
+        // the padding cells of the last storage block, one node per row
+        for (int l = row; l < NN; l += rows) {
+            const int e = (pe.nblk - 1) * kLanes + lane;
+            if (e >= pe.ncells) store_from(z + cell_offset(e, l, NN), (C)0);
+        }
+        const int Y = row % G1, Z = row / G1;
+        // patch rows containing the node row along y and z (ascending vertex, with
+        // the patch-local index), and the row's cell copies
+        int vyp[2], qyp[2], nyp = 0, vzp[2], qzp[2], nzp = 0;
+        int cyc[2], byc[2], nyc = 0, czc[2], bzc[2], nzc = 0;
+        {
+            const int qy = Y / P, ry = Y - qy * P;
+            if (ry == 0) {
+                if (qy >= 1 && qy <= npy) { vyp[nyp] = qy; qyp[nyp] = P - 1; ++nyp; }
+                if (qy >= 1) { cyc[nyc] = qy - 1; byc[nyc] = P; ++nyc; }
+                if (qy <= n1 - 1) { cyc[nyc] = qy; byc[nyc] = 0; ++nyc; }
+            } else {
+                if (qy >= 1) { vyp[nyp] = qy; qyp[nyp] = ry + P - 1; ++nyp; }
+                if (qy + 1 <= npy) { vyp[nyp] = qy + 1; qyp[nyp] = ry - 1; ++nyp; }
+                cyc[nyc] = qy; byc[nyc] = ry; ++nyc;
+            }
+            const int qz = Z / P, rz = Z - qz * P;
+            if (rz == 0) {
+                if (qz >= 1 && qz <= n2 - 1) { vzp[nzp] = qz; qzp[nzp] = P - 1; ++nzp; }
+                if (qz >= 1) { czc[nzc] = qz - 1; bzc[nzc] = P; ++nzc; }
+                if (qz <= n2 - 1) { czc[nzc] = qz; bzc[nzc] = 0; ++nzc; }
+            } else {
+                if (qz >= 1) { vzp[nzp] = qz; qzp[nzp] = rz + P - 1; ++nzp; }
+                if (qz + 1 <= n2 - 1) { vzp[nzp] = qz + 1; qzp[nzp] = rz - 1; ++nzp; }
+                czc[nzc] = qz; bzc[nzc] = rz; ++nzc;
+            }
+        }
+        const C* line[2][2];                         // the row's line of the first x-patch of each (z, y) pair
+#pragma unroll
+        for (int tz = 0; tz < 2; ++tz)
+#pragma unroll
+            for (int ty = 0; ty < 2; ++ty) {
+                const bool ok = tz < nzp && ty < nyp && npx > 0;
+                line[tz][ty] = pbuf + (ok ? (size_t)npx * ((vyp[ty] - 1) + npy * (vzp[tz] - 1)) * nP3 + nP * qyp[ty] +
+                                                nP2 * qzp[tz]
+                                          : 0);
+            }
+        for (int i0 = 0; i0 < n0; i0 += CC) {
+            const int nc = min(CC, n0 - i0);
+            for (int k = lane; k <= nc * P; k += 64) {
+                const int X = i0 * P + k;
+                // the x-patches holding X: the one of the vertex at or below it and
+                // the one of the vertex above
+                const int qx = X / P, rx = X - qx * P;
+                const bool lo_in = qx >= 1 && qx <= npx, hi_in = rx > 0 && qx + 1 <= npx;
+                const uint32_t lo = lo_in ? (uint32_t)((qx - 1) * nP3 + rx + P - 1) : 0u;
+                const uint32_t hi = hi_in ? (uint32_t)(qx * nP3 + rx - 1) : 0u;
+                // every term is loaded (a missing one from the line's first value)
+                // and dropped by a select, so the loads are in flight together
+                C sum = 0;
+#pragma unroll
+                for (int tz = 0; tz < 2; ++tz)
+#pragma unroll
+                    for (int ty = 0; ty < 2; ++ty) {
+                        if (tz >= nzp || ty >= nyp) continue;                  // uniform
+                        const C vl = line[tz][ty][lo], vh = line[tz][ty][hi];
+                        C xs = lo_in ? vl : (C)0;
+                        xs = hi_in ? xs + vh : xs;
+                        sum += xs;
+                    }
+                sx[k] = sum;
+            }
+            wave_sync();
+            // lanes on (a, cell) with the cells padded to a power of two
+            const int sh = nc <= 8 ? 3 : nc <= 16 ? 4 : 5;
+            for (int w = lane; w < (N << sh); w += 64) {
+                const int a = w >> sh, c = w & ((1 << sh) - 1);
+                if (c >= nc) continue;
+                const C v = alpha * sx[c * P + a];
+#pragma unroll
+                for (int cz = 0; cz < 2; ++cz) {
+                    if (cz >= nzc) break;
+#pragma unroll
+                    for (int cy = 0; cy < 2; ++cy) {
+                        if (cy >= nyc) break;
+                        const int e = i0 + c + n0 * (cyc[cy] + n1 * czc[cz]);
+                        S* d = z + cell_offset(e, a + N * (byc[cy] + N * bzc[cz]), NN);
+                        store_from(d, ACC ? load_as<C>(d) + v : v);
+                    }
+                }
+            }
+            wave_sync();
+        }
+    }
+}
+
+// The rows' stores are parts of lines, completed by the next mesh rows' stores
+// while the lines are still cached.  Outputs of 4-byte arithmetic beyond half
+// the Infinity Cache take k_pi_combine_pm, which stores whole runs of 64 cells
+// (a 256-problem batch, 1.4 GB of output: 2.3 ms against 2.5; one problem of
+// 32^3 cells at p = 7, 67 MB: 109 us against 91), and so does the mixed launch,
+// which serves batches.  8-byte stores cover a line with 16 cells.
+constexpr size_t kRowCombineBytes = size_t(128) << 20;
+template <int P, typename C> constexpr bool mixed_combine_pm() { return P >= 4 && sizeof(C) == 4; }
+
+template <int P, typename S, int ACC, bool MULTI>
+__global__ void __launch_bounds__(256) k_pi_combine_wr(LaunchTable L) {
+    __shared__ __align__(16) char smem[wr_lds<P, typename Prec<S>::C>()];
+    pi_combine_wr_body<P, S, ACC, MULTI>(L, blockIdx.x, gridDim.x, smem);
+}
+
+// Launch k<.., false> for one problem, k<.., true> for several.
+#define FEM_LAUNCH_MULTI(kern, grid, table, ...)                                                              \
+    do {                                                                                                      \
+        if (nprob > 1) hipLaunchKernelGGL((kern<__VA_ARGS__, true>), dim3(grid), dim3(256), 0, s, table);     \
+        else hipLaunchKernelGGL((kern<__VA_ARGS__, false>), dim3(grid), dim3(256), 0, s, table);              \
+    } while (0)
+
 template <int P, typename S>
-static hipError_t launch_pi_lines(int accumulate, ProbEntry* ents, int nprob, TableStager* d_tab, hipStream_t s,
-                                 int gcap) {
+static hipError_t launch_pi_lines(int accumulate, ProbEntry* ents, int nprob, TableStager* d_tab, hipStream_t s) {
     using C = typename Prec<S>::C;
     // 1. assemble r into each problem's global-node array
     hipError_t err = launch_assemble<P, S>(ents, nprob, d_tab, s);
     if (err != hipSuccess) return err;
-    int tiles = 0;
     // 2. one wavefront per patch
+    int tiles = 0;
     for (int i = 0; i < nprob; ++i) {
         const int npx = ents[i].n[0] - 1, npy = ents[i].n[1] - 1, npz = ents[i].n[2] - 1;
         ents[i].tile_begin = tiles;
@@ -2712,19 +2878,23 @@ static hipError_t launch_pi_lines(int accumulate, ProbEntry* ents, int nprob, Ta
     if (tiles > 0) {
         const int grid = ((tiles + 3) / 4 + 7) / 8 * 8;
         TraceSpan ts("pi_solve", P, Prec<S>::id, s);
-        if (nprob > 1) hipLaunchKernelGGL((k_pi_solve_l<P, S, C, true>), dim3(grid), dim3(256), 0, s, L1);
-        else hipLaunchKernelGGL((k_pi_solve_l<P, S, C, false>), dim3(grid), dim3(256), 0, s, L1);
+        FEM_LAUNCH_MULTI(k_pi_solve_l, grid, L1, P, C);
         err = hipGetLastError();
         if (err != hipSuccess) return err;
     }
-    // 3. combine into the cells: by global node rows, or per (storage
-    //    block, node plane) with the per-cell switch
-    const int cpc = g_combine_per_cell.load(std::memory_order_relaxed);
-    const bool rows = cpc == 2 || (cpc == 0 && pm_rows_default<S>());
+    // 3. combine into the cells: a wavefront per node row, with the switch a
+    //    workgroup per node row (2) or per (storage block, node plane) (1)
+    int cpc = g_combine_per_cell.load(std::memory_order_relaxed);
+    if (cpc == 0 && sizeof(C) == 4) {
+        size_t bytes = 0;
+        for (int i = 0; i < nprob; ++i) bytes += ents[i].len * sizeof(S);
+        if (bytes > kRowCombineBytes) cpc = 1;
+    }
     int tiles2 = 0;
     for (int i = 0; i < nprob; ++i) {
+        const int rows = (ents[i].n[1] * P + 1) * (ents[i].n[2] * P + 1);
         ents[i].tile_begin = tiles2;
-        ents[i].ntiles = rows ? (ents[i].n[1] * P + 1) * (ents[i].n[2] * P + 1) : ents[i].nblk * (P + 1);
+        ents[i].ntiles = cpc == 0 ? row_tiles(rows, nprob > 1) : cpc == 2 ? rows : ents[i].nblk * (P + 1);
         tiles2 += ents[i].ntiles;
     }
     LaunchTable L2{};
@@ -2734,25 +2904,19 @@ static hipError_t launch_pi_lines(int accumulate, ProbEntry* ents, int nprob, Ta
     if (err != hipSuccess) return err;
     const int grid2 = (tiles2 + 7) / 8 * 8;
     TraceSpan ts("pi_combine", P, Prec<S>::id, s);
-    if (rows) {
-        if (nprob > 1) {
-            if (accumulate) hipLaunchKernelGGL((k_pi_combine_nr<P, S, 1, true>), dim3(grid2), dim3(256), 0, s, L2);
-            else hipLaunchKernelGGL((k_pi_combine_nr<P, S, 0, true>), dim3(grid2), dim3(256), 0, s, L2);
-        } else {
-            if (accumulate) hipLaunchKernelGGL((k_pi_combine_nr<P, S, 1, false>), dim3(grid2), dim3(256), 0, s, L2);
-            else hipLaunchKernelGGL((k_pi_combine_nr<P, S, 0, false>), dim3(grid2), dim3(256), 0, s, L2);
-        }
-        return hipGetLastError();
-    }
-    if (nprob > 1) {
-        if (accumulate) hipLaunchKernelGGL((k_pi_combine_pm<P, S, 1, true>), dim3(grid2), dim3(256), 0, s, L2);
-        else hipLaunchKernelGGL((k_pi_combine_pm<P, S, 0, true>), dim3(grid2), dim3(256), 0, s, L2);
+    if (cpc == 0) {
+        if (accumulate) FEM_LAUNCH_MULTI(k_pi_combine_wr, grid2, L2, P, S, 1);
+        else FEM_LAUNCH_MULTI(k_pi_combine_wr, grid2, L2, P, S, 0);
+    } else if (cpc == 2) {
+        if (accumulate) FEM_LAUNCH_MULTI(k_pi_combine_nr, grid2, L2, P, S, 1);
+        else FEM_LAUNCH_MULTI(k_pi_combine_nr, grid2, L2, P, S, 0);
     } else {
-        if (accumulate) hipLaunchKernelGGL((k_pi_combine_pm<P, S, 1, false>), dim3(grid2), dim3(256), 0, s, L2);
-        else hipLaunchKernelGGL((k_pi_combine_pm<P, S, 0, false>), dim3(grid2), dim3(256), 0, s, L2);
+        if (accumulate) FEM_LAUNCH_MULTI(k_pi_combine_pm, grid2, L2, P, S, 1);
+        else FEM_LAUNCH_MULTI(k_pi_combine_pm, grid2, L2, P, S, 0);
     }
     return hipGetLastError();
 }
+#undef FEM_LAUNCH_MULTI
 
 // Two-phase patch inverse of one problem in z-slabs of vertex layers: the
 // solves of a slab are followed at once by the combine of every cell block
@@ -2897,7 +3061,7 @@ static hipError_t launch_pi_t(int accumulate, ProbEntry* ents, int nprob, TableS
     if constexpr (P >= 4) {
         const int gf = g_pi_fused.load(std::memory_order_relaxed);
         const int mode = cfg.pi_fused >= 0 ? cfg.pi_fused : gf >= 0 ? gf : 0;
-        if (mode != 2) return launch_pi_lines<P, S>(accumulate, ents, nprob, d_tab, s, gcap);
+        if (mode != 2) return launch_pi_lines<P, S>(accumulate, ents, nprob, d_tab, s);
     }
     using C = typename Prec<S>::C;
     constexpr int CBP = pi_patches_per_tile<P, C>();
@@ -3091,7 +3255,7 @@ struct SolveBody {
                               : pi_wave_default<P, S>() ? solve_w_lds<P, C>()
                               : pi_xcomb_default<P, S>() ? solve_x_lds<P, C, CBP>() : solve_g_lds<P, C, CBP>();
     __device__ static __forceinline__ void run(const LaunchTable& L, const NoArg&, int item, int items, char* smem) {
-        if constexpr (P >= 4) pi_solve_l_body<P, S, C, true>(L, item, items, smem);
+        if constexpr (P >= 4) pi_solve_l_body<P, C, true>(L, item, items, smem);
         else if constexpr (pi_wave_default<P, S>()) pi_solve_w_body<P, S, true>(L, item, items, smem);
         else if constexpr (pi_xcomb_default<P, S>()) pi_solve_x_body<P, S, CBP, true>(L, item, items, smem);
         else pi_solve_g_body<P, S, CBP, true>(L, item, items, smem);
@@ -3102,10 +3266,10 @@ template <int P, typename S, int ACC>
 struct CombineBody {
     using C = typename Prec<S>::C;
     using Arg = NoArg;
-    static constexpr int kLds = P >= 4 ? (pm_rows_default<S>() ? nr_lds<P, C>() : pm_lds<P, C>()) : 0;
+    static constexpr int kLds = mixed_combine_pm<P, C>() ? pm_lds<P, C>() : P >= 4 ? wr_lds<P, C>() : 0;
     __device__ static __forceinline__ void run(const LaunchTable& L, const NoArg&, int item, int items, char* smem) {
-        if constexpr (P >= 4 && pm_rows_default<S>()) pi_combine_nr_body<P, S, ACC, true>(L, item, items, smem);
-        else if constexpr (P >= 4) pi_combine_pm_body<P, S, ACC, true>(L, item, items, smem);
+        if constexpr (mixed_combine_pm<P, C>()) pi_combine_pm_body<P, S, ACC, true>(L, item, items, smem);
+        else if constexpr (P >= 4) pi_combine_wr_body<P, S, ACC, true>(L, item, items, smem);
         else if constexpr (pi_xcomb_default<P, S>()) pi_combine_x_body<P, S, pi_xcomb_tile<P, S>(), ACC, true>(L, item, items);
         else pi_combine_planes_body<P, S, ACC, true>(L, item, items);
     }
@@ -3125,8 +3289,8 @@ template <int P, typename S> static int pi_solve_items(int t) {
     else return t;
 }
 template <int P, typename S> static int pi_combine_tiles(const ProbEntry& e) {
-    if constexpr (P >= 4 && pm_rows_default<S>()) return (e.n[1] * P + 1) * (e.n[2] * P + 1);
-    else if constexpr (P >= 4) return e.nblk * (P + 1);
+    if constexpr (mixed_combine_pm<P, typename Prec<S>::C>()) return e.nblk * (P + 1);
+    else if constexpr (P >= 4) return row_tiles((e.n[1] * P + 1) * (e.n[2] * P + 1), true);
     else if constexpr (pi_xcomb_default<P, S>()) return ((e.n[1] * P + 1) * (e.n[2] * P + 1) + 3) / 4;
     else return e.nblk * (P + 1) * ((P + 1 + combine_brows<P>() - 1) / combine_brows<P>());
 }
@@ -3141,7 +3305,7 @@ static hipError_t launch_pi_mixed_t(ProbEntry* ents, int nprob, TableStager* st,
     MixTable T{};
     int grid = 0;
     // 1. assembly into each problem's global-node array
-    auto rows4 = [](int p, const ProbEntry& e) { return (assemble_waves(e, p) + 3) / 4; };
+    auto rows4 = [](int p, const ProbEntry& e) { return row_tiles(block_rows(e, p), true); };
     auto same = [](int, int t) { return t; };
     hipError_t err = mix_build(ents, nprob, st, s, rows4, same, T, grid);
     if (err != hipSuccess) return err;
