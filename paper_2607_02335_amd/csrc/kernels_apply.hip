@@ -22,6 +22,7 @@
 //  * k_apply_lds (any p): a workgroup owns CB cells staged in LDS and walks
 //    the three directions with one thread per 1D line.
 #include <atomic>
+#include <type_traits>
 
 #include "fem_internal.h"
 #include "launch.h"
@@ -30,6 +31,15 @@
 #include "trace.h"
 
 namespace fem {
+
+// A result on its way to storage.  In FP16 the compiler may fold the last FMA
+// and the conversion into one instruction with one rounding, in some kernels
+// and not in others of the same sum; the empty asm keeps the FP32 rounding in
+// all of them, so that every form of an apply gives the same bits.
+template <typename S, typename C> __device__ __forceinline__ C stored(C v) {
+    if constexpr (std::is_same_v<S, f16_t>) asm("" : "+v"(v));
+    return v;
+}
 
 // Process-wide switch for comparisons (FEM_OPT_APPLY_PLANES_P7; atomic: any
 // thread may set it): 1 runs the p = 7 FP64 Laplace and residual applies on
@@ -195,7 +205,7 @@ __device__ __forceinline__ void apply_reg_body(const LaunchTable& L, const RefMa
                     C v = out[a + N * b];
                     if (MODE == kApplyResidual) v = load_as<C>(rres + l * kLanes) - v;
                     if (on_boundary<P>(g, a, b, cz)) v = (C)0;
-                    store_from(y + l * kLanes, v);
+                    store_from(y + l * kLanes, stored<S>(v));
                 }
         };
         if constexpr (SPLIT) {

@@ -59,3 +59,8 @@ def test_split_against_the_oracle(F, p, n, prec):
         check_err(y, ref, 8 * TOL[prec], f"apply split p={p} n={n} prec={prec}")
     else:
         assert not np.any(y)
+
+
+@pytest.mark.parametrize("p", [2, 3])
+def test_split_equals_whole_cells_fp16(F, p):
+    test_split_equals_whole_cells(F, p, 3)
