@@ -400,6 +400,214 @@ static RefMats<P, C> ref_mats() {
 }
 
 // ---------------------------------------------------------------------------
+// Apply of output planes for p >= 4 in 4-byte arithmetic: one wavefront per
+// (storage block, output node plane), lanes on the block's 64 cells.  The wave
+// sums the input planes into its two z-contracted planes
+//     A = Mz u,  B = Kz u           (2 (p+1)^2 registers per lane)
+// and contracts those in registers,
+//     D = My A,  C = cy Ky A + cz My B;   y = Mx C + cx Kx D,
+// with the 1D matrices as scalar operands.  M and K are symmetric about the
+// middle of the element, so the y and x contractions work on the even and odd
+// parts of a line with matrices of half the size (a quarter of the terms each,
+// half in all, and 4 ((p+1)/2)^2 scalars instead of 2 (p+1)^2: at p = 7 they
+// stay in scalar registers).  No LDS, no barrier; every load and store is a run
+// of 64 cells; a block's input comes from HBM once and from L2 for its other
+// planes (neighbouring waves, on one XCD).  Bound by the FMA rate and the latency of the
+// plane loads at two to five wavefronts per SIMD.  Against the LDS form below
+// (k_apply_planes), us: p = 7 on 24^3 cells FP32 apply 32 -> 22, residual 41 ->
+// 25, mass 24 -> 17, BF16 residual 42 -> 28; p = 4 on 40^3 cells 44 -> 15, p = 6 on
+// 28^3 cells 54 -> 25.
+template <int P, typename C> struct PlaneMats {
+    static constexpr int N = P + 1, H = (N + 1) / 2, Q = N / 2;
+    C M[N * N], K[N * N];             // full, for the z sums
+    C Me[H * H], Ke[H * H];           // on even parts (the middle node its own)
+    C Mo[Q * Q], Ko[Q * Q];           // on odd parts
+};
+
+template <int P, typename C>
+static PlaneMats<P, C> plane_mats() {
+    using PM = PlaneMats<P, C>;
+    constexpr int N = PM::N, H = PM::H, Q = PM::Q;
+    PM R{};
+    const double* M = ref_mass(P);
+    const double* K = ref_stiff(P);
+    for (int i = 0; i < N * N; ++i) {
+        R.M[i] = (C)M[i];
+        R.K[i] = (C)K[i];
+    }
+    for (int i = 0; i < H; ++i)
+        for (int j = 0; j < H; ++j) {
+            const bool mid = 2 * j == N - 1;
+            R.Me[i * H + j] = (C)(mid ? M[i * N + j] : 0.5 * (M[i * N + j] + M[i * N + N - 1 - j]));
+            R.Ke[i * H + j] = (C)(mid ? K[i * N + j] : 0.5 * (K[i * N + j] + K[i * N + N - 1 - j]));
+        }
+    for (int i = 0; i < Q; ++i)
+        for (int j = 0; j < Q; ++j) {
+            R.Mo[i * Q + j] = (C)(0.5 * (M[i * N + j] - M[i * N + N - 1 - j]));
+            R.Ko[i * Q + j] = (C)(0.5 * (K[i * N + j] - K[i * N + N - 1 - j]));
+        }
+    return R;
+}
+
+// Even and odd parts of a line: e_j = v_j + v_{N-1-j} (the middle node
+// itself), o_j = v_j - v_{N-1-j}.
+template <int N, typename C>
+__device__ __forceinline__ void even_odd(const C (&v)[N], C (&e)[(N + 1) / 2], C (&o)[N / 2]) {
+#pragma unroll
+    for (int j = 0; j < N / 2; ++j) {
+        e[j] = v[j] + v[N - 1 - j];
+        o[j] = v[j] - v[N - 1 - j];
+    }
+    if (N % 2) e[N / 2] = v[N / 2];
+}
+template <int R, typename C>
+__device__ __forceinline__ C row_dot(const C* T, int i, const C (&v)[R]) {
+    C s = T[i * R] * v[0];
+#pragma unroll
+    for (int j = 1; j < R; ++j) s += T[i * R + j] * v[j];
+    return s;
+}
+
+template <int P, typename S, int MODE, bool MULTI>
+__device__ __forceinline__ void apply_plane_body(const LaunchTable& L, const PlaneMats<P, typename Prec<S>::C>& R,
+                                                 int item, int items) {
+    using C = typename Prec<S>::C;
+    constexpr int N = P + 1, N2 = N * N, NN = N2 * N, H = (N + 1) / 2, Q = N / 2;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int tile = (item % 8) * (items / 8) + item / 8;        // neighbouring planes on one XCD (items % 8 == 0)
+    if (tile >= L.total_tiles) return;
+    const ProbEntry& pe = entry<MULTI>(L, tile);
+    const int wave = (tile - pe.tile_begin) * 4 + wv;
+    const int blk = wave / N, cz = wave % N;
+    if (blk >= pe.nblk) return;
+    const int e = blk * kLanes + lane;
+    const size_t base = (size_t)blk * NN * kLanes + lane;
+    S* __restrict__ y = static_cast<S*>(pe.c) + base + (size_t)cz * N2 * kLanes;
+    if (e >= pe.ncells) {
+#pragma unroll 1
+        for (int l = 0; l < N2; ++l) store_from(y + l * kLanes, (C)0);
+        return;
+    }
+    const CellGeom<C> g = cell_geom<C>(pe, e);
+    const S* __restrict__ x = static_cast<const S*>(pe.a) + base;
+    C A[N2], B[N2];
+#pragma unroll
+    for (int l = 0; l < N2; ++l) A[l] = B[l] = (C)0;
+    // z contraction onto output plane cz; boundary copies of x read as zero
+    // (the mass apply reads them as they are)
+    auto add_plane = [&](int c, bool zb, auto face) {
+        const S* xp = x + (size_t)c * N2 * kLanes;
+        const C m = R.M[cz * N + c], k = R.K[cz * N + c];
+        C u[N2];
+#pragma unroll
+        for (int l = 0; l < N2; ++l) u[l] = load_as<C>(xp + l * kLanes);
+#pragma unroll
+        for (int l = 0; l < N2; ++l) {
+            const int a = l % N, b = l / N;
+            if (MODE != kApplyMass) {
+                const bool zero = (decltype(face)::value && zb) || (a == 0 && g.xlo) || (a == P && g.xhi) ||
+                                  (b == 0 && g.ylo) || (b == P && g.yhi);
+                u[l] = zero ? (C)0 : u[l];
+                B[l] += k * u[l];
+            }
+            A[l] += m * u[l];
+        }
+    };
+    add_plane(0, g.zlo, std::true_type{});
+#pragma unroll 1
+    for (int c = 1; c < P; ++c) add_plane(c, false, std::false_type{});
+    add_plane(P, g.zhi, std::true_type{});
+    // y contraction, in place: A <- D (mass: My A), B <- C
+#pragma unroll
+    for (int a = 0; a < N; ++a) {
+        C v[N], ea[H], oa[Q], eb[H], ob[Q];
+#pragma unroll
+        for (int b = 0; b < N; ++b) v[b] = A[a + N * b];
+        even_odd<N>(v, ea, oa);
+        if (MODE != kApplyMass) {
+#pragma unroll
+            for (int b = 0; b < N; ++b) v[b] = B[a + N * b];
+            even_odd<N>(v, eb, ob);
+        }
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            const C de = row_dot<H>(R.Me, i, ea);
+            const C dn = i < Q ? row_dot<Q>(R.Mo, i < Q ? i : 0, oa) : (C)0;
+            A[a + N * i] = i < Q ? de + dn : de;
+            if (i < Q) A[a + N * (N - 1 - i)] = de - dn;
+            if (MODE != kApplyMass) {
+                const C ce = g.cy * row_dot<H>(R.Ke, i, ea) + g.cz * row_dot<H>(R.Me, i, eb);
+                C cn = (C)0;
+                if (i < Q) cn = g.cy * row_dot<Q>(R.Ko, i < Q ? i : 0, oa) + g.cz * row_dot<Q>(R.Mo, i < Q ? i : 0, ob);
+                B[a + N * i] = i < Q ? ce + cn : ce;
+                if (i < Q) B[a + N * (N - 1 - i)] = ce - cn;
+            }
+        }
+    }
+    // x contraction and store
+    const S* __restrict__ rres = (MODE == kApplyResidual) ? static_cast<const S*>(pe.b) + base + (size_t)cz * N2 * kLanes
+                                                          : nullptr;
+    const bool zb = (cz == 0 && g.zlo) || (cz == P && g.zhi);
+    // the residual's right-hand side: one row ahead (all rows at once, as the
+    // compiler would have it, take the registers of a second wavefront)
+    C rn[N];
+    if (MODE == kApplyResidual) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int a = 0; a < N; ++a) rn[a] = load_as<C>(rres + a * kLanes);
+    }
+#pragma unroll
+    for (int b = 0; b < N; ++b) {
+        C v[N], ed[H], od[Q], ec[H], oc[Q], out[N], rc[N];
+        if (MODE == kApplyResidual) {
+#pragma unroll
+            for (int a = 0; a < N; ++a) {
+                rc[a] = rn[a];
+                if (b + 1 < N) rn[a] = load_as<C>(rres + (a + N * (b + 1)) * kLanes);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int a = 0; a < N; ++a) v[a] = A[a + N * b];
+        even_odd<N>(v, ed, od);
+        if (MODE != kApplyMass) {
+#pragma unroll
+            for (int a = 0; a < N; ++a) v[a] = B[a + N * b];
+            even_odd<N>(v, ec, oc);
+        }
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            C fe, fn = (C)0;
+            if (MODE == kApplyMass) {
+                fe = g.vol * row_dot<H>(R.Me, i, ed);
+                if (i < Q) fn = g.vol * row_dot<Q>(R.Mo, i < Q ? i : 0, od);
+            } else {
+                fe = row_dot<H>(R.Me, i, ec) + g.cx * row_dot<H>(R.Ke, i, ed);
+                if (i < Q) fn = row_dot<Q>(R.Mo, i < Q ? i : 0, oc) + g.cx * row_dot<Q>(R.Ko, i < Q ? i : 0, od);
+            }
+            out[i] = i < Q ? fe + fn : fe;
+            if (i < Q) out[N - 1 - i] = fe - fn;
+        }
+#pragma unroll
+        for (int a = 0; a < N; ++a) {
+            const int l = a + N * b;
+            C w = out[a];
+            if (MODE == kApplyResidual) w = rc[a] - w;
+            const bool zero = zb || (a == 0 && g.xlo) || (a == P && g.xhi) || (b == 0 && g.ylo) || (b == P && g.yhi);
+            store_from(y + l * kLanes, stored<S>(zero ? (C)0 : w));
+        }
+    }
+}
+
+template <int P, typename S, int MODE, bool MULTI>
+__global__ void __launch_bounds__(256, 2) k_apply_plane(LaunchTable L, PlaneMats<P, typename Prec<S>::C> R) {
+    apply_plane_body<P, S, MODE, MULTI>(L, R, blockIdx.x, gridDim.x);
+}
+
+// p >= 4: output planes for 4-byte arithmetic
+template <int P, typename C> constexpr bool apply_plane_default() { return P >= 4 && sizeof(C) == 4; }
+
+// ---------------------------------------------------------------------------
 // Plane-streamed apply for p >= 4.  A workgroup owns 16 consecutive cells of
 // a storage block (so every load and store is a 128-byte run of one node
 // plane) and walks the z node planes two at a time.  Per pair of planes the
@@ -798,7 +1006,8 @@ static hipError_t launch_apply_t(ProbEntry* ents, int nprob, TableStager* d_tab,
     // p = 7 (Laplace, residual): the matrix-core apply unless the plane-streamed
     // one is asked for (apply_lds = 2, or the process-wide option)
     const bool use_mfma = apply_mfma_default<P, MODE, C>() && !force_lds && g_apply_planes_p7 == 0;
-    const bool use_planes = (P >= 4) && !use_mfma && (force_lds == 0 || force_lds == 2);
+    const bool use_plane = apply_plane_default<P, C>() && !force_lds;
+    const bool use_planes = (P >= 4) && !use_mfma && !use_plane && (force_lds == 0 || force_lds == 2);
     constexpr int CB = lds_cells<P>((int)sizeof(C));
     constexpr int MCB = ApplyMfmaShape<C>::CB;
     LaunchTable L{};
@@ -806,6 +1015,7 @@ static hipError_t launch_apply_t(ProbEntry* ents, int nprob, TableStager* d_tab,
     for (int i = 0; i < nprob; ++i) {
         ents[i].tile_begin = tiles;
         ents[i].ntiles = use_reg ? ents[i].nblk
+                       : use_plane ? (ents[i].nblk * (P + 1) + 3) / 4
                        : use_mfma ? ents[i].nblk * (kLanes / MCB)
                        : use_planes ? ents[i].nblk * (kLanes / 16) : ents[i].nblk * (kLanes / CB);
         tiles += ents[i].ntiles;
@@ -827,6 +1037,15 @@ static hipError_t launch_apply_t(ProbEntry* ents, int nprob, TableStager* d_tab,
             const int grid = (tiles + 3) / 4 < gcap ? (tiles + 3) / 4 : gcap;
             if (nprob > 1) hipLaunchKernelGGL((k_apply_reg<P, S, MODE, true, false>), dim3(grid), dim3(256), 0, s, L, R);
             else hipLaunchKernelGGL((k_apply_reg<P, S, MODE, false, false>), dim3(grid), dim3(256), 0, s, L, R);
+            return hipGetLastError();
+        }
+    }
+    if constexpr (apply_plane_default<P, C>()) {
+        if (use_plane) {
+            const int grid = (tiles + 7) / 8 * 8;
+            const PlaneMats<P, C> E = plane_mats<P, C>();
+            if (nprob > 1) hipLaunchKernelGGL((k_apply_plane<P, S, MODE, true>), dim3(grid), dim3(256), 0, s, L, E);
+            else hipLaunchKernelGGL((k_apply_plane<P, S, MODE, false>), dim3(grid), dim3(256), 0, s, L, E);
             return hipGetLastError();
         }
     }
@@ -878,19 +1097,31 @@ static hipError_t launch_apply_p(int prec, int mode, ProbEntry* e, int n, TableS
 // Mixed-degree apply: the register body for p = 2, 3 (four storage blocks
 // per item, one per wavefront) and the plane-streamed body for p = 7 (16
 // cells per item), in one persistent launch.
-// (p = 7 takes the plane-streamed body: the mixed launch serves 4-byte
-// values only when p = 7 is present, see launch_apply_any, and the
-// matrix-core body's accumulator registers would bound the whole launch)
+// (p = 7 in 4-byte arithmetic takes the output-plane body, in FP64 the
+// plane-streamed one, which the mixed launch serves for the mass apply, see
+// launch_apply_any; the matrix-core body's accumulator registers would bound
+// the whole launch)
+template <int P, typename C, bool PLANE> struct ApplyArg { using T = RefMats<P, C>; };
+template <int P, typename C> struct ApplyArg<P, C, true> { using T = PlaneMats<P, C>; };
+
 template <int P, typename S, int MODE>
 struct ApplyBody {
     using C = typename Prec<S>::C;
-    using Arg = RefMats<P, C>;
-    static constexpr int kLds = P <= 3 ? 0 : PlanesShape<P, C>::kLds;
+    static constexpr bool kPlane = apply_plane_default<P, C>();
+    using Arg = typename ApplyArg<P, C, kPlane>::T;
+    static constexpr int kLds = P <= 3 || kPlane ? 0 : PlanesShape<P, C>::kLds;
     __device__ static __forceinline__ void run(const LaunchTable& L, const Arg& R, int item, int items, char* smem) {
         if constexpr (P <= 3) apply_reg_body<P, S, MODE, true>(L, R, item, items);
+        else if constexpr (kPlane) apply_plane_body<P, S, MODE, true>(L, R, item, items);
         else apply_planes_body<P, S, MODE, true>(L, R, item, items, smem);
     }
 };
+
+template <int P, typename S, int MODE> static typename ApplyBody<P, S, MODE>::Arg apply_arg() {
+    using C = typename Prec<S>::C;
+    if constexpr (ApplyBody<P, S, MODE>::kPlane) return plane_mats<P, C>();
+    else return ref_mats<P, C>();
+}
 
 template <typename S, int MODE>
 static hipError_t launch_apply_mixed_t(ProbEntry* ents, int nprob, TableStager* st, hipStream_t s) {
@@ -898,14 +1129,16 @@ static hipError_t launch_apply_mixed_t(ProbEntry* ents, int nprob, TableStager* 
     static_assert(mix_degree(0) == 7 && mix_degree(1) == 3 && mix_degree(2) == 2, "segment degrees");
     MixTable T{};
     int grid = 0;
-    auto tiles = [](int p, const ProbEntry& e) { return p <= 3 ? e.nblk : e.nblk * (kLanes / 16); };
+    auto tiles = [](int p, const ProbEntry& e) {
+        return p <= 3 ? e.nblk : apply_plane_default<7, C>() ? (e.nblk * 8 + 3) / 4 : e.nblk * (kLanes / 16);
+    };
     auto items = [](int p, int t) { return p <= 3 ? (t + 3) / 4 : t; };
     hipError_t err = mix_build(ents, nprob, st, s, tiles, items, T, grid);
     if (err != hipSuccess || grid == 0) return err;
     TraceSpan ts(MODE == kApplyLaplace ? "apply" : MODE == kApplyResidual ? "apply_residual" : "mass_apply", 0,
                  Prec<S>::id, s);
     hipLaunchKernelGGL((k_mixed<ApplyBody<7, S, MODE>, ApplyBody<3, S, MODE>, ApplyBody<2, S, MODE>>), dim3(grid),
-                       dim3(256), 0, s, T, ref_mats<7, C>(), ref_mats<3, C>(), ref_mats<2, C>());
+                       dim3(256), 0, s, T, apply_arg<7, S, MODE>(), apply_arg<3, S, MODE>(), apply_arg<2, S, MODE>());
     return hipGetLastError();
 }
 

@@ -51,7 +51,7 @@ __device__ __forceinline__ void mix_segment(const MixSeg& g, const A& a, char* s
 }
 
 template <class B0, class B1, class B2>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, 2)     // two wavefronts per SIMD at least
 k_mixed(MixTable T, typename B0::Arg a0, typename B1::Arg a1, typename B2::Arg a2) {
     constexpr int kL = lds_max(16, lds_max(B0::kLds, lds_max(B1::kLds, B2::kLds)));
     __shared__ __align__(16) char smem[kL];
