@@ -295,14 +295,15 @@ fem_status fem_batch_apply(fem_batch* B, void* const* x, void* const* y, int pre
 /* z[i] = P_AS r[i] for every problem i. */
 fem_status fem_batch_patch_inverse(fem_batch* B, void* const* r, void* const* z, int prec);
 /* Tile-shape autotuner: for each degree present in the batch, time the
- * candidate kernel shapes on the batch's own problems (apply: register
- * (p <= 3) or plane-streamed (p >= 4; for p = 7 in FP64 the matrix-core
- * kernel) kernel, or the LDS line kernel, and for p = 7 also the
- * plane-streamed kernel, each x two persistent grid caps; patch inverse for p <= 3: two launches through
+ * candidate kernel shapes on the batch's own problems (apply: the default
+ * kernel (register for p <= 3; for p >= 4 output planes in 4-byte arithmetic,
+ * plane-streamed in FP64, matrix-core for p = 7 in FP64) or the LDS line
+ * kernel, and for p = 7 also the plane-streamed kernel, each x two persistent
+ * grid caps; patch inverse for p <= 3: two launches through
  * the patch buffer, fused sweep from the cell copies, fused sweep from the
- * assembled residual, or solves with the in-tile x-combine; for p >= 4: MFMA
- * or line patch solves; each x two grid caps) and keep the fastest for later
- * batched calls.  choice (may be
+ * assembled residual, or solves with the in-tile x-combine, per workgroup or
+ * per wavefront; for p >= 4 one kernel; each x two grid caps) and keep the
+ * fastest for later batched calls.  choice (may be
  * NULL): int[14], choice[2(p-1)] = apply candidate index, choice[2(p-1)+1]
  * = patch-inverse candidate index of degree p, candidates in the order
  * listed with the grid cap varying fastest (untouched for absent degrees).
@@ -460,16 +461,16 @@ fem_status fem_host_fd_1d(int p, double h0, double h1, double* S, double* lambda
  * p = 3), then a combine by global node rows, 4 the same with one wavefront
  * per tile of floor(64 / (2p-1)) patches (x and y contractions on a lane's
  * patch plane in registers, two transposes through LDS instead of four);
- * for p >= 4, 2 selects line (VALU) patch solves instead of MFMA; -1
- * (default) picks by degree and precision only (4 for p = 2, 3 for p = 3
- * in FP64, else 0).  The p <= 3 combine of the two-launch
- * form runs by global node rows (FP64, every mesh with at least 48 cells
+ * no effect for p >= 4; -1 (default) picks by degree and precision only (4
+ * for p = 2, 3 for p = 3 in FP64, else 0).  The p <= 3 combine of the
+ * two-launch form runs by global node rows (FP64, every mesh with at least 48 cells
  * along x) or by (block, node plane), with identical results;
  * FEM_OPT_COMBINE_PER_CELL = 1 makes it use one wavefront per 64-cell block
- * (all node planes) instead.  For p >= 4 the combine runs by global node
- * rows in FP64 and per (64-cell block, node plane) otherwise, with
- * identical results; FEM_OPT_COMBINE_PER_CELL = 1 selects the latter and 2
- * the former for every precision (0, the default, picks by precision).  FEM_OPT_RESTRICT_FROM_CELLS = 1 makes
+ * (all node planes) instead.  For p >= 4 the combine runs with one wavefront
+ * per global node row, large 4-byte outputs and mixed-degree launches per
+ * (64-cell block, node plane); FEM_OPT_COMBINE_PER_CELL = 1 selects the latter
+ * and 2 one workgroup per node row (0, the default, picks), with identical
+ * results.  FEM_OPT_RESTRICT_FROM_CELLS = 1 makes
  * the p <= 3 patch solves sum the residual copies from the cell vector
  * instead of reading the assembled global-node array.  FEM_OPT_PI_SLAB_MB =
  * m > 0 runs the p <= 3 two-launch patch inverse of a single problem in

@@ -221,16 +221,16 @@ extern "C" fem_status fem_batch_autotune(fem_batch* B, int prec, int* choice) {
     for (int p = 1; p <= kMaxP && result == FEM_OK; ++p) {
         if (B->group[p].empty()) continue;
         for (int which = 0; which < 2 && result == FEM_OK; ++which) {
-            // apply: 0 = register (p <= 3) / plane-streamed (p >= 4; matrix-core
-            //        for p = 7 in FP64) kernel, 1 = LDS line kernel,
-            //        2 = plane-streamed (p = 7);
+            // apply: 0 = register (p <= 3) / output-plane (p >= 4, 4-byte) /
+            //        plane-streamed (p >= 4, FP64; matrix-core for p = 7) kernel,
+            //        1 = LDS line kernel, 2 = plane-streamed (p = 7);
             // patch inverse, p <= 3: 0 = two launches through the patch buffer,
             //        1 = fused sweep summing cell copies, 2 = fused sweep from the
             //        assembled residual, 3 = solves with the in-tile x-combine,
             //        4 = the same with one wavefront per tile;
-            //        p >= 4: 0 = MFMA solves, 2 = line solves
+            //        p >= 4: one kernel
             std::vector<int> kinds = which == 0 ? (p == 7 ? std::vector<int>{0, 1, 2} : std::vector<int>{0, 1})
-                                   : (p <= 3 ? std::vector<int>{0, 1, 2, 3, 4} : std::vector<int>{0, 2});
+                                   : (p <= 3 ? std::vector<int>{0, 1, 2, 3, 4} : std::vector<int>{0});
             std::vector<LaunchCfg> cand;
             for (int kind : kinds) {
                 for (int c : caps) {

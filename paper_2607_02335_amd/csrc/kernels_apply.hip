@@ -14,11 +14,17 @@
 // and written as zero) while the mass apply is P_I M (input read in full), so
 // that P_I M f is the load vector of nodal source values f.
 //
-// Two kernel shapes:
+// Kernel shapes:
 //  * k_apply_reg (p <= 3): one thread per cell.  The cell's (p+1)^3 values
 //    are loaded into registers (one coalesced 64-cell segment per node), and
 //    the output is produced one z-plane at a time, so the live state is the
-//    input cell plus a few planes.
+//    input cell plus a few planes; on meshes of few blocks one wavefront per
+//    output plane.
+//  * k_apply_plane (p >= 4, 4-byte arithmetic; FP64 where its sums fit the
+//    registers, p = 4, 5): one wavefront per 64 cells and output plane.
+//  * k_apply_planes (p = 6, 7 in FP64; p = 7 in every precision as an autotuner
+//    candidate): 16 cells per workgroup, z-planes streamed through LDS.
+//  * k_apply_mfma (p = 7 in FP64, Laplace and residual): matrix cores.
 //  * k_apply_lds (any p): a workgroup owns CB cells staged in LDS and walks
 //    the three directions with one thread per 1D line.
 #include <atomic>
@@ -400,7 +406,7 @@ static RefMats<P, C> ref_mats() {
 }
 
 // ---------------------------------------------------------------------------
-// Apply of output planes for p >= 4 in 4-byte arithmetic: one wavefront per
+// Apply of output planes for p >= 4 (apply_plane_default): one wavefront per
 // (storage block, output node plane), lanes on the block's 64 cells.  The wave
 // sums the input planes into its two z-contracted planes
 //     A = Mz u,  B = Kz u           (2 (p+1)^2 registers per lane)
@@ -415,8 +421,8 @@ static RefMats<P, C> ref_mats() {
 // planes (neighbouring waves, on one XCD).  Bound by the FMA rate and the latency of the
 // plane loads at two to five wavefronts per SIMD.  Against the LDS form below
 // (k_apply_planes), us: p = 7 on 24^3 cells FP32 apply 32 -> 22, residual 41 ->
-// 25, mass 24 -> 17, BF16 residual 42 -> 28; p = 4 on 40^3 cells 44 -> 15, p = 6 on
-// 28^3 cells 54 -> 25.
+// 25, mass 24 -> 17, BF16 residual 42 -> 28; p = 4 on 40^3 cells FP32 44 -> 15,
+// FP64 82 -> 46; p = 6 on 28^3 cells FP32 54 -> 25.
 template <int P, typename C> struct PlaneMats {
     static constexpr int N = P + 1, H = (N + 1) / 2, Q = N / 2;
     C M[N * N], K[N * N];             // full, for the z sums
@@ -431,20 +437,24 @@ static PlaneMats<P, C> plane_mats() {
     PM R{};
     const double* M = ref_mass(P);
     const double* K = ref_stiff(P);
-    for (int i = 0; i < N * N; ++i) {
-        R.M[i] = (C)M[i];
-        R.K[i] = (C)K[i];
-    }
+    // the mean of an entry and its mirror image: they differ in the last bits
+    // (1e-16 to 2e-15 of the largest), the mean is nearer to the exact value
+    auto at = [](const double* T, int i, int j) { return 0.5 * (T[i * N + j] + T[(N - 1 - i) * N + N - 1 - j]); };
+    for (int i = 0; i < N; ++i)
+        for (int j = 0; j < N; ++j) {
+            R.M[i * N + j] = (C)at(M, i, j);
+            R.K[i * N + j] = (C)at(K, i, j);
+        }
     for (int i = 0; i < H; ++i)
         for (int j = 0; j < H; ++j) {
             const bool mid = 2 * j == N - 1;
-            R.Me[i * H + j] = (C)(mid ? M[i * N + j] : 0.5 * (M[i * N + j] + M[i * N + N - 1 - j]));
-            R.Ke[i * H + j] = (C)(mid ? K[i * N + j] : 0.5 * (K[i * N + j] + K[i * N + N - 1 - j]));
+            R.Me[i * H + j] = (C)(mid ? at(M, i, j) : 0.5 * (at(M, i, j) + at(M, i, N - 1 - j)));
+            R.Ke[i * H + j] = (C)(mid ? at(K, i, j) : 0.5 * (at(K, i, j) + at(K, i, N - 1 - j)));
         }
     for (int i = 0; i < Q; ++i)
         for (int j = 0; j < Q; ++j) {
-            R.Mo[i * Q + j] = (C)(0.5 * (M[i * N + j] - M[i * N + N - 1 - j]));
-            R.Ko[i * Q + j] = (C)(0.5 * (K[i * N + j] - K[i * N + N - 1 - j]));
+            R.Mo[i * Q + j] = (C)(0.5 * (at(M, i, j) - at(M, i, N - 1 - j)));
+            R.Ko[i * Q + j] = (C)(0.5 * (at(K, i, j) - at(K, i, N - 1 - j)));
         }
     return R;
 }
@@ -604,8 +614,17 @@ __global__ void __launch_bounds__(256, 2) k_apply_plane(LaunchTable L, PlaneMats
     apply_plane_body<P, S, MODE, MULTI>(L, R, blockIdx.x, gridDim.x);
 }
 
-// p >= 4: output planes for 4-byte arithmetic
-template <int P, typename C> constexpr bool apply_plane_default() { return P >= 4 && sizeof(C) == 4; }
+// Output planes for p >= 4 in 4-byte arithmetic and, in FP64, as far as the
+// sums fit the registers of two wavefronts per SIMD.  FP64 against
+// k_apply_planes, us: Laplace p = 4 on 40^3 cells 46 against 82 (80^3 307
+// against 609, 8^3 8.4 against 9.5), p = 5 on 32^3 44 against 77, p = 6 on 28^3
+// 143 (spilling) against 102, p = 7 on 24^3 89 against 77; residual p = 4 52
+// against 111, p = 5 56 against 111, p = 6 178 against 142; mass p = 4 41
+// against 50, p = 5 41 against 39, p = 6 55 against 72, p = 7 57 against 59 (the
+// mixed launch would take its registers).
+template <int P, int MODE, typename C> constexpr bool apply_plane_default() {
+    return P >= 4 && (sizeof(C) == 4 || (MODE == kApplyMass ? P == 4 || P == 6 : P <= 5));
+}
 
 // ---------------------------------------------------------------------------
 // Plane-streamed apply for p >= 4.  A workgroup owns 16 consecutive cells of
@@ -778,7 +797,7 @@ k_apply_planes(LaunchTable L, RefMats<P, typename Prec<S>::C> R) {
 }
 
 // The matrix-core apply serves p = 7 in the Laplace and residual modes in
-// FP64; with 4-byte values the plane-streamed kernel measured faster.
+// FP64; 4-byte values take the output planes.
 template <int P, int MODE, typename C> constexpr bool apply_mfma_default() {
     return P == 7 && MODE != kApplyMass && sizeof(C) == 8;
 }
@@ -1006,8 +1025,8 @@ static hipError_t launch_apply_t(ProbEntry* ents, int nprob, TableStager* d_tab,
     // p = 7 (Laplace, residual): the matrix-core apply unless the plane-streamed
     // one is asked for (apply_lds = 2, or the process-wide option)
     const bool use_mfma = apply_mfma_default<P, MODE, C>() && !force_lds && g_apply_planes_p7 == 0;
-    const bool use_plane = apply_plane_default<P, C>() && !force_lds;
-    const bool use_planes = (P >= 4) && !use_mfma && !use_plane && (force_lds == 0 || force_lds == 2);
+    const bool use_plane = apply_plane_default<P, MODE, C>() && !force_lds;
+    const bool use_planes = (P >= 4) && !use_mfma && !use_plane && (force_lds == 0 || (force_lds == 2 && P == 7));
     constexpr int CB = lds_cells<P>((int)sizeof(C));
     constexpr int MCB = ApplyMfmaShape<C>::CB;
     LaunchTable L{};
@@ -1040,7 +1059,7 @@ static hipError_t launch_apply_t(ProbEntry* ents, int nprob, TableStager* d_tab,
             return hipGetLastError();
         }
     }
-    if constexpr (apply_plane_default<P, C>()) {
+    if constexpr (apply_plane_default<P, MODE, C>()) {
         if (use_plane) {
             const int grid = (tiles + 7) / 8 * 8;
             const PlaneMats<P, C> E = plane_mats<P, C>();
@@ -1057,7 +1076,7 @@ static hipError_t launch_apply_t(ProbEntry* ents, int nprob, TableStager* d_tab,
             return hipGetLastError();
         }
     }
-    if constexpr (P >= 4) {
+    if constexpr (P == 7 || (P >= 4 && !apply_plane_default<P, MODE, C>())) {
         if (use_planes) {
             const int grid = tiles < gcap ? tiles : gcap;
             constexpr int NT = PlanesShape<P, C>::NT;
@@ -1095,19 +1114,18 @@ static hipError_t launch_apply_p(int prec, int mode, ProbEntry* e, int n, TableS
 
 // ---------------------------------------------------------------------------
 // Mixed-degree apply: the register body for p = 2, 3 (four storage blocks
-// per item, one per wavefront) and the plane-streamed body for p = 7 (16
-// cells per item), in one persistent launch.
-// (p = 7 in 4-byte arithmetic takes the output-plane body, in FP64 the
-// plane-streamed one, which the mixed launch serves for the mass apply, see
-// launch_apply_any; the matrix-core body's accumulator registers would bound
-// the whole launch)
+// per item, one per wavefront) and for p = 7 in 4-byte arithmetic the
+// output-plane body (four planes per item), in FP64 the plane-streamed one
+// (16 cells per item; for the mass apply, see launch_apply_any: the
+// matrix-core body's accumulator registers would bound the whole launch), in
+// one launch.
 template <int P, typename C, bool PLANE> struct ApplyArg { using T = RefMats<P, C>; };
 template <int P, typename C> struct ApplyArg<P, C, true> { using T = PlaneMats<P, C>; };
 
 template <int P, typename S, int MODE>
 struct ApplyBody {
     using C = typename Prec<S>::C;
-    static constexpr bool kPlane = apply_plane_default<P, C>();
+    static constexpr bool kPlane = apply_plane_default<P, MODE, C>();
     using Arg = typename ApplyArg<P, C, kPlane>::T;
     static constexpr int kLds = P <= 3 || kPlane ? 0 : PlanesShape<P, C>::kLds;
     __device__ static __forceinline__ void run(const LaunchTable& L, const Arg& R, int item, int items, char* smem) {
@@ -1130,7 +1148,7 @@ static hipError_t launch_apply_mixed_t(ProbEntry* ents, int nprob, TableStager* 
     MixTable T{};
     int grid = 0;
     auto tiles = [](int p, const ProbEntry& e) {
-        return p <= 3 ? e.nblk : apply_plane_default<7, C>() ? (e.nblk * 8 + 3) / 4 : e.nblk * (kLanes / 16);
+        return p <= 3 ? e.nblk : apply_plane_default<7, MODE, C>() ? (e.nblk * 8 + 3) / 4 : e.nblk * (kLanes / 16);
     };
     auto items = [](int p, int t) { return p <= 3 ? (t + 3) / 4 : t; };
     hipError_t err = mix_build(ents, nprob, st, s, tiles, items, T, grid);
@@ -1154,7 +1172,7 @@ static hipError_t launch_apply_mixed_m(int mode, ProbEntry* ents, int nprob, Tab
 hipError_t launch_apply_any(int prec, int mode, ProbEntry* ents, int nprob, TableStager* st, hipStream_t s,
                             bool mix) {
     if (nprob <= 0) return hipSuccess;
-    // the mixed p = 7 body is the plane-streamed one, the default for 4-byte
+    // the mixed p = 7 body is the default of one launch per degree for 4-byte
     // values and the mass apply; FP64 Laplace and residual applies with p = 7
     // present take one launch per degree (p = 7 on the matrix cores)
     bool p7_mfma = false;
