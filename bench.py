@@ -152,7 +152,8 @@ def op_bytes(op, p, n, esize=8):
     apply and the patch inverse read one cell-wise vector and write one
     (2 x esize bytes per cell DoF; geometry and eigen-data are O(n) and not
     counted); the structured DSS reads and writes both coincident copies of
-    every face pair of every axis pass (4 x esize per pair)."""
+    every face pair of every axis pass (4 x esize per pair; the library's one
+    pass moves a copy once for all axes, so its fraction can pass 1)."""
     cell = cell_dofs(p, n) * esize
     if op in ("apply", "mass", "patch_inverse"):
         return 2 * cell
