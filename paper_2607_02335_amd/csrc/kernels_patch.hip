@@ -5,16 +5,16 @@
 // the cells [vi-1, vi] x [vj-1, vj] x [vk-1, vk]; patch-local node
 // (qx, qy, qz), qx = I - (vi-1) p - 1 for global node plane I.
 //
-// Phase 1 (k_pi_solve), one workgroup per CBP consecutive patches along x:
+// Phase 1, the patch solves:
 //   restrict:  r_P(q) = sum of the coincident cell copies of node q among the
 //              patch's eight cells (= (G^T r)(q): every cell holding q lies in
 //              the patch), so the smoother sees r only through its assembly,
 //              the consistency the paper's equivalence theorem asks of a
 //              preconditioner (Section 3.2, Remarks after the theorem);
 //   solve:     z_P = (Sx (x) Sy (x) Sz) diag(1/(lx+ly+lz)) (Sx (x) Sy (x) Sz)^T r_P,
-//              six 1D contractions staged in LDS, one thread per line;
+//              six 1D contractions;
 //   store z_P in a patch buffer.
-// Phase 2 (k_pi_combine), one thread per cell copy:
+// Phase 2, the combine:
 //   z(node) = sum of z_P(node) over the patches whose interior contains the
 //   node, added in increasing vertex order.  That order depends only on the
 //   global node, so all copies of a node receive bitwise identical values:
@@ -70,208 +70,8 @@ template <int P, typename C> constexpr int pi_patches_per_tile() {
     return cb;
 }
 
-// pe: a = r (S), d = patch buffer (C), fd[0..2] = FD records (C) per
-// direction, indexed by vertex line v-1.
-template <int P, typename S, int CBP, bool MULTI>
-__global__ void __launch_bounds__(256) k_pi_solve(LaunchTable L) {
-    using C = typename Prec<S>::C;
-    constexpr int N = P + 1, NN = N * N * N;
-    constexpr int nP = 2 * P - 1, nP2 = nP * nP, nP3 = nP2 * nP;
-    constexpr int REC = fd_record(P);
-    constexpr int NT = 256, LPT = NT / CBP;     // lines per tile-thread stride
-    static_assert(NT % CBP == 0, "patches per tile must divide the workgroup");
-    __shared__ C sv[nP3 * CBP];
-    __shared__ C sS[3][CBP][nP2];
-    __shared__ C sL[3][CBP][nP];
-    const int tid = threadIdx.x;
-    const int pc = tid % CBP;
-    for (int tile = blockIdx.x; tile < L.total_tiles; tile += gridDim.x) {
-        const ProbEntry& pe = entry<MULTI>(L, tile);
-        const int t = tile - pe.tile_begin;
-        const int npx = pe.n[0] - 1, npy = pe.n[1] - 1;
-        const int tpr = (npx + CBP - 1) / CBP;
-        const int row = t / tpr, xt = t % tpr;
-        const int vj = 1 + row % npy, vk = 1 + row / npy;
-        const int vi = 1 + xt * CBP + pc;
-        const bool valid = vi <= npx;
-        // FD data of this patch's three vertex lines
-        for (int idx = tid / CBP; idx < 3 * (nP2 + nP); idx += LPT) {
-            const int d = idx / (nP2 + nP), w = idx % (nP2 + nP);
-            const int line = (d == 0 ? (valid ? vi : npx) : d == 1 ? vj : vk) - 1;
-            const C v = static_cast<const C*>(pe.fd[d])[(size_t)line * REC + w];
-            if (w < nP2) sS[d][pc][w] = v; else sL[d][pc][w - nP2] = v;
-        }
-        // restrict: sum coincident copies from the eight cells
-        const S* r = static_cast<const S*>(pe.a);
-        const int n0 = pe.n[0], n1 = pe.n[1];
-        for (int q = tid / CBP; q < nP3; q += LPT) {
-            const int qx = q % nP, qy = (q / nP) % nP, qz = q / nP2;
-            C s = 0;
-            if (valid) {
-#pragma unroll
-                for (int s3 = 0; s3 < 2; ++s3) {
-                    const int c = qz + 1 - s3 * P;
-                    if (c < 0 || c > P) continue;
-#pragma unroll
-                    for (int s2 = 0; s2 < 2; ++s2) {
-                        const int b = qy + 1 - s2 * P;
-                        if (b < 0 || b > P) continue;
-#pragma unroll
-                        for (int s1 = 0; s1 < 2; ++s1) {
-                            const int a = qx + 1 - s1 * P;
-                            if (a < 0 || a > P) continue;
-                            const int e = (vi - 1 + s1) + n0 * ((vj - 1 + s2) + n1 * (vk - 1 + s3));
-                            s += load_as<C>(r + cell_offset(e, a + N * (b + N * c), NN));
-                        }
-                    }
-                }
-            }
-            sv[q * CBP + pc] = s;
-        }
-        __syncthreads();
-        // forward z: v <- Sz^T v along z lines
-        for (int ln = tid / CBP; ln < nP2; ln += LPT) {
-            C v[nP];
-#pragma unroll
-            for (int i = 0; i < nP; ++i) v[i] = sv[(ln + nP2 * i) * CBP + pc];
-#pragma unroll
-            for (int j = 0; j < nP; ++j) {
-                C s = 0;
-#pragma unroll
-                for (int i = 0; i < nP; ++i) s += sS[2][pc][i * nP + j] * v[i];
-                sv[(ln + nP2 * j) * CBP + pc] = s;
-            }
-        }
-        __syncthreads();
-        // forward y
-        for (int ln = tid / CBP; ln < nP2; ln += LPT) {
-            const int qx = ln % nP, qz = ln / nP;
-            C v[nP];
-#pragma unroll
-            for (int i = 0; i < nP; ++i) v[i] = sv[(qx + nP * i + nP2 * qz) * CBP + pc];
-#pragma unroll
-            for (int j = 0; j < nP; ++j) {
-                C s = 0;
-#pragma unroll
-                for (int i = 0; i < nP; ++i) s += sS[1][pc][i * nP + j] * v[i];
-                sv[(qx + nP * j + nP2 * qz) * CBP + pc] = s;
-            }
-        }
-        __syncthreads();
-        // forward x, scale by 1/(lx+ly+lz), backward x (same line, no sync)
-        for (int ln = tid / CBP; ln < nP2; ln += LPT) {
-            const int qy = ln % nP, qz = ln / nP;
-            C v[nP], w[nP];
-#pragma unroll
-            for (int i = 0; i < nP; ++i) v[i] = sv[(i + nP * ln) * CBP + pc];
-            const C lyz = sL[1][pc][qy] + sL[2][pc][qz];
-#pragma unroll
-            for (int j = 0; j < nP; ++j) {
-                C s = 0;
-#pragma unroll
-                for (int i = 0; i < nP; ++i) s += sS[0][pc][i * nP + j] * v[i];
-                w[j] = s * recip(sL[0][pc][j] + lyz);
-            }
-#pragma unroll
-            for (int i = 0; i < nP; ++i) {
-                C s = 0;
-#pragma unroll
-                for (int j = 0; j < nP; ++j) s += sS[0][pc][i * nP + j] * w[j];
-                sv[(i + nP * ln) * CBP + pc] = s;
-            }
-        }
-        __syncthreads();
-        // backward y
-        for (int ln = tid / CBP; ln < nP2; ln += LPT) {
-            const int qx = ln % nP, qz = ln / nP;
-            C v[nP];
-#pragma unroll
-            for (int j = 0; j < nP; ++j) v[j] = sv[(qx + nP * j + nP2 * qz) * CBP + pc];
-#pragma unroll
-            for (int i = 0; i < nP; ++i) {
-                C s = 0;
-#pragma unroll
-                for (int j = 0; j < nP; ++j) s += sS[1][pc][i * nP + j] * v[j];
-                sv[(qx + nP * i + nP2 * qz) * CBP + pc] = s;
-            }
-        }
-        __syncthreads();
-        // backward z and store to the patch buffer
-        C* pbuf = static_cast<C*>(pe.d);
-        const int pidx = (vi - 1) + npx * ((vj - 1) + npy * (vk - 1));
-        C* out = pbuf + (size_t)(pidx / kLanes) * nP3 * kLanes + (pidx % kLanes);
-        for (int ln = tid / CBP; ln < nP2; ln += LPT) {
-            C v[nP];
-#pragma unroll
-            for (int j = 0; j < nP; ++j) v[j] = sv[(ln + nP2 * j) * CBP + pc];
-#pragma unroll
-            for (int i = 0; i < nP; ++i) {
-                C s = 0;
-#pragma unroll
-                for (int j = 0; j < nP; ++j) s += sS[2][pc][i * nP + j] * v[j];
-                if (valid) out[(size_t)(ln + nP2 * i) * kLanes] = s;
-            }
-        }
-        __syncthreads();
-    }
-}
-
-// pe: c = z (S), d = patch buffer (C), alpha = damping; ACC: z += alpha sum.
-template <int P, typename S, int ACC, bool MULTI>
-__global__ void __launch_bounds__(256) k_pi_combine(LaunchTable L) {
-    using C = typename Prec<S>::C;
-    constexpr int N = P + 1, NN = N * N * N;
-    constexpr int nP = 2 * P - 1, nP2 = nP * nP, nP3 = nP2 * nP;
-    for (int tile = blockIdx.x; tile < L.total_tiles; tile += gridDim.x) {
-        const ProbEntry& pe = entry<MULTI>(L, tile);
-        const int blk = tile - pe.tile_begin;
-        const int n0 = pe.n[0], n1 = pe.n[1], n2 = pe.n[2];
-        const int npx = n0 - 1, npy = n1 - 1;
-        const C* pbuf = static_cast<const C*>(pe.d);
-        S* z = static_cast<S*>(pe.c) + (size_t)blk * NN * kLanes;
-        const C alpha = (C)pe.alpha;
-        for (int idx = threadIdx.x; idx < NN * kLanes; idx += 256) {
-            const int l = idx / kLanes, lane = idx % kLanes;
-            const int e = blk * kLanes + lane;
-            C sum = 0;
-            if (e < pe.ncells) {
-                const int i = e % n0, j = (e / n0) % n1, k = e / (n0 * n1);
-                const int a = l % N, b = (l / N) % N, c = l / (N * N);
-                // per direction: up to two (vertex, patch-local index) pairs,
-                // increasing vertex order
-                int vx[2], qx[2], nx = 0, vy[2], qy[2], ny = 0, vz[2], qz[2], nz = 0;
-                if (a == 0) { vx[0] = i; qx[0] = P - 1; nx = 1; }
-                else if (a == P) { vx[0] = i + 1; qx[0] = P - 1; nx = 1; }
-                else { vx[0] = i; qx[0] = P - 1 + a; vx[1] = i + 1; qx[1] = a - 1; nx = 2; }
-                if (b == 0) { vy[0] = j; qy[0] = P - 1; ny = 1; }
-                else if (b == P) { vy[0] = j + 1; qy[0] = P - 1; ny = 1; }
-                else { vy[0] = j; qy[0] = P - 1 + b; vy[1] = j + 1; qy[1] = b - 1; ny = 2; }
-                if (c == 0) { vz[0] = k; qz[0] = P - 1; nz = 1; }
-                else if (c == P) { vz[0] = k + 1; qz[0] = P - 1; nz = 1; }
-                else { vz[0] = k; qz[0] = P - 1 + c; vz[1] = k + 1; qz[1] = c - 1; nz = 2; }
-                for (int sz = 0; sz < nz; ++sz) {
-                    if (vz[sz] < 1 || vz[sz] > n2 - 1) continue;
-                    for (int sy = 0; sy < ny; ++sy) {
-                        if (vy[sy] < 1 || vy[sy] > npy) continue;
-                        for (int sx = 0; sx < nx; ++sx) {
-                            if (vx[sx] < 1 || vx[sx] > npx) continue;
-                            const int pidx = (vx[sx] - 1) + npx * ((vy[sy] - 1) + npy * (vz[sz] - 1));
-                            const int q = qx[sx] + nP * (qy[sy] + nP * qz[sz]);
-                            sum += pbuf[(size_t)(pidx / kLanes) * nP3 * kLanes + (size_t)q * kLanes + (pidx % kLanes)];
-                        }
-                    }
-                }
-            }
-            C out = alpha * sum;
-            if (ACC) out = load_as<C>(z + idx) + out;
-            if (e >= pe.ncells) out = (C)0;
-            store_from(z + idx, out);
-        }
-    }
-}
-
 // ---------------------------------------------------------------------------
-// Low-degree variants (p <= 4): the 1D eigenbasis of the current direction is
+// Low-degree variants (p <= 3): the 1D eigenbasis of the current direction is
 // held in registers during each pass (the y and z bases are shared by the
 // whole tile and read as LDS broadcasts), so LDS carries only line data.
 // Tiles are spread so that consecutive tiles (neighbouring patch rows that
@@ -3036,45 +2836,37 @@ template <int P, typename S> constexpr int pi_xcomb_tile() {
     return pi_wave_default<P, S>() ? solve_w_tile<P>() : solve_g_tile<P>();
 }
 
+// The patch inverse for p <= 3.
 template <int P, typename S>
-static hipError_t launch_pi_t(int accumulate, ProbEntry* ents, int nprob, TableStager* d_tab, hipStream_t s,
+static hipError_t launch_pi_low(int accumulate, ProbEntry* ents, int nprob, TableStager* d_tab, hipStream_t s,
                               const LaunchCfg& cfg) {
-    if constexpr (P <= 3) {
-        // default by degree and precision only (never by size or launch mix, so
-        // a problem gets the same variant alone and batched): the solves with
-        // the in-tile x-combine where they measured faster (p = 2: one
-        // wavefront per tile, in every precision; p = 3 in FP64: one
-        // workgroup per tile), the two launches through the patch buffer
-        // otherwise
-        const int dflt = pi_wave_default<P, S>() ? 4 : pi_xcomb_default<P, S>() ? 3 : 0;
-        const int gf = g_pi_fused.load(std::memory_order_relaxed);
-        const int fused = cfg.pi_fused >= 0 ? cfg.pi_fused : gf >= 0 ? gf : dflt;
-        if (fused == 3 || fused == 4) {
-            const int gc = cfg.grid_cap > 0 ? cfg.grid_cap : kMaxGrid;
-            return fused == 4 ? launch_pi_xcomb<P, S, true>(accumulate, ents, nprob, d_tab, s, gc)
-                              : launch_pi_xcomb<P, S, false>(accumulate, ents, nprob, d_tab, s, gc);
-        }
-        if (fused == 2) return launch_pi_sweep_g<P, S>(accumulate, ents, nprob, d_tab, s);
-        if (fused) return launch_pi_sweep<P, S>(accumulate, ents, nprob, d_tab, s);
+    // default by degree and precision only (never by size or launch mix, so
+    // a problem gets the same variant alone and batched): the solves with
+    // the in-tile x-combine where they measured faster (p = 2: one
+    // wavefront per tile, in every precision; p = 3 in FP64: one
+    // workgroup per tile), the two launches through the patch buffer
+    // otherwise
+    const int dflt = pi_wave_default<P, S>() ? 4 : pi_xcomb_default<P, S>() ? 3 : 0;
+    const int gf = g_pi_fused.load(std::memory_order_relaxed);
+    const int fused = cfg.pi_fused >= 0 ? cfg.pi_fused : gf >= 0 ? gf : dflt;
+    if (fused == 3 || fused == 4) {
+        const int gc = cfg.grid_cap > 0 ? cfg.grid_cap : kMaxGrid;
+        return fused == 4 ? launch_pi_xcomb<P, S, true>(accumulate, ents, nprob, d_tab, s, gc)
+                          : launch_pi_xcomb<P, S, false>(accumulate, ents, nprob, d_tab, s, gc);
     }
+    if (fused == 2) return launch_pi_sweep_g<P, S>(accumulate, ents, nprob, d_tab, s);
+    if (fused) return launch_pi_sweep<P, S>(accumulate, ents, nprob, d_tab, s);
     const int gcap = cfg.grid_cap > 0 ? cfg.grid_cap : kMaxGrid;
-    if constexpr (P >= 4) {
-        const int gf = g_pi_fused.load(std::memory_order_relaxed);
-        const int mode = cfg.pi_fused >= 0 ? cfg.pi_fused : gf >= 0 ? gf : 0;
-        if (mode != 2) return launch_pi_lines<P, S>(accumulate, ents, nprob, d_tab, s);
-    }
     using C = typename Prec<S>::C;
     constexpr int CBP = pi_patches_per_tile<P, C>();
-    if constexpr (P <= 3) {
-        if (nprob == 1 && !g_restrict_from_cells && g_combine_per_cell != 1) {
-            // slabs of at most ~pi_slab_bytes of patch results (one slab: plain two launches)
-            const size_t pbytes = (size_t)(ents[0].n[0] - 1) * (ents[0].n[1] - 1) * (ents[0].n[2] - 1) *
-                                  (2 * P - 1) * (2 * P - 1) * (2 * P - 1) * sizeof(C);
-            const size_t slab_mb = (size_t)g_pi_slab_mb.load(std::memory_order_relaxed);
-            int nslab = slab_mb > 0 ? (int)((pbytes + (slab_mb << 20) - 1) / (slab_mb << 20)) : 1;
-            nslab = std::max(1, std::min(nslab, std::max(1, ents[0].n[2] - 1)));
-            if (nslab > 1) return launch_pi_slabs<P, S>(accumulate, ents[0], s, nslab, gcap);
-        }
+    if (nprob == 1 && !g_restrict_from_cells && g_combine_per_cell != 1) {
+        // slabs of at most ~pi_slab_bytes of patch results (one slab: plain two launches)
+        const size_t pbytes = (size_t)(ents[0].n[0] - 1) * (ents[0].n[1] - 1) * (ents[0].n[2] - 1) *
+                              (2 * P - 1) * (2 * P - 1) * (2 * P - 1) * sizeof(C);
+        const size_t slab_mb = (size_t)g_pi_slab_mb.load(std::memory_order_relaxed);
+        int nslab = slab_mb > 0 ? (int)((pbytes + (slab_mb << 20) - 1) / (slab_mb << 20)) : 1;
+        nslab = std::max(1, std::min(nslab, std::max(1, ents[0].n[2] - 1)));
+        if (nslab > 1) return launch_pi_slabs<P, S>(accumulate, ents[0], s, nslab, gcap);
     }
     LaunchTable L{};
     int tiles = 0;
@@ -3086,49 +2878,37 @@ static hipError_t launch_pi_t(int accumulate, ProbEntry* ents, int nprob, TableS
     }
     L.nprob = nprob;
     L.total_tiles = tiles;
-    // the default p <= 3 path stages its own tables (assembly, solves)
-    const bool own_tables = (P <= 3) && !g_restrict_from_cells;
+    // the default path stages its own tables (assembly, solves)
+    const bool own_tables = !g_restrict_from_cells;
     hipError_t err = own_tables ? hipSuccess : stage_table(L, ents, nprob, d_tab, s);
     if (err != hipSuccess) return err;
     if (tiles > 0) {
-        if constexpr (P <= 3) {
-            const int grid = (tiles + 7) / 8 * 8;
-            if (g_restrict_from_cells) {
-                TraceSpan ts("pi_solve", P, Prec<S>::id, s);
-                if (nprob > 1) hipLaunchKernelGGL((k_pi_solve_r<P, S, CBP, true>), dim3(grid), dim3(256), 0, s, L);
-                else hipLaunchKernelGGL((k_pi_solve_r<P, S, CBP, false>), dim3(grid), dim3(256), 0, s, L);
-            } else {
-                err = launch_assemble<P, S>(ents, nprob, d_tab, s);
-                if (err != hipSuccess) return err;
-                int t1 = 0;
-                for (int i = 0; i < nprob; ++i) {
-                    const int npx = ents[i].n[0] - 1, npy = ents[i].n[1] - 1, npz = ents[i].n[2] - 1;
-                    ents[i].tile_begin = t1;
-                    constexpr int TG = solve_g_tile<P>();
-                    ents[i].ntiles = (npx > 0 && npy > 0 && npz > 0) ? ((npx + TG - 1) / TG) * npy * npz : 0;
-                    t1 += ents[i].ntiles;
-                }
-                LaunchTable Lg{};
-                Lg.nprob = nprob;
-                Lg.total_tiles = t1;
-                err = stage_table(Lg, ents, nprob, d_tab, s);
-                if (err != hipSuccess) return err;
-                TraceSpan ts("pi_solve", P, Prec<S>::id, s);
-                constexpr int TG = solve_g_tile<P>();
-                const int grid_g = (t1 + 7) / 8 * 8;
-                if (nprob > 1) hipLaunchKernelGGL((k_pi_solve_g<P, S, TG, true>), dim3(grid_g), dim3(256), 0, s, Lg);
-                else hipLaunchKernelGGL((k_pi_solve_g<P, S, TG, false>), dim3(grid_g), dim3(256), 0, s, Lg);
-            }
-        } else if constexpr (P == 4) {
-            const int grid = (tiles + 7) / 8 * 8;
+        const int grid = (tiles + 7) / 8 * 8;
+        if (g_restrict_from_cells) {
             TraceSpan ts("pi_solve", P, Prec<S>::id, s);
             if (nprob > 1) hipLaunchKernelGGL((k_pi_solve_r<P, S, CBP, true>), dim3(grid), dim3(256), 0, s, L);
             else hipLaunchKernelGGL((k_pi_solve_r<P, S, CBP, false>), dim3(grid), dim3(256), 0, s, L);
         } else {
-            const int grid = tiles < gcap ? tiles : gcap;
+            err = launch_assemble<P, S>(ents, nprob, d_tab, s);
+            if (err != hipSuccess) return err;
+            int t1 = 0;
+            for (int i = 0; i < nprob; ++i) {
+                const int npx = ents[i].n[0] - 1, npy = ents[i].n[1] - 1, npz = ents[i].n[2] - 1;
+                ents[i].tile_begin = t1;
+                constexpr int TG = solve_g_tile<P>();
+                ents[i].ntiles = (npx > 0 && npy > 0 && npz > 0) ? ((npx + TG - 1) / TG) * npy * npz : 0;
+                t1 += ents[i].ntiles;
+            }
+            LaunchTable Lg{};
+            Lg.nprob = nprob;
+            Lg.total_tiles = t1;
+            err = stage_table(Lg, ents, nprob, d_tab, s);
+            if (err != hipSuccess) return err;
             TraceSpan ts("pi_solve", P, Prec<S>::id, s);
-            if (nprob > 1) hipLaunchKernelGGL((k_pi_solve<P, S, CBP, true>), dim3(grid), dim3(256), 0, s, L);
-            else hipLaunchKernelGGL((k_pi_solve<P, S, CBP, false>), dim3(grid), dim3(256), 0, s, L);
+            constexpr int TG = solve_g_tile<P>();
+            const int grid_g = (t1 + 7) / 8 * 8;
+            if (nprob > 1) hipLaunchKernelGGL((k_pi_solve_g<P, S, TG, true>), dim3(grid_g), dim3(256), 0, s, Lg);
+            else hipLaunchKernelGGL((k_pi_solve_g<P, S, TG, false>), dim3(grid_g), dim3(256), 0, s, Lg);
         }
         err = hipGetLastError();
         if (err != hipSuccess) return err;
@@ -3145,80 +2925,75 @@ static hipError_t launch_pi_t(int accumulate, ProbEntry* ents, int nprob, TableS
     L2.total_tiles = tiles2;
     err = stage_table(L2, ents, nprob, d_tab, s);
     if (err != hipSuccess) return err;
-    if constexpr (P <= 3) {
-        if (g_combine_per_cell == 1) {
-            const int grid = (tiles2 + 3) / 4;
-            TraceSpan ts("pi_combine", P, Prec<S>::id, s);
-            if (nprob > 1) {
-                if (accumulate) hipLaunchKernelGGL((k_pi_combine_cell<P, S, 1, true>), dim3(grid), dim3(256), 0, s, L2);
-                else hipLaunchKernelGGL((k_pi_combine_cell<P, S, 0, true>), dim3(grid), dim3(256), 0, s, L2);
-            } else {
-                if (accumulate) hipLaunchKernelGGL((k_pi_combine_cell<P, S, 1, false>), dim3(grid), dim3(256), 0, s, L2);
-                else hipLaunchKernelGGL((k_pi_combine_cell<P, S, 0, false>), dim3(grid), dim3(256), 0, s, L2);
-            }
-            return hipGetLastError();
-        }
-        // FP64 on long rows: one wavefront per global node row, each patch
-        // value read once (identical results to the per-plane combine below,
-        // which is the faster one for 4-byte values)
-        bool long_rows = Prec<S>::id == FEM_F64;
-        for (int i = 0; i < nprob; ++i) long_rows = long_rows && ents[i].n[0] >= 48;
-        if (long_rows) {
-            int t4 = 0;
-            for (int i = 0; i < nprob; ++i) {
-                const int rows = (ents[i].n[1] * P + 1) * (ents[i].n[2] * P + 1);
-                ents[i].tile_begin = t4;
-                ents[i].ntiles = (rows + 3) / 4;
-                t4 += ents[i].ntiles;
-            }
-            LaunchTable L4{};
-            L4.nprob = nprob;
-            L4.total_tiles = t4;
-            err = stage_table(L4, ents, nprob, d_tab, s);
-            if (err != hipSuccess) return err;
-            TraceSpan ts("pi_combine", P, Prec<S>::id, s);
-            if (nprob > 1) {
-                if (accumulate) hipLaunchKernelGGL((k_pi_combine_rows<P, S, 1, true>), dim3(t4), dim3(256), 0, s, L4);
-                else hipLaunchKernelGGL((k_pi_combine_rows<P, S, 0, true>), dim3(t4), dim3(256), 0, s, L4);
-            } else {
-                if (accumulate) hipLaunchKernelGGL((k_pi_combine_rows<P, S, 1, false>), dim3(t4), dim3(256), 0, s, L4);
-                else hipLaunchKernelGGL((k_pi_combine_rows<P, S, 0, false>), dim3(t4), dim3(256), 0, s, L4);
-            }
-            return hipGetLastError();
-        }
-        // one wavefront per (block, plane)
-        int t3 = 0;
-        for (int i = 0; i < nprob; ++i) {
-            ents[i].tile_begin = t3;
-            ents[i].ntiles = ents[i].nblk * (P + 1) * ((P + 1 + combine_brows<P>() - 1) / combine_brows<P>());
-            t3 += ents[i].ntiles;
-        }
-        LaunchTable L3{};
-        L3.nprob = nprob;
-        L3.total_tiles = t3;
-        err = stage_table(L3, ents, nprob, d_tab, s);
-        if (err != hipSuccess) return err;
-        const int grid = ((t3 + 3) / 4 + 7) / 8 * 8;
+    if (g_combine_per_cell == 1) {
+        const int grid = (tiles2 + 3) / 4;
         TraceSpan ts("pi_combine", P, Prec<S>::id, s);
         if (nprob > 1) {
-            if (accumulate) hipLaunchKernelGGL((k_pi_combine_planes<P, S, 1, true>), dim3(grid), dim3(256), 0, s, L3);
-            else hipLaunchKernelGGL((k_pi_combine_planes<P, S, 0, true>), dim3(grid), dim3(256), 0, s, L3);
+            if (accumulate) hipLaunchKernelGGL((k_pi_combine_cell<P, S, 1, true>), dim3(grid), dim3(256), 0, s, L2);
+            else hipLaunchKernelGGL((k_pi_combine_cell<P, S, 0, true>), dim3(grid), dim3(256), 0, s, L2);
         } else {
-            if (accumulate) hipLaunchKernelGGL((k_pi_combine_planes<P, S, 1, false>), dim3(grid), dim3(256), 0, s, L3);
-            else hipLaunchKernelGGL((k_pi_combine_planes<P, S, 0, false>), dim3(grid), dim3(256), 0, s, L3);
+            if (accumulate) hipLaunchKernelGGL((k_pi_combine_cell<P, S, 1, false>), dim3(grid), dim3(256), 0, s, L2);
+            else hipLaunchKernelGGL((k_pi_combine_cell<P, S, 0, false>), dim3(grid), dim3(256), 0, s, L2);
         }
         return hipGetLastError();
     }
-    const int grid2 = tiles2 < gcap ? tiles2 : gcap;
+    // FP64 on long rows: one wavefront per global node row, each patch
+    // value read once (identical results to the per-plane combine below,
+    // which is the faster one for 4-byte values)
+    bool long_rows = Prec<S>::id == FEM_F64;
+    for (int i = 0; i < nprob; ++i) long_rows = long_rows && ents[i].n[0] >= 48;
+    if (long_rows) {
+        int t4 = 0;
+        for (int i = 0; i < nprob; ++i) {
+            const int rows = (ents[i].n[1] * P + 1) * (ents[i].n[2] * P + 1);
+            ents[i].tile_begin = t4;
+            ents[i].ntiles = (rows + 3) / 4;
+            t4 += ents[i].ntiles;
+        }
+        LaunchTable L4{};
+        L4.nprob = nprob;
+        L4.total_tiles = t4;
+        err = stage_table(L4, ents, nprob, d_tab, s);
+        if (err != hipSuccess) return err;
+        TraceSpan ts("pi_combine", P, Prec<S>::id, s);
+        if (nprob > 1) {
+            if (accumulate) hipLaunchKernelGGL((k_pi_combine_rows<P, S, 1, true>), dim3(t4), dim3(256), 0, s, L4);
+            else hipLaunchKernelGGL((k_pi_combine_rows<P, S, 0, true>), dim3(t4), dim3(256), 0, s, L4);
+        } else {
+            if (accumulate) hipLaunchKernelGGL((k_pi_combine_rows<P, S, 1, false>), dim3(t4), dim3(256), 0, s, L4);
+            else hipLaunchKernelGGL((k_pi_combine_rows<P, S, 0, false>), dim3(t4), dim3(256), 0, s, L4);
+        }
+        return hipGetLastError();
+    }
+    // one wavefront per (block, plane)
+    int t3 = 0;
+    for (int i = 0; i < nprob; ++i) {
+        ents[i].tile_begin = t3;
+        ents[i].ntiles = ents[i].nblk * (P + 1) * ((P + 1 + combine_brows<P>() - 1) / combine_brows<P>());
+        t3 += ents[i].ntiles;
+    }
+    LaunchTable L3{};
+    L3.nprob = nprob;
+    L3.total_tiles = t3;
+    err = stage_table(L3, ents, nprob, d_tab, s);
+    if (err != hipSuccess) return err;
+    const int grid = ((t3 + 3) / 4 + 7) / 8 * 8;
     TraceSpan ts("pi_combine", P, Prec<S>::id, s);
     if (nprob > 1) {
-        if (accumulate) hipLaunchKernelGGL((k_pi_combine<P, S, 1, true>), dim3(grid2), dim3(256), 0, s, L2);
-        else hipLaunchKernelGGL((k_pi_combine<P, S, 0, true>), dim3(grid2), dim3(256), 0, s, L2);
+        if (accumulate) hipLaunchKernelGGL((k_pi_combine_planes<P, S, 1, true>), dim3(grid), dim3(256), 0, s, L3);
+        else hipLaunchKernelGGL((k_pi_combine_planes<P, S, 0, true>), dim3(grid), dim3(256), 0, s, L3);
     } else {
-        if (accumulate) hipLaunchKernelGGL((k_pi_combine<P, S, 1, false>), dim3(grid2), dim3(256), 0, s, L2);
-        else hipLaunchKernelGGL((k_pi_combine<P, S, 0, false>), dim3(grid2), dim3(256), 0, s, L2);
+        if (accumulate) hipLaunchKernelGGL((k_pi_combine_planes<P, S, 1, false>), dim3(grid), dim3(256), 0, s, L3);
+        else hipLaunchKernelGGL((k_pi_combine_planes<P, S, 0, false>), dim3(grid), dim3(256), 0, s, L3);
     }
     return hipGetLastError();
+}
+
+template <int P, typename S>
+static hipError_t launch_pi_t(int accumulate, ProbEntry* ents, int nprob, TableStager* d_tab, hipStream_t s,
+                              const LaunchCfg& cfg) {
+    if constexpr (P >= 4) return launch_pi_lines<P, S>(accumulate, ents, nprob, d_tab, s);
+    else return launch_pi_low<P, S>(accumulate, ents, nprob, d_tab, s, cfg);
 }
 
 template <int P>

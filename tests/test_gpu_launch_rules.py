@@ -1,0 +1,46 @@
+"""Rules that pick a kernel or its launch: the same results on both sides of
+each line, and no launch that a rule says is not needed."""
+import numpy as np
+import pytest
+
+from oracle import operators
+from tests.gpu_util import check_err, graded, note, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def F():
+    import torch
+    from paper_2607_02335_amd import fem
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    fem.lib()
+    return fem
+
+
+def _launches(F, label, call):
+    import torch
+    torch.cuda.synchronize()
+    F.trace_enable(True)
+    try:
+        call()
+        torch.cuda.synchronize()
+        return sum(k["launches"] for k in F.trace_read() if k["label"] == label)
+    finally:
+        F.trace_enable(False)
+
+
+@pytest.mark.parametrize("p", [4, 5, 6, 7])
+@pytest.mark.parametrize("prec", [0, 1, 2, 3])
+def test_pi_fused_has_no_effect_from_degree_4(F, p, prec):
+    note(f"pi_fused p={p} prec={prec}")
+    m, w, rng = graded(p, (3, 4, 2), 30 + p)
+    P = F.Problem(p, m.n, w)
+    r = P.pack(to_dev(rng.uniform(-1, 1, m.ncells * m.n1 ** 3)), prec)
+    z = P.patch_inverse(r)
+    try:
+        for v in range(5):
+            F.set_option(F.OPT_PI_FUSED, v)
+            assert bool((P.patch_inverse(r) == z).all()), v
+    finally:
+        F.set_option(F.OPT_PI_FUSED, -1)
