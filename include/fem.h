@@ -296,17 +296,17 @@ fem_status fem_batch_apply(fem_batch* B, void* const* x, void* const* y, int pre
 fem_status fem_batch_patch_inverse(fem_batch* B, void* const* r, void* const* z, int prec);
 /* Tile-shape autotuner: for each degree present in the batch, time the
  * candidate kernel shapes on the batch's own problems (apply: the default
- * kernel (register for p <= 3; for p >= 4 output planes in 4-byte arithmetic,
- * plane-streamed in FP64, matrix-core for p = 7 in FP64) or the LDS line
- * kernel, and for p = 7 also the plane-streamed kernel, each x two persistent
- * grid caps; patch inverse for p <= 3: two launches through
- * the patch buffer, fused sweep from the cell copies, fused sweep from the
- * assembled residual, or solves with the in-tile x-combine, per workgroup or
- * per wavefront; for p >= 4 one kernel; each x two grid caps) and keep the
- * fastest for later batched calls.  choice (may be
- * NULL): int[14], choice[2(p-1)] = apply candidate index, choice[2(p-1)+1]
- * = patch-inverse candidate index of degree p, candidates in the order
- * listed with the grid cap varying fastest (untouched for absent degrees).
+ * kernel (register for p <= 3; output planes for p >= 4 in 4-byte arithmetic
+ * and p = 4, 5 in FP64; in FP64 plane-streamed for p = 6, matrix-core for
+ * p = 7) or the LDS line kernel, and for p = 7 also the plane-streamed kernel;
+ * patch inverse for p <= 3: two launches through the patch buffer, fused sweep
+ * from the cell copies, fused sweep from the assembled residual, or solves with
+ * the in-tile x-combine, per workgroup or per wavefront; for p >= 4 one kernel;
+ * the applies with a persistent grid x two grid caps) and keep the fastest for
+ * later batched calls.  choice (may be NULL): int[14], choice[2(p-1)] = apply
+ * candidate index, choice[2(p-1)+1] = patch-inverse candidate index of degree p,
+ * twice the kernel's place in the order listed, plus one for the second grid
+ * cap (untouched for absent degrees).
  * Where mixed-degree launches are possible it then times a whole pass
  * (apply + patch inverse) with the tuned per-degree launches and with the
  * mixed launches and keeps the faster (fem_batch_mixed reports which).

@@ -196,8 +196,9 @@ extern "C" fem_status fem_batch_patch_inverse(fem_batch* B, void* const* r, void
 
 // Autotuner: for each degree present, time every candidate kernel shape on
 // this batch's own problems (all problems of that degree in one launch) and
-// keep the fastest.  Candidates: apply = {register/LDS kernel} x {grid cap};
-// patch inverse = {two-phase, fused sweep (p <= 3)} x {grid cap}.
+// keep the fastest.  Candidates: kernel x grid cap; the second cap is timed only
+// for kernels with a persistent grid (the others would run the same launch twice
+// and noise would choose), so the others' index is that of the first.
 extern "C" fem_status fem_batch_autotune(fem_batch* B, int prec, int* choice) {
     if (!B) return set_error(FEM_EINVAL, "fem_batch_autotune: NULL batch");
     if (prec < FEM_F64 || prec > FEM_F16) return set_error(FEM_EINVAL, "unknown precision");
@@ -221,9 +222,10 @@ extern "C" fem_status fem_batch_autotune(fem_batch* B, int prec, int* choice) {
     for (int p = 1; p <= kMaxP && result == FEM_OK; ++p) {
         if (B->group[p].empty()) continue;
         for (int which = 0; which < 2 && result == FEM_OK; ++which) {
-            // apply: 0 = register (p <= 3) / output-plane (p >= 4, 4-byte) /
-            //        plane-streamed (p >= 4, FP64; matrix-core for p = 7) kernel,
-            //        1 = LDS line kernel, 2 = plane-streamed (p = 7);
+            // apply: 0 = register (p <= 3) / output-plane (p >= 4 in 4-byte arithmetic,
+            //        p = 4, 5 in FP64) / plane-streamed (p = 6 in FP64) / matrix-core
+            //        (p = 7 in FP64) kernel, 1 = LDS line kernel, 2 = plane-streamed
+            //        (p = 7);
             // patch inverse, p <= 3: 0 = two launches through the patch buffer,
             //        1 = fused sweep summing cell copies, 2 = fused sweep from the
             //        assembled residual, 3 = solves with the in-tile x-combine,
@@ -240,9 +242,14 @@ extern "C" fem_status fem_batch_autotune(fem_batch* B, int prec, int* choice) {
                     cand.push_back(cfg);
                 }
             }
+            std::vector<ProbEntry> ents;
+            for (int i : B->group[p]) ents.push_back(entry_of(B->probs[i]));
             float best = 1e30f;
             int best_i = 0;
             for (size_t ci = 0; ci < cand.size(); ++ci) {
+                if (ci % 2 == 1 && (which == 1 || !apply_takes_cap(p, prec, cand[ci].apply_lds, ents.data(),
+                                                                   (int)ents.size())))
+                    continue;
                 LaunchCfg cfgs[kMaxP + 1];
                 for (int q = 0; q <= kMaxP; ++q) cfgs[q] = which == 0 ? B->cfg_apply[q] : B->cfg_pi[q];
                 cfgs[p] = cand[ci];

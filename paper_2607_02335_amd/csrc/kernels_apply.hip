@@ -1112,6 +1112,32 @@ static hipError_t launch_apply_p(int prec, int mode, ProbEntry* e, int n, TableS
     }
 }
 
+template <int P, typename C>
+static bool apply_takes_cap_p(int apply_lds, const ProbEntry* ents, int nprob) {
+    if (apply_lds) return true;
+    int blocks = 0;
+    for (int i = 0; i < nprob; ++i) blocks += ents[i].nblk;
+    if (P <= 3) return P == 1 || blocks > split_tiles<kApplyLaplace, C>();
+    return !apply_plane_default<P, kApplyLaplace, C>();
+}
+
+bool apply_takes_cap(int p, int prec, int apply_lds, const ProbEntry* ents, int nprob) {
+    auto by_prec = [&](auto d) {
+        constexpr int P = decltype(d)::value;
+        return prec == FEM_F64 ? apply_takes_cap_p<P, double>(apply_lds, ents, nprob)
+                               : apply_takes_cap_p<P, float>(apply_lds, ents, nprob);
+    };
+    switch (p) {
+        case 1: return by_prec(std::integral_constant<int, 1>{});
+        case 2: return by_prec(std::integral_constant<int, 2>{});
+        case 3: return by_prec(std::integral_constant<int, 3>{});
+        case 4: return by_prec(std::integral_constant<int, 4>{});
+        case 5: return by_prec(std::integral_constant<int, 5>{});
+        case 6: return by_prec(std::integral_constant<int, 6>{});
+        default: return by_prec(std::integral_constant<int, 7>{});
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Mixed-degree apply: the register body for p = 2, 3 (four storage blocks
 // per item, one per wavefront) and for p = 7 in 4-byte arithmetic the

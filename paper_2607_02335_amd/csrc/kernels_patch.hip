@@ -2725,7 +2725,7 @@ static hipError_t launch_pi_lines(int accumulate, ProbEntry* ents, int nprob, Ta
 // arithmetic as one launch of each (the results are identical); tiles are
 // offset through the entry's tile_begin.
 template <int P, typename S>
-static hipError_t launch_pi_slabs(int accumulate, ProbEntry e, hipStream_t s, int nslab, int gcap) {
+static hipError_t launch_pi_slabs(int accumulate, ProbEntry e, hipStream_t s, int nslab) {
     constexpr int CBP = solve_g_tile<P>();
     constexpr int N = P + 1;
     hipError_t err = launch_assemble<P, S>(&e, 1, nullptr, s);
@@ -2770,8 +2770,7 @@ static hipError_t launch_pi_slabs(int accumulate, ProbEntry e, hipStream_t s, in
 // Patch inverse for p <= 3 through the x-combined buffer: assembly, the
 // solves with the in-tile x-combine, the combine by global node rows.
 template <int P, typename S, bool WAVE>
-static hipError_t launch_pi_xcomb(int accumulate, ProbEntry* ents, int nprob, TableStager* d_tab, hipStream_t s,
-                                  int gcap) {
+static hipError_t launch_pi_xcomb(int accumulate, ProbEntry* ents, int nprob, TableStager* d_tab, hipStream_t s) {
     constexpr int CBP = WAVE ? solve_w_tile<P>() : solve_g_tile<P>();
     hipError_t err = launch_assemble<P, S>(ents, nprob, d_tab, s);
     if (err != hipSuccess) return err;
@@ -2849,14 +2848,10 @@ static hipError_t launch_pi_low(int accumulate, ProbEntry* ents, int nprob, Tabl
     const int dflt = pi_wave_default<P, S>() ? 4 : pi_xcomb_default<P, S>() ? 3 : 0;
     const int gf = g_pi_fused.load(std::memory_order_relaxed);
     const int fused = cfg.pi_fused >= 0 ? cfg.pi_fused : gf >= 0 ? gf : dflt;
-    if (fused == 3 || fused == 4) {
-        const int gc = cfg.grid_cap > 0 ? cfg.grid_cap : kMaxGrid;
-        return fused == 4 ? launch_pi_xcomb<P, S, true>(accumulate, ents, nprob, d_tab, s, gc)
-                          : launch_pi_xcomb<P, S, false>(accumulate, ents, nprob, d_tab, s, gc);
-    }
+    if (fused == 4) return launch_pi_xcomb<P, S, true>(accumulate, ents, nprob, d_tab, s);
+    if (fused == 3) return launch_pi_xcomb<P, S, false>(accumulate, ents, nprob, d_tab, s);
     if (fused == 2) return launch_pi_sweep_g<P, S>(accumulate, ents, nprob, d_tab, s);
     if (fused) return launch_pi_sweep<P, S>(accumulate, ents, nprob, d_tab, s);
-    const int gcap = cfg.grid_cap > 0 ? cfg.grid_cap : kMaxGrid;
     using C = typename Prec<S>::C;
     constexpr int CBP = pi_patches_per_tile<P, C>();
     if (nprob == 1 && !g_restrict_from_cells && g_combine_per_cell != 1) {
@@ -2866,7 +2861,7 @@ static hipError_t launch_pi_low(int accumulate, ProbEntry* ents, int nprob, Tabl
         const size_t slab_mb = (size_t)g_pi_slab_mb.load(std::memory_order_relaxed);
         int nslab = slab_mb > 0 ? (int)((pbytes + (slab_mb << 20) - 1) / (slab_mb << 20)) : 1;
         nslab = std::max(1, std::min(nslab, std::max(1, ents[0].n[2] - 1)));
-        if (nslab > 1) return launch_pi_slabs<P, S>(accumulate, ents[0], s, nslab, gcap);
+        if (nslab > 1) return launch_pi_slabs<P, S>(accumulate, ents[0], s, nslab);
     }
     LaunchTable L{};
     int tiles = 0;

@@ -120,6 +120,9 @@ inline hipError_t stage_table(LaunchTable& L, const ProbEntry* ents, int nprob, 
 // apply: mode 0 y=Ax (a=x, c=y), 1 y=b-Ax (a=x, b=b, c=y), 2 y=Mx.
 hipError_t launch_apply(int p, int prec, int mode, ProbEntry* ents, int nprob, TableStager* st,
                         hipStream_t s, const LaunchCfg& cfg = LaunchCfg());
+// Whether the Laplace apply of these problems (of degree p) by kernel apply_lds has
+// a persistent grid, which cfg.grid_cap bounds.  The patch inverse has none.
+bool apply_takes_cap(int p, int prec, int apply_lds, const ProbEntry* ents, int nprob);
 // apply over problems of any degrees: with `mix`, one mixed-degree launch
 // when the degrees are two or three of {2, 3, 7}, else one launch per degree
 // (the same kernel bodies and results either way)

@@ -44,3 +44,18 @@ def test_pi_fused_has_no_effect_from_degree_4(F, p, prec):
             assert bool((P.patch_inverse(r) == z).all()), v
     finally:
         F.set_option(F.OPT_PI_FUSED, -1)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_autotune_times_a_launch_once(F, prec):
+    """Kernels without a persistent grid are timed with one cap: a warm-up and
+    three runs of each kernel, the first index."""
+    note(f"autotune prec={prec}")
+    B = F.Batch([(p, (5, 4, 3), None) for p in (2, 4, 7, 7)])
+    choice = {}
+    n = _launches(F, "pi_solve", lambda: choice.update(B.autotune(prec)))
+    # degrees 4 and 7: one kernel; degree 2: three kernels with a patch solve
+    # launch of their own (the fused sweeps have none)
+    assert n == 4 * (1 + 1 + 3)
+    assert all(pi % 2 == 0 for _, pi in choice.values()), choice
+    B.close()
