@@ -59,3 +59,22 @@ def test_autotune_times_a_launch_once(F, prec):
     assert n == 4 * (1 + 1 + 3)
     assert all(pi % 2 == 0 for _, pi in choice.values()), choice
     B.close()
+
+
+@pytest.mark.parametrize("p", [4, 5, 6, 7])
+@pytest.mark.parametrize("prec", [0, 1, 2, 3])
+def test_padding_cells_take_no_part(F, p, prec):
+    """Whatever a vector holds in its padding cells, the applies and the residual
+    write zero there and the same values elsewhere."""
+    import torch
+    note(f"padding p={p} prec={prec}")
+    m, w, rng = graded(p, (3, 2, 2), 890 + p)
+    P = F.Problem(p, m.n, w)
+    x = P.pack(to_dev(rng.uniform(-1, 1, m.ncells * m.n1 ** 3)), prec)
+    bad = x.clone().view(-1, 64)
+    bad[:, m.ncells:] = float("nan")
+    bad = bad.view(-1)
+    for f in (P.apply, P.mass_apply, lambda v: P.smoother_step(v, sweeps=2, omega=0.125)):
+        y = f(x)
+        assert not bool(y.view(-1, 64)[:, m.ncells:].any())
+        assert bool((f(bad) == y).all())
