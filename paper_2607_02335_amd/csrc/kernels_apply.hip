@@ -625,6 +625,17 @@ template <int P, int MODE, typename C> constexpr bool apply_plane_default() {
     return P >= 4 && (sizeof(C) == 4 || (MODE == kApplyMass ? P == 4 || P == 6 : P <= 5));
 }
 
+// Storage blocks of a problem from which it takes the output planes; a smaller one
+// keeps k_apply_planes.  A wavefront here streams the whole cell, plane after
+// plane, where the workgroups of k_apply_planes divide 16 cells among 256 threads,
+// so a few blocks take as long as a full chip: mass p = 6 in FP64, n^3 cells,
+// planes streamed against output planes, us: n = 4 13 and 14, 8 13 and 15, 16 (64
+// blocks) 15 and 16, 18 (92 blocks) 18 and 17, 24 37 and 28.  The other forms are as
+// fast from one block on.
+template <int P, int MODE, typename C> constexpr int apply_plane_blocks() {
+    return apply_plane_default<P, MODE, C>() && sizeof(C) == 8 && P == 6 ? 80 : 0;
+}
+
 // ---------------------------------------------------------------------------
 // Plane-streamed apply for p >= 4.  A workgroup owns 16 consecutive cells of
 // a storage block (so every load and store is a 128-byte run of one node
@@ -1019,12 +1030,15 @@ static hipError_t launch_apply_t(ProbEntry* ents, int nprob, TableStager* d_tab,
     const int force_lds = cfg.apply_lds;
     const int gcap = cfg.grid_cap > 0 ? cfg.grid_cap : kMaxGrid;
     using C = typename Prec<S>::C;
+    constexpr int kFrom = apply_plane_blocks<P, MODE, C>();
+    bool large = true;                  // (mass applies are launched one problem at a time)
+    for (int i = 0; i < nprob; ++i) large = large && ents[i].nblk >= kFrom;
     const RefMats<P, C> R = ref_mats<P, C>();
     const bool use_reg = (P <= 3) && !force_lds;
     // p = 7 (Laplace, residual): the matrix-core apply unless the plane-streamed
     // one is asked for (apply_lds = 2, or the process-wide option)
     const bool use_mfma = apply_mfma_default<P, MODE, C>() && !force_lds && g_apply_planes_p7 == 0;
-    const bool use_plane = apply_plane_default<P, MODE, C>() && !force_lds;
+    const bool use_plane = apply_plane_default<P, MODE, C>() && !force_lds && large;
     const bool use_planes = (P >= 4) && !use_mfma && !use_plane && (force_lds == 0 || (force_lds == 2 && P == 7));
     constexpr int CB = lds_cells<P>((int)sizeof(C));
     constexpr int MCB = ApplyMfmaShape<C>::CB;
@@ -1075,7 +1089,7 @@ static hipError_t launch_apply_t(ProbEntry* ents, int nprob, TableStager* d_tab,
             return hipGetLastError();
         }
     }
-    if constexpr (P == 7 || (P >= 4 && !apply_plane_default<P, MODE, C>())) {
+    if constexpr (P == 7 || (P >= 4 && (!apply_plane_default<P, MODE, C>() || kFrom > 0))) {
         if (use_planes) {
             const int grid = tiles < gcap ? tiles : gcap;
             constexpr int NT = PlanesShape<P, C>::NT;

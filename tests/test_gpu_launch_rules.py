@@ -78,3 +78,16 @@ def test_padding_cells_take_no_part(F, p, prec):
         y = f(x)
         assert not bool(y.view(-1, 64)[:, m.ncells:].any())
         assert bool((f(bad) == y).all())
+
+
+@pytest.mark.parametrize("n", [(17, 17, 17), (18, 17, 17)])
+def test_fp64_mass_on_both_sides_of_the_plane_limit(F, n):
+    """The FP64 mass apply at p = 6 takes the output planes from 80 storage
+    blocks on."""
+    note(f"plane limit n={n}")
+    m, w, rng = graded(6, n, 886)
+    assert (m.ncells + 63) // 64 in (77, 82)
+    P = F.Problem(6, n, w)
+    xd = P.pack(to_dev(rng.uniform(-1, 1, m.ncells * m.n1 ** 3)))
+    y = to_np(P.unpack(P.mass_apply(xd)))
+    check_err(y, operators.mass_cells(m, to_np(P.unpack(xd))), 1e-12, f"mass n={n}")
