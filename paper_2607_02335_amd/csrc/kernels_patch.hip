@@ -1413,38 +1413,42 @@ __device__ __forceinline__ void assemble_body(const LaunchTable& L, int item, in
         const int n0 = pe.n[0], n1 = pe.n[1], n2 = pe.n[2];
         const BlockRow br = block_row<P>(pe, wave);
         const int b = br.b, c = br.c;
-        const int e = br.blk * kLanes + lane;
+        const int e = min(br.e0 + lane, pe.nblk * kLanes - 1);
         const int i = e % n0, j = (e / n0) % n1, k = e / (n0 * n1);
-        const bool own = e < pe.ncells && (b < P || j == n1 - 1) && (c < P || k == n2 - 1);
-        if (__ballot(own) == 0) continue;
+        const bool own = br.e0 + lane < br.e1 && (c < P || k == n2 - 1);
         const S* v = static_cast<const S*>(pe.a);
+        // the loads of all copies first, in flight together (a lane without a
+        // copy reads its own cell's and drops it), then the sums
+        double val[4][N], left[4];
+#pragma unroll
+        for (int q = 3; q >= 0; --q) {
+            const int y = q % 2, z = q / 2;
+            left[q] = 0.0;
+#pragma unroll
+            for (int a = 0; a < N; ++a) val[q][a] = 0.0;
+            if ((z && c != 0) || (y && b != 0)) continue;          // uniform: no lower copy of this row
+            const bool ok = own && (!z || k > 0) && (!y || j > 0);
+            const int ee = ok ? e - (z ? n0 * n1 : 0) - (y ? n0 : 0) : e;
+            const int lyz = N * ((y ? P : b) + N * (z ? P : c));
+            const S* src = v + cell_offset(ee, lyz, NN);
+#pragma unroll
+            for (int a = 0; a < N; ++a)
+                val[q][a] = P >= 4 ? load_as<double>(src + a * kLanes) : load_stream<double>(src + a * kLanes);
+            if (lane == 0 && ok && i > 0) left[q] = load_as<double>(v + cell_offset(ee - 1, P + lyz, NN));
+        }
         double acc[N];
 #pragma unroll
         for (int a = 0; a < N; ++a) acc[a] = 0.0;
 #pragma unroll
-        for (int z = 1; z >= 0; --z)
+        for (int q = 3; q >= 0; --q) {
+            const int y = q % 2, z = q / 2;
+            if ((z && c != 0) || (y && b != 0)) continue;
+            const bool ok = own && (!z || k > 0) && (!y || j > 0);
+            const double prev = __shfl_up(val[q][P], 1, 64), lower = lane == 0 ? left[q] : prev;
+            acc[0] = ok && i > 0 ? acc[0] + lower : acc[0];        // lower cell first
 #pragma unroll
-            for (int y = 1; y >= 0; --y) {
-                if ((z && c != 0) || (y && b != 0)) continue;      // uniform: no lower copy of this row
-                const bool ok = own && (!z || k > 0) && (!y || j > 0);
-                const int ee = e - (z ? n0 * n1 : 0) - (y ? n0 : 0);
-                const int lyz = N * ((y ? P : b) + N * (z ? P : c));
-                double val[N];
-#pragma unroll
-                for (int a = 0; a < N; ++a) val[a] = 0.0;
-                if (ok) {
-                    const S* src = v + cell_offset(ee, lyz, NN);
-#pragma unroll
-                    for (int a = 0; a < N; ++a) val[a] = P >= 4 ? load_as<double>(src + a * kLanes) : load_stream<double>(src + a * kLanes);
-                }
-                double left = __shfl_up(val[P], 1, 64);
-                if (lane == 0 && ok && i > 0) left = load_as<double>(v + cell_offset(ee - 1, P + lyz, NN));
-                if (ok && i > 0) acc[0] += left;                   // lower cell first
-                if (ok) {
-#pragma unroll
-                    for (int a = 0; a < N; ++a) acc[a] += val[a];
-                }
-            }
+            for (int a = 0; a < N; ++a) acc[a] = ok ? acc[a] + val[q][a] : acc[a];
+        }
         const size_t G0 = (size_t)n0 * P + 1, G1 = (size_t)n1 * P + 1;
         C* out = own ? static_cast<C*>(pe.e) + ((size_t)(i * P) + G0 * ((size_t)(j * P + b) + G1 * (size_t)(k * P + c)))
                      : nullptr;

@@ -341,10 +341,9 @@ __global__ void __launch_bounds__(256) k_dss(ProbEntry pe, int waves) {
     const BlockRow br = block_row<P>(pe, wave);
     const int lane = threadIdx.x % 64, b = br.b, c = br.c;
     const int n0 = pe.n[0], n1 = pe.n[1], n2 = pe.n[2];
-    const int e = br.blk * kLanes + lane;
+    const int e = br.e0 + lane;
     const int i = e % n0, j = (e / n0) % n1, k = e / (n0 * n1);
-    const bool own = e < pe.ncells && (b < P || j == n1 - 1) && (c < P || k == n2 - 1);
-    if (__ballot(own) == 0) return;
+    const bool own = e < br.e1 && (c < P || k == n2 - 1);
     const bool all = b == 0 || c == 0;                       // uniform: every node of the row may be shared
     const bool y2 = own && b == 0 && j > 0, z2 = own && c == 0 && k > 0;
     S* v = static_cast<S*>(pe.c);
