@@ -1393,12 +1393,20 @@ static inline int row_tiles(int rows, bool multi) {
     return (rows + per - 1) / per;
 }
 
+// FP64 vectors from this size on are read past the caches by the assembly: the
+// arrays that the rest of a patch inverse reads again are kept in them instead.
+// Below it the next pass finds r in the cache.  FP64, p = 2, streamed against
+// cached, us: smoother on 40^3 cells (13 MB) 70 and 63, 64^3 (54 MB) 151 and 135, 72^3
+// (77 MB) 235 and 234, 96^3 (182 MB) 508 and 549; apply and patch inverse 30 and
+// 30, 68 and 64, 103 and 101, 213 and 248.
+constexpr size_t kStreamBytes = size_t(96) << 20;
+
 template <int P, typename C> constexpr bool assemble_staged() { return P >= 3 && sizeof(C) == 8; }
 template <int P, typename C> constexpr int assemble_lds() {
     return assemble_staged<P, C>() ? 4 * 64 * (P + 1) * 8 : 16;      // per wavefront: P nodes and an address per lane
 }
 
-template <int P, typename S, typename C, bool MULTI>
+template <int P, typename S, typename C, bool MULTI, bool STREAM>
 __device__ __forceinline__ void assemble_body(const LaunchTable& L, int item, int items, char* smem) {
     constexpr int N = P + 1, NN = N * N * N;
     const int tile = P >= 4 ? xcd_tile(item, items) : item;
@@ -1433,7 +1441,7 @@ __device__ __forceinline__ void assemble_body(const LaunchTable& L, int item, in
             const S* src = v + cell_offset(ee, lyz, NN);
 #pragma unroll
             for (int a = 0; a < N; ++a)
-                val[q][a] = P >= 4 ? load_as<double>(src + a * kLanes) : load_stream<double>(src + a * kLanes);
+                val[q][a] = STREAM ? load_stream<double>(src + a * kLanes) : load_as<double>(src + a * kLanes);
             if (lane == 0 && ok && i > 0) left[q] = load_as<double>(v + cell_offset(ee - 1, P + lyz, NN));
         }
         double acc[N];
@@ -1476,10 +1484,10 @@ __device__ __forceinline__ void assemble_body(const LaunchTable& L, int item, in
     }
 }
 
-template <int P, typename S, typename C, bool MULTI>
+template <int P, typename S, typename C, bool MULTI, bool STREAM>
 __global__ void __launch_bounds__(256) k_assemble(LaunchTable L) {
     __shared__ __align__(16) char smem[assemble_lds<P, C>()];
-    assemble_body<P, S, C, MULTI>(L, blockIdx.x, gridDim.x, smem);
+    assemble_body<P, S, C, MULTI, STREAM>(L, blockIdx.x, gridDim.x, smem);
 }
 
 // Fused sweep from the assembled residual (p <= 3): like k_pi_sweep, but the
@@ -1743,21 +1751,30 @@ __global__ void __launch_bounds__(256) k_pi_sweep_g(LaunchTable L) {
 template <int P, typename S>
 static hipError_t launch_assemble(ProbEntry* ents, int nprob, TableStager* d_tab, hipStream_t s) {
     using C = typename Prec<S>::C;
+    size_t bytes = 0;
+    for (int i = 0; i < nprob; ++i) bytes += ents[i].len * sizeof(S);
+    LaunchTable L{};
     int tiles = 0;
     for (int i = 0; i < nprob; ++i) {
         ents[i].tile_begin = tiles;
         ents[i].ntiles = row_tiles(block_rows(ents[i], P), nprob > 1);
         tiles += ents[i].ntiles;
     }
-    LaunchTable L{};
     L.nprob = nprob;
     L.total_tiles = tiles;
     hipError_t err = stage_table(L, ents, nprob, d_tab, s);
     if (err != hipSuccess || tiles == 0) return err;
     const int grid = (tiles + 7) / 8 * 8;
     TraceSpan ts("pi_assemble", P, Prec<S>::id, s);
-    if (nprob > 1) hipLaunchKernelGGL((k_assemble<P, S, C, true>), dim3(grid), dim3(256), 0, s, L);
-    else hipLaunchKernelGGL((k_assemble<P, S, C, false>), dim3(grid), dim3(256), 0, s, L);
+    if constexpr (P <= 3 && std::is_same_v<S, double>) {
+        if (bytes >= kStreamBytes) {
+            if (nprob > 1) hipLaunchKernelGGL((k_assemble<P, S, C, true, true>), dim3(grid), dim3(256), 0, s, L);
+            else hipLaunchKernelGGL((k_assemble<P, S, C, false, true>), dim3(grid), dim3(256), 0, s, L);
+            return hipGetLastError();
+        }
+    }
+    if (nprob > 1) hipLaunchKernelGGL((k_assemble<P, S, C, true, false>), dim3(grid), dim3(256), 0, s, L);
+    else hipLaunchKernelGGL((k_assemble<P, S, C, false, false>), dim3(grid), dim3(256), 0, s, L);
     return hipGetLastError();
 }
 
@@ -3016,7 +3033,7 @@ struct AssembleBody {
     using Arg = NoArg;
     static constexpr int kLds = assemble_lds<P, typename Prec<S>::C>();
     __device__ static __forceinline__ void run(const LaunchTable& L, const NoArg&, int item, int items, char* smem) {
-        assemble_body<P, S, typename Prec<S>::C, true>(L, item, items, smem);
+        assemble_body<P, S, typename Prec<S>::C, true, false>(L, item, items, smem);
     }
 };
 

@@ -91,3 +91,23 @@ def test_fp64_mass_on_both_sides_of_the_plane_limit(F, n):
     xd = P.pack(to_dev(rng.uniform(-1, 1, m.ncells * m.n1 ** 3)))
     y = to_np(P.unpack(P.mass_apply(xd)))
     check_err(y, operators.mass_cells(m, to_np(P.unpack(xd))), 1e-12, f"mass n={n}")
+
+
+@pytest.mark.parametrize("p", [1, 2, 3])
+def test_streamed_assembly_equals_cached(F, p):
+    """FP64 vectors of 96 MiB and more are read past the caches: the leading
+    layers of such a mesh against those layers alone."""
+    import torch
+    note(f"streamed assembly p={p}")
+    e = 128 if p == 1 else 64
+    per_layer = e * e * (p + 1) ** 3 * 8
+    nz, k = (96 << 20) // per_layer + 2, 6
+    assert per_layer * nz >= 96 << 20 > per_layer * k
+    w = [np.full(e, 1.0 / e)] * 2 + [np.full(nz, 1.0 / e)]
+    big = F.Problem(p, (e, e, nz), w)
+    small = F.Problem(p, (e, e, k), [w[0], w[1], w[2][:k]])
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    r = torch.rand(big.cell_len, generator=g, device="cuda", dtype=torch.float64) - 0.5
+    inner = small.cell_len // k * (k - 2)
+    assert bool((big.patch_inverse(r)[:inner] == small.patch_inverse(r[:small.cell_len].clone())[:inner]).all())
