@@ -118,6 +118,7 @@ struct ProbEntry {
 struct LaunchTable {
     int nprob;
     int total_tiles;
+    int rows;               // node rows per wavefront of the assembly (nprob > 1)
     const ProbEntry* tab;   // device array of nprob entries (nprob > 1)
     ProbEntry one;          // used when nprob == 1
 };

@@ -1384,14 +1384,17 @@ __global__ void __launch_bounds__(256) k_pi_combine_x(LaunchTable L) {
 // At p >= 4 neighbouring blocks run on one XCD (5-8% faster; at p <= 3 5-15%
 // slower).
 // pe: a = r (S), e = global array (C); tiles of four wavefronts.
-// Rows per wavefront: launches over several problems search the entry table
-// once per wavefront, a chain of dependent loads as long as a row's own work
-// (the assembly of a 256-problem batch: 622 us with one row, 589 with four).
-template <bool MULTI> __host__ __device__ constexpr int wave_rows() { return MULTI ? 4 : 1; }
-static inline int row_tiles(int rows, bool multi) {
-    const int per = 4 * (multi ? wave_rows<true>() : wave_rows<false>());
-    return (rows + per - 1) / per;
-}
+// Node rows per wavefront: one, but four in a mixed-degree launch with rows for
+// many times the wavefronts that the chip holds.  There a wavefront's search of
+// the entry table, a chain of dependent loads, costs as much as its row (200
+// problems of p = 2, 3 and 4 to 32 cells an edge in FP32 182 us with one row, 142
+// with four); launches of few rows (16 problems of 4 to 12 cells: 8 us with one,
+// 12 with four) and launches of one degree (43 both; in FP64 32 and 37) gain
+// nothing by it.
+constexpr long kManyRows = 1 << 15;
+template <bool MULTI> __device__ __forceinline__ int wave_rows(const LaunchTable& L) { return MULTI ? L.rows : 1; }
+static inline int row_tiles(int rows, int per_wave) { return (rows + 4 * per_wave - 1) / (4 * per_wave); }
+static inline int node_rows(const ProbEntry& e, int P) { return (e.n[1] * P + 1) * (e.n[2] * P + 1); }
 
 // FP64 vectors from this size on are read past the caches by the assembly: the
 // arrays that the rest of a patch inverse reads again are kept in them instead.
@@ -1415,8 +1418,8 @@ __device__ __forceinline__ void assemble_body(const LaunchTable& L, int item, in
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
     const int lane = threadIdx.x % 64, waves = block_rows(pe, P);
 #pragma unroll 1
-    for (int rr = 0; rr < wave_rows<MULTI>(); ++rr) {
-        const int wave = ((tile - pe.tile_begin) * wave_rows<MULTI>() + rr) * 4 + wv;
+    for (int rr = 0; rr < wave_rows<MULTI>(L); ++rr) {
+        const int wave = ((tile - pe.tile_begin) * wave_rows<MULTI>(L) + rr) * 4 + wv;
         if (wave >= waves) return;
         const int n0 = pe.n[0], n1 = pe.n[1], n2 = pe.n[2];
         const BlockRow br = block_row<P>(pe, wave);
@@ -1754,10 +1757,11 @@ static hipError_t launch_assemble(ProbEntry* ents, int nprob, TableStager* d_tab
     size_t bytes = 0;
     for (int i = 0; i < nprob; ++i) bytes += ents[i].len * sizeof(S);
     LaunchTable L{};
+    L.rows = 1;
     int tiles = 0;
     for (int i = 0; i < nprob; ++i) {
         ents[i].tile_begin = tiles;
-        ents[i].ntiles = row_tiles(block_rows(ents[i], P), nprob > 1);
+        ents[i].ntiles = row_tiles(block_rows(ents[i], P), L.rows);
         tiles += ents[i].ntiles;
     }
     L.nprob = nprob;
@@ -2539,8 +2543,7 @@ __global__ void __launch_bounds__(256) k_pi_solve_l(LaunchTable L) {
 // z once: p = 7 on 24^3 cells 42 us in FP32 (3.2 TB/s; a workgroup per node row
 // 47, per block and node plane 50) and 65 in FP64 (63, 71), on 12^3 cells in
 // FP32 8 (13, 16), p = 4 on 20^3 cells 8 (12, 19).
-// pe: d = patch buffer, c = z (S), alpha = damping; tiles of wave_rows per
-// wavefront.
+// pe: d = patch buffer, c = z (S), alpha = damping; tiles of four rows.
 template <int P, typename C> constexpr int wr_lds() { return 4 * (kNrCells * P + 1) * (int)sizeof(C); }
 
 template <int P, typename S, int ACC, bool MULTI>
@@ -2560,98 +2563,95 @@ __device__ __forceinline__ void pi_combine_wr_body(const LaunchTable& L, int ite
     const C* pbuf = static_cast<const C*>(pe.d);
     S* z = static_cast<S*>(pe.c);
     const C alpha = (C)pe.alpha;
-#pragma unroll 1
-    for (int rr = 0; rr < wave_rows<MULTI>(); ++rr) {
-        const int row = ((tile - pe.tile_begin) * wave_rows<MULTI>() + rr) * 4 + wv;
-        if (row >= rows) return;                     // per wavefront: no workgroup barrier follows
-        // the padding cells of the last storage block, one node per row
-        for (int l = row; l < NN; l += rows) {
-            const int e = (pe.nblk - 1) * kLanes + lane;
-            if (e >= pe.ncells) store_from(z + cell_offset(e, l, NN), (C)0);
+    const int row = (tile - pe.tile_begin) * 4 + wv;
+    if (row >= rows) return;                     // per wavefront: no workgroup barrier follows
+    // the padding cells of the last storage block, one node per row
+    for (int l = row; l < NN; l += rows) {
+        const int e = (pe.nblk - 1) * kLanes + lane;
+        if (e >= pe.ncells) store_from(z + cell_offset(e, l, NN), (C)0);
+    }
+    const int Y = row % G1, Z = row / G1;
+    // patch rows containing the node row along y and z (ascending vertex, with
+    // the patch-local index), and the row's cell copies
+    int vyp[2], qyp[2], nyp = 0, vzp[2], qzp[2], nzp = 0;
+    int cyc[2], byc[2], nyc = 0, czc[2], bzc[2], nzc = 0;
+    {
+        const int qy = Y / P, ry = Y - qy * P;
+        if (ry == 0) {
+            if (qy >= 1 && qy <= npy) { vyp[nyp] = qy; qyp[nyp] = P - 1; ++nyp; }
+            if (qy >= 1) { cyc[nyc] = qy - 1; byc[nyc] = P; ++nyc; }
+            if (qy <= n1 - 1) { cyc[nyc] = qy; byc[nyc] = 0; ++nyc; }
+        } else {
+            if (qy >= 1) { vyp[nyp] = qy; qyp[nyp] = ry + P - 1; ++nyp; }
+            if (qy + 1 <= npy) { vyp[nyp] = qy + 1; qyp[nyp] = ry - 1; ++nyp; }
+            cyc[nyc] = qy; byc[nyc] = ry; ++nyc;
         }
-        const int Y = row % G1, Z = row / G1;
-        // patch rows containing the node row along y and z (ascending vertex, with
-        // the patch-local index), and the row's cell copies
-        int vyp[2], qyp[2], nyp = 0, vzp[2], qzp[2], nzp = 0;
-        int cyc[2], byc[2], nyc = 0, czc[2], bzc[2], nzc = 0;
-        {
-            const int qy = Y / P, ry = Y - qy * P;
-            if (ry == 0) {
-                if (qy >= 1 && qy <= npy) { vyp[nyp] = qy; qyp[nyp] = P - 1; ++nyp; }
-                if (qy >= 1) { cyc[nyc] = qy - 1; byc[nyc] = P; ++nyc; }
-                if (qy <= n1 - 1) { cyc[nyc] = qy; byc[nyc] = 0; ++nyc; }
-            } else {
-                if (qy >= 1) { vyp[nyp] = qy; qyp[nyp] = ry + P - 1; ++nyp; }
-                if (qy + 1 <= npy) { vyp[nyp] = qy + 1; qyp[nyp] = ry - 1; ++nyp; }
-                cyc[nyc] = qy; byc[nyc] = ry; ++nyc;
-            }
-            const int qz = Z / P, rz = Z - qz * P;
-            if (rz == 0) {
-                if (qz >= 1 && qz <= n2 - 1) { vzp[nzp] = qz; qzp[nzp] = P - 1; ++nzp; }
-                if (qz >= 1) { czc[nzc] = qz - 1; bzc[nzc] = P; ++nzc; }
-                if (qz <= n2 - 1) { czc[nzc] = qz; bzc[nzc] = 0; ++nzc; }
-            } else {
-                if (qz >= 1) { vzp[nzp] = qz; qzp[nzp] = rz + P - 1; ++nzp; }
-                if (qz + 1 <= n2 - 1) { vzp[nzp] = qz + 1; qzp[nzp] = rz - 1; ++nzp; }
-                czc[nzc] = qz; bzc[nzc] = rz; ++nzc;
-            }
+        const int qz = Z / P, rz = Z - qz * P;
+        if (rz == 0) {
+            if (qz >= 1 && qz <= n2 - 1) { vzp[nzp] = qz; qzp[nzp] = P - 1; ++nzp; }
+            if (qz >= 1) { czc[nzc] = qz - 1; bzc[nzc] = P; ++nzc; }
+            if (qz <= n2 - 1) { czc[nzc] = qz; bzc[nzc] = 0; ++nzc; }
+        } else {
+            if (qz >= 1) { vzp[nzp] = qz; qzp[nzp] = rz + P - 1; ++nzp; }
+            if (qz + 1 <= n2 - 1) { vzp[nzp] = qz + 1; qzp[nzp] = rz - 1; ++nzp; }
+            czc[nzc] = qz; bzc[nzc] = rz; ++nzc;
         }
-        const C* line[2][2];                         // the row's line of the first x-patch of each (z, y) pair
+    }
+    const C* line[2][2];                         // the row's line of the first x-patch of each (z, y) pair
 #pragma unroll
-        for (int tz = 0; tz < 2; ++tz)
+    for (int tz = 0; tz < 2; ++tz)
 #pragma unroll
-            for (int ty = 0; ty < 2; ++ty) {
-                const bool ok = tz < nzp && ty < nyp && npx > 0;
-                line[tz][ty] = pbuf + (ok ? (size_t)npx * ((vyp[ty] - 1) + npy * (vzp[tz] - 1)) * nP3 + nP * qyp[ty] +
-                                                nP2 * qzp[tz]
-                                          : 0);
-            }
-        for (int i0 = 0; i0 < n0; i0 += CC) {
-            const int nc = min(CC, n0 - i0);
-            for (int k = lane; k <= nc * P; k += 64) {
-                const int X = i0 * P + k;
-                // the x-patches holding X: the one of the vertex at or below it and
-                // the one of the vertex above
-                const int qx = X / P, rx = X - qx * P;
-                const bool lo_in = qx >= 1 && qx <= npx, hi_in = rx > 0 && qx + 1 <= npx;
-                const uint32_t lo = lo_in ? (uint32_t)((qx - 1) * nP3 + rx + P - 1) : 0u;
-                const uint32_t hi = hi_in ? (uint32_t)(qx * nP3 + rx - 1) : 0u;
-                // every term is loaded (a missing one from the line's first value)
-                // and dropped by a select, so the loads are in flight together
-                C sum = 0;
+        for (int ty = 0; ty < 2; ++ty) {
+            const bool ok = tz < nzp && ty < nyp && npx > 0;
+            line[tz][ty] = pbuf + (ok ? (size_t)npx * ((vyp[ty] - 1) + npy * (vzp[tz] - 1)) * nP3 + nP * qyp[ty] +
+                                            nP2 * qzp[tz]
+                                      : 0);
+        }
+    for (int i0 = 0; i0 < n0; i0 += CC) {
+        const int nc = min(CC, n0 - i0);
+        for (int k = lane; k <= nc * P; k += 64) {
+            const int X = i0 * P + k;
+            // the x-patches holding X: the one of the vertex at or below it and
+            // the one of the vertex above
+            const int qx = X / P, rx = X - qx * P;
+            const bool lo_in = qx >= 1 && qx <= npx, hi_in = rx > 0 && qx + 1 <= npx;
+            const uint32_t lo = lo_in ? (uint32_t)((qx - 1) * nP3 + rx + P - 1) : 0u;
+            const uint32_t hi = hi_in ? (uint32_t)(qx * nP3 + rx - 1) : 0u;
+            // every term is loaded (a missing one from the line's first value)
+            // and dropped by a select, so the loads are in flight together
+            C sum = 0;
 #pragma unroll
-                for (int tz = 0; tz < 2; ++tz)
+            for (int tz = 0; tz < 2; ++tz)
 #pragma unroll
-                    for (int ty = 0; ty < 2; ++ty) {
-                        if (tz >= nzp || ty >= nyp) continue;                  // uniform
-                        const C vl = line[tz][ty][lo], vh = line[tz][ty][hi];
-                        C xs = lo_in ? vl : (C)0;
-                        xs = hi_in ? xs + vh : xs;
-                        sum += xs;
-                    }
-                sx[k] = sum;
-            }
-            wave_sync();
-            // lanes on (a, cell) with the cells padded to a power of two
-            const int sh = nc <= 8 ? 3 : nc <= 16 ? 4 : 5;
-            for (int w = lane; w < (N << sh); w += 64) {
-                const int a = w >> sh, c = w & ((1 << sh) - 1);
-                if (c >= nc) continue;
-                const C v = alpha * sx[c * P + a];
+                for (int ty = 0; ty < 2; ++ty) {
+                    if (tz >= nzp || ty >= nyp) continue;                  // uniform
+                    const C vl = line[tz][ty][lo], vh = line[tz][ty][hi];
+                    C xs = lo_in ? vl : (C)0;
+                    xs = hi_in ? xs + vh : xs;
+                    sum += xs;
+                }
+            sx[k] = sum;
+        }
+        wave_sync();
+        // lanes on (a, cell) with the cells padded to a power of two
+        const int sh = nc <= 8 ? 3 : nc <= 16 ? 4 : 5;
+        for (int w = lane; w < (N << sh); w += 64) {
+            const int a = w >> sh, c = w & ((1 << sh) - 1);
+            if (c >= nc) continue;
+            const C v = alpha * sx[c * P + a];
 #pragma unroll
-                for (int cz = 0; cz < 2; ++cz) {
-                    if (cz >= nzc) break;
+            for (int cz = 0; cz < 2; ++cz) {
+                if (cz >= nzc) break;
 #pragma unroll
-                    for (int cy = 0; cy < 2; ++cy) {
-                        if (cy >= nyc) break;
-                        const int e = i0 + c + n0 * (cyc[cy] + n1 * czc[cz]);
-                        S* d = z + cell_offset(e, a + N * (byc[cy] + N * bzc[cz]), NN);
-                        store_from(d, ACC ? load_as<C>(d) + v : v);
-                    }
+                for (int cy = 0; cy < 2; ++cy) {
+                    if (cy >= nyc) break;
+                    const int e = i0 + c + n0 * (cyc[cy] + n1 * czc[cz]);
+                    S* d = z + cell_offset(e, a + N * (byc[cy] + N * bzc[cz]), NN);
+                    store_from(d, ACC ? load_as<C>(d) + v : v);
                 }
             }
-            wave_sync();
         }
+        wave_sync();
     }
 }
 
@@ -2713,9 +2713,9 @@ static hipError_t launch_pi_lines(int accumulate, ProbEntry* ents, int nprob, Ta
     }
     int tiles2 = 0;
     for (int i = 0; i < nprob; ++i) {
-        const int rows = (ents[i].n[1] * P + 1) * (ents[i].n[2] * P + 1);
+        const int rows = node_rows(ents[i], P);
         ents[i].tile_begin = tiles2;
-        ents[i].ntiles = cpc == 0 ? row_tiles(rows, nprob > 1) : cpc == 2 ? rows : ents[i].nblk * (P + 1);
+        ents[i].ntiles = cpc == 0 ? row_tiles(rows, 1) : cpc == 2 ? rows : ents[i].nblk * (P + 1);
         tiles2 += ents[i].ntiles;
     }
     LaunchTable L2{};
@@ -3081,7 +3081,7 @@ template <int P, typename S> static int pi_solve_items(int t) {
 }
 template <int P, typename S> static int pi_combine_tiles(const ProbEntry& e) {
     if constexpr (mixed_combine_pm<P, typename Prec<S>::C>()) return e.nblk * (P + 1);
-    else if constexpr (P >= 4) return row_tiles((e.n[1] * P + 1) * (e.n[2] * P + 1), true);
+    else if constexpr (P >= 4) return row_tiles(node_rows(e, P), 1);
     else if constexpr (pi_xcomb_default<P, S>()) return ((e.n[1] * P + 1) * (e.n[2] * P + 1) + 3) / 4;
     else return e.nblk * (P + 1) * ((P + 1 + combine_brows<P>() - 1) / combine_brows<P>());
 }
@@ -3096,9 +3096,13 @@ static hipError_t launch_pi_mixed_t(ProbEntry* ents, int nprob, TableStager* st,
     MixTable T{};
     int grid = 0;
     // 1. assembly into each problem's global-node array
-    auto rows4 = [](int p, const ProbEntry& e) { return row_tiles(block_rows(e, p), true); };
+    long rows = 0;
+    for (int i = 0; i < nprob; ++i) rows += block_rows(ents[i], ents[i].p);
+    const int per = rows >= kManyRows ? 4 : 1;
+    auto atiles = [per](int p, const ProbEntry& e) { return row_tiles(block_rows(e, p), per); };
     auto same = [](int, int t) { return t; };
-    hipError_t err = mix_build(ents, nprob, st, s, rows4, same, T, grid);
+    hipError_t err = mix_build(ents, nprob, st, s, atiles, same, T, grid);
+    for (MixSeg& g : T.seg) g.L.rows = per;
     if (err != hipSuccess) return err;
     if (grid > 0) {
         TraceSpan ts("pi_assemble", 0, Prec<S>::id, s);
