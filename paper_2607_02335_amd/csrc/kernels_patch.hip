@@ -2660,8 +2660,13 @@ __device__ __forceinline__ void pi_combine_wr_body(const LaunchTable& L, int ite
 // the Infinity Cache take k_pi_combine_pm, which stores whole runs of 64 cells
 // (a 256-problem batch, 1.4 GB of output: 2.3 ms against 2.5; one problem of
 // 32^3 cells at p = 7, 67 MB: 109 us against 91), and so does the mixed launch,
-// which serves batches.  8-byte stores cover a line with 16 cells.
-constexpr size_t kRowCombineBytes = size_t(128) << 20;
+// which serves batches.  8-byte stores cover a line with 16 cells; there the limit
+// is the buffer, three to four times the output: once it exceeds the cache,
+// k_pi_combine_nr, whose workgroups ask for a row's runs at once, reads it faster
+// (patch inverse at p = 5 on 40^3 cells, 111 MB of output: 337 us with
+// k_pi_combine_wr, 325 with it; p = 6 28^3, 60 MB: 182 and 175; 24^3, 38 MB: 101
+// and 109; p = 7 24^3, 57 MB: 206 and 205, 36^3 712 and 689; p = 4 64^3 607 and 612).
+template <typename C> constexpr size_t kRowCombineBytes() { return size_t(sizeof(C) == 4 ? 128 : 56) << 20; }
 template <int P, typename C> constexpr bool mixed_combine_pm() { return P >= 4 && sizeof(C) == 4; }
 
 template <int P, typename S, int ACC, bool MULTI>
@@ -2703,13 +2708,14 @@ static hipError_t launch_pi_lines(int accumulate, ProbEntry* ents, int nprob, Ta
         err = hipGetLastError();
         if (err != hipSuccess) return err;
     }
-    // 3. combine into the cells: a wavefront per node row, with the switch a
-    //    workgroup per node row (2) or per (storage block, node plane) (1)
+    // 3. combine into the cells: a wavefront per node row; for large outputs and
+    //    with the switch a workgroup per node row (2) or per (storage block, node
+    //    plane) (1)
     int cpc = g_combine_per_cell.load(std::memory_order_relaxed);
-    if (cpc == 0 && sizeof(C) == 4) {
+    if (cpc == 0) {
         size_t bytes = 0;
         for (int i = 0; i < nprob; ++i) bytes += ents[i].len * sizeof(S);
-        if (bytes > kRowCombineBytes) cpc = 1;
+        if (bytes > kRowCombineBytes<C>()) cpc = sizeof(C) == 4 ? 1 : 2;
     }
     int tiles2 = 0;
     for (int i = 0; i < nprob; ++i) {

@@ -111,3 +111,20 @@ def test_streamed_assembly_equals_cached(F, p):
     r = torch.rand(big.cell_len, generator=g, device="cuda", dtype=torch.float64) - 0.5
     inner = small.cell_len // k * (k - 2)
     assert bool((big.patch_inverse(r)[:inner] == small.patch_inverse(r[:small.cell_len].clone())[:inner]).all())
+
+
+@pytest.mark.parametrize("p,n", [(5, (34, 33, 34)), (7, (25, 24, 24))])
+def test_large_fp64_combine_equals_the_others(F, p, n):
+    note(f"large combine p={p} n={n}")
+    import torch
+    P = F.Problem(p, n)
+    assert P.cell_len * 8 > 56 << 20
+    g = torch.Generator(device="cuda")
+    g.manual_seed(8)
+    r = torch.rand(P.cell_len, generator=g, device="cuda", dtype=torch.float64) - 0.5
+    z = P.patch_inverse(r)
+    F.set_option(F.OPT_COMBINE_PER_CELL, 1)
+    try:
+        assert bool((P.patch_inverse(r) == z).all())
+    finally:
+        F.set_option(F.OPT_COMBINE_PER_CELL, 0)
