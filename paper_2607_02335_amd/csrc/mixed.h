@@ -42,6 +42,13 @@ struct NoArg {};
 
 constexpr int lds_max(int a, int b) { return a > b ? a : b; }
 
+// The body of a segment that is empty in every launch of its kernel.
+struct NoBody {
+    using Arg = NoArg;
+    static constexpr int kLds = 0;
+    __device__ static __forceinline__ void run(const LaunchTable&, const NoArg&, int, int, char*) {}
+};
+
 // A body B provides: Arg (its by-value kernel argument), kLds (bytes of
 // LDS), and run(L, arg, item, items, smem) doing what workgroup `item` of a
 // grid of `items` workgroups of its own kernel does.

@@ -128,3 +128,23 @@ def test_large_fp64_combine_equals_the_others(F, p, n):
         assert bool((P.patch_inverse(r) == z).all())
     finally:
         F.set_option(F.OPT_COMBINE_PER_CELL, 0)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("degrees", [(2, 3), (7, 3, 2)])
+def test_many_rows_batch_equals_single(F, degrees, prec):
+    """Above the number of node rows from which a mixed-degree assembly gives a
+    wavefront four of them, and without degree 7 the solves without its body."""
+    note(f"many rows {degrees} prec={prec}")
+    shapes = [(17, 16, 15), (14, 15, 16), (3, 3, 65)] if 7 in degrees else [(29, 28, 31), (30, 33, 27), (3, 130, 5)]
+    specs = [(degrees[i % len(degrees)], shapes[i % 3]) for i in range(24)]
+    specs += [(degrees[(i + 1) % len(degrees)], shapes[i % 3]) for i in range(12)]
+    assert sum(p * p * (a * b * c // 64) for p, (a, b, c) in specs) > 32768
+    B = F.Batch([(p, n, None) for p, n in specs])
+    rng = np.random.default_rng(14)
+    rs = [Q.gather(to_dev(rng.uniform(-1, 1, Q.global_len)), prec) for Q in B.problems]
+    zs = [Q.cell_vector(prec) for Q in B.problems]
+    B.patch_inverse(rs, zs)
+    for Q, r, z in zip(B.problems, rs, zs):
+        assert bool((Q.patch_inverse(r) == z).all())
+    B.close()
