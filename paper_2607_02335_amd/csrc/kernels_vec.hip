@@ -115,8 +115,7 @@ __device__ __forceinline__ void anorm_body(const LaunchTable& L, int group, int 
         size_t lo, hi;
         red_range(pe, t, lo, hi);
         const S* v = static_cast<const S*>(pe.a);
-        NodeAt at;
-        at.n0 = pe.n[0], at.n1 = pe.n[1], at.n2 = pe.n[2];
+        const int n0 = pe.n[0], n1 = pe.n[1], n2 = pe.n[2];
         double acc = 0.0;
         // walk the range block by block: a thread keeps its cell (lane) within a block
         for (size_t base = lo - lo % ((size_t)NN * kLanes); base < hi; base += (size_t)NN * kLanes) {
@@ -125,13 +124,21 @@ __device__ __forceinline__ void anorm_body(const LaunchTable& L, int group, int 
             if (e >= pe.ncells) continue;
             const int lb = base < lo ? (int)((lo - base) / kLanes) : 0;
             const int le = base + (size_t)NN * kLanes > hi ? (int)((hi - base) / kLanes) : NN;
-            at.i = e % at.n0, at.j = (e / at.n0) % at.n1, at.k = e / (at.n0 * at.n1);
+            const int i = e % n0, j = (e / n0) % n1, k = e / (n0 * n1);
             for (int l = lb + lq; l < le; l += 4) {
-                at.a = l % N, at.b = (l / N) % N, at.c = l / N2;
-                if ((at.a == P && at.i < at.n0 - 1) || (at.b == P && at.j < at.n1 - 1) ||
-                    (at.c == P && at.k < at.n2 - 1)) continue;
+                const int a = l % N, b = (l / N) % N, c = l / N2;
+                if ((a == P && i < n0 - 1) || (b == P && j < n1 - 1) || (c == P && k < n2 - 1)) continue;
+                const int cx = (a == 0 && i > 0) ? 2 : 1;
+                const int cy = (b == 0 && j > 0) ? 2 : 1;
+                const int cz = (c == 0 && k > 0) ? 2 : 1;
                 double s = 0.0;
-                node_copies<P>(at, [&](int ee, int ll, int, int, int) { s += load_as<double>(v + cell_offset(ee, ll, NN)); });
+                for (int sz = 0; sz < cz; ++sz)
+                    for (int sy = 0; sy < cy; ++sy)
+                        for (int sx = 0; sx < cx; ++sx) {
+                            const int ee = (i - sx) + n0 * ((j - sy) + n1 * (k - sz));
+                            const int ll = (sx ? P : a) + N * ((sy ? P : b) + N * (sz ? P : c));
+                            s += load_as<double>(v + cell_offset(ee, ll, NN));
+                        }
                 acc += s * s;
             }
         }
