@@ -231,13 +231,24 @@ __device__ __forceinline__ void distribute_body(const LaunchTable& L, int group,
                 continue;
             }
             at.i = e % at.n0, at.j = (e / at.n0) % at.n1, at.k = e / (at.n0 * at.n1);
+            // the widths of the cell and its neighbours, once per block
+            double h[3][3];
+            if constexpr (MODE == kDistJacobi) {
+                const int at3[3] = {at.i, at.j, at.k};
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const double* w = pe.h[q] + at3[q];
+                    h[q][0] = w[at3[q] > 0 ? -1 : 0], h[q][1] = w[0], h[q][2] = w[at3[q] + 1 < pe.n[q] ? 1 : 0];
+                }
+            }
             for (int l = lb + lq; l < le; l += 4) {
                 at.a = l % N, at.b = (l / N) % N, at.c = l / N2;
                 double s = 0.0, d = 0.0;
                 const int copies = node_copies<P>(at, [&](int ee, int ll, int ci, int cj, int ck) {
                     s += v[cell_offset(ee, ll, NN)];
-                    if (MODE == kDistJacobi) {
-                        const double hx = pe.h[0][ci], hy = pe.h[1][cj], hz = pe.h[2][ck];
+                    if constexpr (MODE == kDistJacobi) {
+                        auto width = [](const double* w, int d) { return d < 0 ? w[0] : d > 0 ? w[2] : w[1]; };
+                        const double hx = width(h[0], ci - at.i), hy = width(h[1], cj - at.j), hz = width(h[2], ck - at.k);
                         const int ax = ll % N, by = (ll / N) % N, cz = ll / N2;
                         d += (hy * hz / hx) * dg.k[ax] * dg.m[by] * dg.m[cz] +
                              (hx * hz / hy) * dg.m[ax] * dg.k[by] * dg.m[cz] +
