@@ -148,3 +148,34 @@ def test_many_rows_batch_equals_single(F, degrees, prec):
     for Q, r, z in zip(B.problems, rs, zs):
         assert bool((Q.patch_inverse(r) == z).all())
     B.close()
+
+
+@pytest.mark.parametrize("pc,per_precond", [(0, 2), (3, 2)])
+def test_solve_stops_without_a_spare_patch_inverse(F, pc, per_precond):
+    """The last allowed iteration queues no preconditioner ahead of reading its
+    residual: one preconditioner for p_0, one per iteration but the last."""
+    note(f"solve launches pc={pc}")
+    m, w, rng = graded(3, (6, 5, 4), 77)
+    P = F.Problem(3, m.n, w)
+    b = P.mass_apply(P.gather(to_dev(rng.uniform(-1, 1, m.nglob))))
+    for maxit in (1, 2, 3):
+        def solve():
+            _, info = P.pcg_solve(b, rtol=1e-14, maxit=maxit, precond=pc, sweeps=2 if pc == 0 else 1,
+                                  omega=0.125 if pc == 0 else 0.2, raise_on_error=False)
+            assert info["iters"] == maxit
+        assert _launches(F, "pi_solve", solve) == maxit * per_precond
+
+
+@pytest.mark.parametrize("sp", [0, 1])
+def test_head_start_changes_no_iterate(F, sp):
+    """A solve to the tolerance and the same solve cut at each iteration end
+    at the same residuals (whichever iterations queue work ahead)."""
+    note(f"solve iterates sp={sp}")
+    m, w, rng = graded(3, (6, 5, 4), 78)
+    P = F.Problem(3, m.n, w)
+    b = P.mass_apply(P.gather(to_dev(rng.uniform(-1, 1, m.nglob))))
+    u, info = P.pcg_solve(b, rtol=1e-8, maxit=200, smoother_prec=sp)
+    k = info["iters"]
+    v, cut = P.pcg_solve(b, rtol=1e-30, maxit=k, smoother_prec=sp, raise_on_error=False)
+    assert cut["iters"] == k and cut["relres"] == info["relres"]
+    assert bool((u == v).all())
