@@ -144,7 +144,7 @@ __device__ __forceinline__ double vertex_sum(const ProbEntry& pe, int vi, int vj
 }
 
 // The coarse solve in three launches where a z-plane of coarse values and the
-// bases fit in 64 KB of LDS (coarse_planes_fit): x and y forward per z-plane
+// bases fit in 64 KB of LDS (kPlaneLds): x and y forward per z-plane
 // (reading the corner sums), z forward, scaling and z backward per 32
 // columns, y and x backward per z-plane.  The work is a few MFLOP, so the
 // time is launches and dependent loads: the nine launches of the pass solve
@@ -157,14 +157,12 @@ constexpr int kPlaneLds = 8192;                     // doubles
 constexpr int kPlaneThreads = 512;
 constexpr int kColumns = 32;
 
-static int plane_lds(const ProbEntry& e) {
-    const int m0 = e.n[0] - 1, m1 = e.n[1] - 1, mx = m0 > m1 ? m0 : m1;
-    return 2 * m0 * m1 + mx * mx;
-}
-static int column_lds(const ProbEntry& e) {
-    const int m2 = e.n[2] - 1;
-    return m2 * m2 + 2 * m2 * kColumns;
-}
+// Doubles of LDS for meshes of m0 x m1 x m2 interior vertices (long: the squares
+// of long edges exceed an int).
+static constexpr long plane_lds(long m0, long m1) { return 2 * m0 * m1 + (m0 > m1 ? m0 * m0 : m1 * m1); }
+static constexpr long column_lds(long m2) { return m2 * m2 + 2 * m2 * kColumns; }
+static_assert(plane_lds(50000, 2) > kPlaneLds && plane_lds(30000, 30000) > kPlaneLds && column_lds(50000) > kPlaneLds,
+              "long edges must not pass for short ones");
 
 // out(o, r) = sum_i A(i, o) x(i, r) over a plane in LDS, i ascending; the
 // value (i, r) sits at i si + r sr, A row-major [m][m].
@@ -408,7 +406,7 @@ static hipError_t coarse_table(LaunchTable& L, ProbEntry* ents, int nprob, Table
 // coarse values for the passes.
 struct CoarseSolve {
     bool planes = true;
-    int lds_plane = 0, lds_column = 0;
+    long lds_plane = 0, lds_column = 0;
     LaunchTable Lp{}, Lc{}, Lv{};
     bool empty() const { return planes ? Lp.total_tiles == 0 : Lv.total_tiles == 0; }
 };
@@ -416,8 +414,8 @@ struct CoarseSolve {
 static hipError_t coarse_solve_tables(CoarseSolve& cs, ProbEntry* ents, int nprob, TableStager* st, hipStream_t s) {
     for (int i = 0; i < nprob; ++i) {
         if (!has_coarse(ents[i])) continue;
-        cs.lds_plane = std::max(cs.lds_plane, plane_lds(ents[i]));
-        cs.lds_column = std::max(cs.lds_column, column_lds(ents[i]));
+        cs.lds_plane = std::max(cs.lds_plane, plane_lds(ents[i].n[0] - 1, ents[i].n[1] - 1));
+        cs.lds_column = std::max(cs.lds_column, column_lds(ents[i].n[2] - 1));
     }
     cs.planes = cs.lds_plane <= kPlaneLds && cs.lds_column <= kPlaneLds;
     if (!cs.planes)
@@ -435,7 +433,7 @@ static hipError_t coarse_solve_tables(CoarseSolve& cs, ProbEntry* ents, int npro
 template <bool MULTI>
 static void launch_coarse_solve(const CoarseSolve& cs, hipStream_t s) {
     if (cs.planes) {
-        const int lp = cs.lds_plane * (int)sizeof(double), lc = cs.lds_column * (int)sizeof(double);
+        const int lp = (int)(cs.lds_plane * sizeof(double)), lc = (int)(cs.lds_column * sizeof(double));
         hipLaunchKernelGGL(k_coarse_plane<MULTI>, dim3(cs.Lp.total_tiles), dim3(kPlaneThreads), lp, s, cs.Lp, 1);
         hipLaunchKernelGGL(k_coarse_columns<MULTI>, dim3(cs.Lc.total_tiles), dim3(256), lc, s, cs.Lc);
         hipLaunchKernelGGL(k_coarse_plane<MULTI>, dim3(cs.Lp.total_tiles), dim3(kPlaneThreads), lp, s, cs.Lp, 0);
