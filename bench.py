@@ -143,7 +143,7 @@ def measure_workload(fem, torch, p, n, seed, steps, warmup, prec=0):
 
 # Launch-trace label -> the operation of the hot path it belongs to.
 OP_OF = {"apply": "apply", "mass": "mass", "pi_assemble": "patch_inverse", "pi_solve": "patch_inverse",
-         "pi_combine": "patch_inverse", "pi_sweep": "patch_inverse", "dss": "dss", "dss_axis": "dss"}
+         "pi_combine": "patch_inverse", "pi_sweep": "patch_inverse", "dss": "dss_once", "dss_axis": "dss"}
 
 
 def op_bytes(op, p, n, esize=8):
@@ -151,14 +151,19 @@ def op_bytes(op, p, n, esize=8):
     figure of the measurement model times the units.  The apply, the mass
     apply and the patch inverse read one cell-wise vector and write one
     (2 x esize bytes per cell DoF; geometry and eigen-data are O(n) and not
-    counted); the structured DSS reads and writes both coincident copies of
-    every face pair of every axis pass (4 x esize per pair; the library's one
-    pass moves a copy once for all axes, so its fraction can pass 1)."""
+    counted).  dss: the structured DSS as three axis passes, each reading and
+    writing both coincident copies of every face pair (4 x esize per pair);
+    dss_once: the library's one pass, every copy that shares its node with
+    another read and written once."""
     cell = cell_dofs(p, n) * esize
     if op in ("apply", "mass", "patch_inverse"):
         return 2 * cell
     if op == "dss":
         return 4 * esize * (p + 1) ** 2 * 3 * (n - 1) * n * n
+    if op == "dss_once":
+        # all copies but those alone at their node: per direction the inner
+        # nodes of every cell and the two ends of the mesh
+        return 2 * esize * ((n * (p + 1)) ** 3 - (n * (p - 1) + 2) ** 3)
     return None
 
 
@@ -337,7 +342,7 @@ def copy_peak(torch, nbytes=1 << 30, reps=10):
 def paper_kernels(fem, torch, reps=10, n_dss=128, degrees=(2, 3, 7)):
     """The paper's own measured kernels on uniform unit-cube meshes, FP64:
     the mass operator (one volumetric apply, Table "mass operator"), the
-    structured DSS in place (three axis passes, Table "DSS throughput") and
+    structured DSS in place (Table "DSS throughput") and
     the entire assembled mass operator (volumetric apply + DSS, Table
     "entire mass operator", 128^3 cells).  Rates in unique DoFs per second,
     bytes by the algorithmic model; cold (two rotating buffer pairs)."""
@@ -360,7 +365,7 @@ def paper_kernels(fem, torch, reps=10, n_dss=128, degrees=(2, 3, 7)):
             P.dss(pairs[i % 2][1], pairs[i % 2][1])
         t_op = tm.time(both, reps)
         u, c = unique_dofs(p, n), cell_dofs(p, n)
-        bm, bd = op_bytes("mass", p, n), op_bytes("dss", p, n)
+        bm, bd = op_bytes("mass", p, n), op_bytes("dss_once", p, n)
         out[f"q{p}_{n}"] = dict(
             p=p, n=n, unique_dofs=u, cell_dofs=c,
             mass=dict(s=t_vol, unique_gdofs=u / t_vol / 1e9, cell_gdofs=c / t_vol / 1e9,
