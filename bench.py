@@ -14,7 +14,7 @@ Inputs live in HBM before timing starts; the timed region rotates through
 several independent (x, y, z) buffer sets larger than the 256 MB Infinity
 Cache so repeated steps do not run out of cache.
 
-Usage: python bench.py [--gpus 1] [--steps 20] [--warmup 5] [--quick]
+Usage: python bench.py [--gpus 1] [--steps 20] [--warmup 5] [--quick] [--detail FILE]
        python bench.py --mode calib        (plain 1 GiB copy, for counters)
        python bench.py --mode serve        (continuous-batching stream)
 """
@@ -527,6 +527,43 @@ def cpu_baseline(steps_budget_s=20.0):
                 host_cpus=os.cpu_count())
 
 
+def summary(extra):
+    """The main figures of the secondary records, short enough that the whole
+    result line stays a few thousand characters (whoever keeps only the end of
+    the output still has all of it; --detail writes the records in full)."""
+    out = {}
+    for k in ("q3_64", "q2_96", "q7_24"):
+        if k in extra:
+            r = extra[k]
+            out[k] = {"ms_per_step": r["s_per_step"] * 1e3, "apply_us": r["apply_s"] * 1e6, "pi_us": r["pi_s"] * 1e6,
+                      "kernels_us": {q["label"]: q["avg_us"] for q in r["kernels"]}}
+    if "q7_solve" in extra:
+        out["q7_solve_iters_p50_ms"] = {k: [r["iters"], r["p50_s"] * 1e3] for k, r in extra["q7_solve"].items()}
+    if "batch_256" in extra:
+        r = extra["batch_256"]
+        out["batch_256"] = {"ms_mixed": r["s_per_pass_mixed"] * 1e3, "ms_per_degree": r["s_per_pass_per_degree"] * 1e3,
+                            "launches": r["launches"], "unique_gdofs": r["unique_gdofs"]}
+    if "paper_kernels" in extra:
+        out["mass_dss_assembled_unique_gdofs"] = {
+            k: [r[q]["unique_gdofs"] for q in ("mass", "dss", "assembled_mass")] for k, r in extra["paper_kernels"].items()}
+    if "layout_sweep" in extra:
+        out["layout_mass_dss_unique_gdofs"] = {
+            k: {str(r["B"]): [r["mass_unique_gdofs"], r["dss_unique_gdofs"]] for r in rows}
+            for k, rows in extra["layout_sweep"].items()}
+    if "serve" in extra:
+        out["serve"] = {k: extra["serve"][k] for k in ("requests", "wall_s", "failures", "p50_latency_s", "p99_latency_s",
+                                                       "mean_iters", "solved_unique_dofs_per_s", "steps",
+                                                       "hbm_high_water_bytes")}
+
+    def short(v):
+        if isinstance(v, dict):
+            return {k: short(x) for k, x in v.items()}
+        if isinstance(v, list):
+            return [short(x) for x in v]
+        return float(f"{v:.4g}") if isinstance(v, float) else v
+    return short(out)
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -537,6 +574,7 @@ def main():
     ap.add_argument("--only", choices=["q2_96", "q7_24", "q7_solve", "batch_256", "paper_kernels", "layout"], default=None,
                     help="run one secondary workload alone (for profiling) and print its record")
     ap.add_argument("--no-cpu", action="store_true")
+    ap.add_argument("--detail", metavar="FILE", help="write the result with every secondary record in full")
     ap.add_argument("--solve-reps", type=int, default=5)
     ap.add_argument("--requests", type=int, default=10000, help="serving mode: stream length")
     ap.add_argument("--serve-requests", type=int, default=10000,
@@ -626,8 +664,11 @@ def main():
                    "cell_dofs": head["cell_dofs"], "parallelism": "single GPU"},
         "roofline": roof,
         "cpu_baseline": cpu,
-        "extra": extra,
+        "extra": summary(extra),
     }
+    if a.detail:
+        with open(a.detail, "w") as f:
+            json.dump({**line, "extra": extra}, f)
     print(json.dumps(line))
 
 
