@@ -415,8 +415,9 @@ static RefMats<P, C> ref_mats() {
 // with the 1D matrices as scalar operands.  M and K are symmetric about the
 // middle of the element, so the y and x contractions work on the even and odd
 // parts of a line with matrices of half the size (a quarter of the terms each,
-// half in all, and 4 ((p+1)/2)^2 scalars instead of 2 (p+1)^2: at p = 7 they
-// stay in scalar registers).  No LDS, no barrier; every load and store is a run
+// half in all, and 4 ((p+1)/2)^2 scalars instead of 2 (p+1)^2, which the scalar
+// registers hold up to p = 7; the residual, with one more operand, spills up to 124
+// of its scalars to vector lanes).  No LDS, no barrier; every load and store is a run
 // of 64 cells; a block's input comes from HBM once and from L2 for its other
 // planes (neighbouring waves, on one XCD).  Bound by the FMA rate and the latency of the
 // plane loads at two to five wavefronts per SIMD.  Against the LDS form below
@@ -614,7 +615,8 @@ __global__ void __launch_bounds__(256, 2) k_apply_plane(LaunchTable L, PlaneMats
 }
 
 // Output planes for p >= 4 in 4-byte arithmetic and, in FP64, as far as the
-// sums fit the registers of two wavefronts per SIMD.  FP64 against
+// sums about fit the registers of two wavefronts per SIMD (256 each: the p = 5
+// residual in FP64 puts 8 into scratch memory, the p = 7 one in BF16 14).  FP64 against
 // k_apply_planes, us: Laplace p = 4 on 40^3 cells 46 against 82 (80^3 307
 // against 609, 8^3 8.4 against 9.5), p = 5 on 32^3 44 against 77, p = 6 on 28^3
 // 143 (spilling) against 102, p = 7 on 24^3 89 against 77; residual p = 4 52

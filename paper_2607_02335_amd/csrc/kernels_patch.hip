@@ -1366,8 +1366,8 @@ __global__ void __launch_bounds__(256) k_pi_combine_x(LaunchTable L) {
     pi_combine_x_body<P, S, CBP, ACC, MULTI>(L, blockIdx.x, gridDim.x);
 }
 
-// Assembly into the global-node array: one wavefront per (storage block, node
-// row (b, c)) of cells, lanes on the block's 64 cells.  A lane owns its cell's
+// Assembly into the global-node array: one wavefront per node row (b, c) of up
+// to 64 consecutive cells (block_row), lanes on the cells.  A lane owns its cell's
 // nodes a < P of the row (a = P too in the last cell along x; rows b = P and
 // c = P only in the last cells along y and z), and adds to them the copies of
 // its lower neighbours: along x by a lane shuffle, along y and z by loading the
@@ -1376,11 +1376,14 @@ __global__ void __launch_bounds__(256) k_pi_combine_x(LaunchTable L) {
 // once, whatever the length of the mesh rows.  Each node sums its copies in
 // ascending cell order along z, y, x, the same order for every node.  Bound by
 // reading r and writing the nodes once: Q7 24^3 FP32 11 us (4.2 TB/s), FP64
-// 20 us (4.7 TB/s), Q3 64^3 FP64 30 us, Q2 96^3 FP64 46 us; lanes on the nodes
-// of a mesh row, each load 64 different lines of r, took 26, 26, 34 and 61 us.
+// 17 us (5.5 TB/s), Q3 64^3 FP64 31 us, Q2 96^3 FP64 43 us, FP32 29 us, p = 1 144^3
+// FP32 27 us.  Lanes on the nodes of a mesh row, each load 64 different lines of r,
+// took 26, 26, 34, 61, 37 and 33 us; the same rows with one copy's loads waiting for
+// the other's 11, 18, 31, 50, 39 and 38.
 // For 8-byte nodes at p >= 3 the row's runs go through LDS and leave with lanes
-// on consecutive nodes (stores 8 p bytes apart: 25 us at Q7 24^3 against 20, 32
-// at Q3 64^3 against 30; 4-byte nodes and p = 2 measured 3-8% faster without).
+// on consecutive nodes (measured with the loads one after the other: stores 8 p
+// bytes apart 25 us at Q7 24^3 against 20, 32 at Q3 64^3 against 30; 4-byte nodes
+// and p = 2 3-8% faster without).
 // At p >= 4 neighbouring blocks run on one XCD (5-8% faster; at p <= 3 5-15%
 // slower).
 // pe: a = r (S), e = global array (C); tiles of four wavefronts.

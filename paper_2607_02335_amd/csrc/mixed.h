@@ -11,9 +11,14 @@
 // whichever way it is launched.  Segments are ordered heaviest degree first,
 // so the long items start early; segment offsets are multiples of 8, so item
 // i runs on XCD i % 8 as in a launch of the body's own kernel.  A workgroup
-// runs exactly one item: a loop over items (a persistent grid) would let the
-// compiler keep one body's loop-invariant values live in registers across
-// the whole launch, which measured 67 -> 127 VGPRs for the FP32 solves.
+// runs exactly one item: a loop over items (a persistent grid) lets the
+// compiler keep one body's loop-invariant values live in registers across the
+// whole launch.  All bodies of a kernel share its registers and LDS: with the
+// p = 7 body the FP32 solves hold 116 VGPRs and 35 KB, without 66 and 20; in FP64
+// 198 and 70 KB, 126 and 40.  So a mixed launch gains where one degree alone
+// leaves the chip idle and loses a little where it does not; patch inverse of 16
+// problems of 4 to 12 cells an edge, FP32, mixed 81 us, one launch per degree 150,
+// FP64 111 and 165; of 64 problems of 16 to 32 3399 and 3333, FP64 5908 and 5594.
 #pragma once
 
 #include <vector>
