@@ -1367,7 +1367,7 @@ __global__ void __launch_bounds__(256) k_pi_combine_x(LaunchTable L) {
 }
 
 // Assembly into the global-node array: one wavefront per node row (b, c) of up
-// to 64 consecutive cells (block_row), lanes on the cells.  A lane owns its cell's
+// to 64 cells (row_run), lanes on the cells.  A lane owns its cell's
 // nodes a < P of the row (a = P too in the last cell along x; rows b = P and
 // c = P only in the last cells along y and z), and adds to them the copies of
 // its lower neighbours: along x by a lane shuffle, along y and z by loading the
@@ -1419,17 +1419,27 @@ __device__ __forceinline__ void assemble_body(const LaunchTable& L, int item, in
     if (tile >= L.total_tiles) return;
     const ProbEntry& pe = entry<MULTI>(L, tile);
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));
-    const int lane = threadIdx.x % 64, waves = block_rows(pe, P);
+    const int lane = threadIdx.x % 64, waves = row_runs(pe, P);
 #pragma unroll 1
     for (int rr = 0; rr < wave_rows<MULTI>(L); ++rr) {
         const int wave = ((tile - pe.tile_begin) * wave_rows<MULTI>(L) + rr) * 4 + wv;
         if (wave >= waves) return;
         const int n0 = pe.n[0], n1 = pe.n[1], n2 = pe.n[2];
-        const BlockRow br = block_row<P>(pe, wave);
-        const int b = br.b, c = br.c;
-        const int e = min(br.e0 + lane, pe.nblk * kLanes - 1);
-        const int i = e % n0, j = (e / n0) % n1, k = e / (n0 * n1);
-        const bool own = br.e0 + lane < br.e1 && (c < P || k == n2 - 1);
+        const RowRun run = row_run<P>(pe, wave);
+        const int b = run.b, c = run.c;
+        // lanes past the last cell read what is there and own nothing
+        int e, i, j, k;
+        bool own;
+        if (run.edge) {
+            const int t = min(run.first + lane, n0 * n2 - 1);
+            i = t % n0, j = n1 - 1, k = t / n0;
+            e = i + n0 * (j + n1 * k);
+            own = run.first + lane < n0 * n2;
+        } else {
+            e = min(run.first + lane, pe.nblk * kLanes - 1);
+            i = e % n0, j = (e / n0) % n1, k = e / (n0 * n1);
+            own = run.first + lane < pe.ncells && (c < P || k == n2 - 1);
+        }
         const S* v = static_cast<const S*>(pe.a);
         // the loads of all copies first, in flight together (a lane without a
         // copy reads its own cell's and drops it), then the sums
@@ -1764,7 +1774,7 @@ static hipError_t launch_assemble(ProbEntry* ents, int nprob, TableStager* d_tab
     int tiles = 0;
     for (int i = 0; i < nprob; ++i) {
         ents[i].tile_begin = tiles;
-        ents[i].ntiles = row_tiles(block_rows(ents[i], P), L.rows);
+        ents[i].ntiles = row_tiles(row_runs(ents[i], P), L.rows);
         tiles += ents[i].ntiles;
     }
     L.nprob = nprob;
@@ -3106,9 +3116,9 @@ static hipError_t launch_pi_mixed_t(ProbEntry* ents, int nprob, TableStager* st,
     int grid = 0;
     // 1. assembly into each problem's global-node array
     long rows = 0;
-    for (int i = 0; i < nprob; ++i) rows += block_rows(ents[i], ents[i].p);
+    for (int i = 0; i < nprob; ++i) rows += row_runs(ents[i], ents[i].p);
     const int per = rows >= kManyRows ? 4 : 1;
-    auto atiles = [per](int p, const ProbEntry& e) { return row_tiles(block_rows(e, p), per); };
+    auto atiles = [per](int p, const ProbEntry& e) { return row_tiles(row_runs(e, p), per); };
     auto same = [](int, int t) { return t; };
     hipError_t err = mix_build(ents, nprob, st, s, atiles, same, T, grid);
     for (MixSeg& g : T.seg) g.L.rows = per;

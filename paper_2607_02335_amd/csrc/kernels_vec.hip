@@ -341,17 +341,17 @@ __global__ void __launch_bounds__(256) k_dss_axis(ProbEntry pe, int axis, long t
 
 // ------------------------------------------------------------- whole DSS
 // The three axis passes z, y, x of the cascade in one, in place: every shared
-// node is summed and written back by one lane.  One wavefront per node row (b, c)
-// of up to 64 consecutive cells (block_row), lanes on the cells: a lane sums its
-// cell's nodes of the row with the copies of the lower z and y neighbours (loads
-// of runs of consecutive cells), takes the x neighbour's sum by a shuffle, and
-// writes its cell's row and the lower neighbours' copies of it; only the x copies
-// across the edge of a run are read and written by the next run's first lane.
-// Rows with 0 < b, c hold x-shared nodes alone.  Each node adds in the cascade's own
+// node is summed and written back by one lane.  One wavefront per (storage
+// block, node row (b, c)), lanes on its cells: a lane sums its cell's nodes of
+// the row with the copies of the lower z and y neighbours (loads of runs of
+// consecutive cells), takes the x neighbour's sum by a shuffle, and writes its
+// cell's row and the lower neighbours' copies of it; only the x copies across a
+// block's edge are read and written by the next block's first lane.  Rows with
+// 0 < b, c hold x-shared nodes alone.  Each node adds in the cascade's own
 // order (bitwise equal to the three passes in FP64 and FP32; 2-byte storage
 // rounds once instead of after every pass).  Bound by reading and writing the
 // (p+1)^3 - (p-1)^3 surface copies of a cell once, where the passes move 3 x 2
-// (p+1)^2 of them: 135 us for 793 MB at Q3 96^3 FP64 (5.9 TB/s), three passes
+// (p+1)^2 of them: 139 us for 793 MB at Q3 96^3 FP64 (5.7 TB/s), three passes
 // 221 us.
 template <int P, typename S>
 __global__ void __launch_bounds__(256) k_dss(ProbEntry pe, int waves) {
@@ -362,9 +362,10 @@ __global__ void __launch_bounds__(256) k_dss(ProbEntry pe, int waves) {
     const BlockRow br = block_row<P>(pe, wave);
     const int lane = threadIdx.x % 64, b = br.b, c = br.c;
     const int n0 = pe.n[0], n1 = pe.n[1], n2 = pe.n[2];
-    const int e = br.e0 + lane;
+    const int e = br.blk * kLanes + lane;
     const int i = e % n0, j = (e / n0) % n1, k = e / (n0 * n1);
-    const bool own = e < br.e1 && (c < P || k == n2 - 1);
+    const bool own = e < pe.ncells && (b < P || j == n1 - 1) && (c < P || k == n2 - 1);
+    if (__ballot(own) == 0) return;
     const bool all = b == 0 || c == 0;                       // uniform: every node of the row may be shared
     const bool y2 = own && b == 0 && j > 0, z2 = own && c == 0 && k > 0;
     S* v = static_cast<S*>(pe.c);
@@ -393,7 +394,7 @@ __global__ void __launch_bounds__(256) k_dss(ProbEntry pe, int waves) {
     }
     // x pass
     C left = __shfl_up(sum[P], 1, 64);
-    const bool edge = own && lane == 0 && i > 0;             // the left copies lie in the previous run
+    const bool edge = own && lane == 0 && i > 0;             // the left copies lie in the previous block
     if (edge) left = column(e - 1, AP);
     if (own && i > 0) sum[0] = left + sum[0];
     const C right = __shfl_down(sum[0], 1, 64);

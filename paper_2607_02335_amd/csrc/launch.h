@@ -55,32 +55,43 @@ __host__ __device__ inline void red_range(const ProbEntry& pe, int t, size_t& lo
     if (lo > hi) lo = hi;
 }
 
-// Wavefronts of a kernel that gives every node row (b, c) of up to 64
-// consecutive cells one wavefront, lanes on the cells [e0, e1), each owning the
-// nodes below P of its cell, in four parts: the rows b < P of the planes c < P
-// of every storage block; then of the plane c = P of the blocks holding cells of
-// the last layer; the rows b = P of the planes c < P of every layer's last
-// x-rows of cells, in runs of 64; then of the plane c = P.  (Rows b = P dealt to
-// every block as the others are leave 1 / (p + 1) of the wavefronts nothing.)
-// A lane owns its cell's nodes of the row if e0 + lane < e1 and the cell lies in
-// the last layer where c = P.
-struct BlockRow { int e0, e1, b, c; };
+// Wavefronts of a kernel that gives every (storage block, node row (b, c)) one
+// wavefront, lanes on the block's cells, each owning the nodes below P of its
+// cell: rows b = 0..P of the planes c < P of every block, then of the plane
+// c = P of the blocks holding cells of the last layer.
+struct BlockRow { int blk, b, c; };
+__host__ __device__ inline int block_rows(const ProbEntry& e, int P) {
+    const int top = e.nblk - e.n[0] * e.n[1] * (e.n[2] - 1) / kLanes;
+    return (P + 1) * (e.nblk * P + top);
+}
+template <int P> __device__ __forceinline__ BlockRow block_row(const ProbEntry& e, int wave) {
+    const int w = wave / (P + 1);
+    const bool top = w >= e.nblk * P;
+    return {top ? e.n[0] * e.n[1] * (e.n[2] - 1) / kLanes + w - e.nblk * P : w / P, wave % (P + 1), top ? P : w % P};
+}
+
+// The same rows for the assembly, without the wavefronts that own nothing: rows
+// b = P, which only the last x-row of cells of a layer owns, are dealt not to every
+// block (which leaves 1 / (p + 1) of the wavefronts nothing to do) but to runs of 64 of
+// those cells, layer after layer.  Lane l of the wavefront stands for cell
+// first + l (edge: of those cells; else: of all).  In order: rows b < P of the
+// planes c < P of every block; of the plane c = P of the blocks holding cells of the
+// last layer; rows b = P of the planes c < P; of the plane c = P, the last layer's
+// cells alone.
+struct RowRun { int first, b, c; bool edge; };
 __host__ __device__ inline int top_blocks(const ProbEntry& e) {
     return e.nblk - e.n[0] * e.n[1] * (e.n[2] - 1) / kLanes;
 }
-__host__ __device__ inline int block_rows(const ProbEntry& e, int P) {
-    return (e.nblk * P + top_blocks(e)) * P + (e.n[2] * P + 1) * ((e.n[0] + kLanes - 1) / kLanes);
+__host__ __device__ inline int edge_runs(const ProbEntry& e) { return (e.n[0] * e.n[2] + kLanes - 1) / kLanes; }
+__host__ __device__ inline int row_runs(const ProbEntry& e, int P) {
+    return (e.nblk * P + top_blocks(e) + edge_runs(e)) * P + (e.n[0] + kLanes - 1) / kLanes;
 }
-template <int P> __host__ __device__ inline BlockRow block_row(const ProbEntry& e, int wave) {
-    const int inner = e.nblk * P * P, top = inner + top_blocks(e) * P;
-    if (wave < inner) return {wave / (P * P) * kLanes, e.ncells, wave % P, wave / P % P};
-    if (wave < top) {
-        const int w = wave - inner;
-        return {(e.nblk - top_blocks(e) + w / P) * kLanes, e.ncells, w % P, P};
-    }
-    const int runs = (e.n[0] + kLanes - 1) / kLanes, w = (wave - top) / runs;      // w = k P + c, n[2] P for the top
-    const int k = w < e.n[2] * P ? w / P : e.n[2] - 1, row = e.n[0] * (e.n[1] - 1 + e.n[1] * k);
-    return {row + (wave - top) % runs * kLanes, row + e.n[0], P, w < e.n[2] * P ? w % P : P};
+template <int P> __host__ __device__ inline RowRun row_run(const ProbEntry& e, int wave) {
+    const int inner = e.nblk * P * P, top = inner + top_blocks(e) * P, edge = top + edge_runs(e) * P;
+    if (wave < inner) return {wave / (P * P) * kLanes, wave % P, wave / P % P, false};
+    if (wave < top) return {(e.nblk - top_blocks(e) + (wave - inner) / P) * kLanes, (wave - inner) % P, P, false};
+    if (wave < edge) return {(wave - top) / P * kLanes, P, (wave - top) % P, true};
+    return {e.n[0] * (e.n[2] - 1) + (wave - edge) * kLanes, P, P, true};
 }
 
 // 1D reference matrices of degree p on [0,1] (row-major, (p+1)^2), built on
