@@ -206,6 +206,20 @@ __device__ __forceinline__ double f16_residual_scale(const ProbEntry& pe) {
     return ldexp(1.0, -9 - ex);
 }
 
+// A cell's width and its neighbours' along one direction (the cell's own past an
+// end of the mesh).
+struct Widths {
+    double lower, own, upper;
+    __device__ __forceinline__ double at(int d) const {
+        const double u = upper, o = own, l = lower;
+        const double r = d > 0 ? u : o;
+        return d < 0 ? l : r;
+    }
+};
+__device__ __forceinline__ Widths widths_at(const double* h, int i, int n) {
+    return {h[i > 0 ? i - 1 : i], h[i], h[i + 1 < n ? i + 1 : i]};
+}
+
 template <int P, typename RS, int MODE, bool MULTI>
 __device__ __forceinline__ void distribute_body(const LaunchTable& L, int group, const Diag1D& dg, int item, int items,
                                                 char* smem) {
@@ -234,15 +248,13 @@ __device__ __forceinline__ void distribute_body(const LaunchTable& L, int group,
                 continue;
             }
             at.i = e % at.n0, at.j = (e / at.n0) % at.n1, at.k = e / (at.n0 * at.n1);
-            // the widths of the cell and its neighbours, once per block
-            double h[3][3];
+            // the widths of the cell and its neighbours, once per block (each its own
+            // variable: the compiler moves an indexed array to LDS)
+            Widths wx{}, wy{}, wz{};
             if constexpr (MODE == kDistJacobi) {
-                const int at3[3] = {at.i, at.j, at.k};
-#pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    const double* w = pe.h[q] + at3[q];
-                    h[q][0] = w[at3[q] > 0 ? -1 : 0], h[q][1] = w[0], h[q][2] = w[at3[q] + 1 < pe.n[q] ? 1 : 0];
-                }
+                wx = widths_at(pe.h[0], at.i, at.n0);
+                wy = widths_at(pe.h[1], at.j, at.n1);
+                wz = widths_at(pe.h[2], at.k, at.n2);
             }
             for (int l = lb + lq; l < le; l += 4) {
                 at.a = l % N, at.b = (l / N) % N, at.c = l / N2;
@@ -250,8 +262,7 @@ __device__ __forceinline__ void distribute_body(const LaunchTable& L, int group,
                 const int copies = node_copies<P>(at, [&](int ee, int ll, int ci, int cj, int ck) {
                     s += v[cell_offset(ee, ll, NN)];
                     if constexpr (MODE == kDistJacobi) {
-                        auto width = [](const double* w, int d) { return d < 0 ? w[0] : d > 0 ? w[2] : w[1]; };
-                        const double hx = width(h[0], ci - at.i), hy = width(h[1], cj - at.j), hz = width(h[2], ck - at.k);
+                        const double hx = wx.at(ci - at.i), hy = wy.at(cj - at.j), hz = wz.at(ck - at.k);
                         const int ax = ll % N, by = (ll / N) % N, cz = ll / N2;
                         d += (hy * hz / hx) * dg.k[ax] * dg.m[by] * dg.m[cz] +
                              (hx * hz / hy) * dg.m[ax] * dg.k[by] * dg.m[cz] +
