@@ -609,8 +609,15 @@ __device__ __forceinline__ void apply_plane_body(const LaunchTable& L, const Pla
     }
 }
 
+// Wavefronts per SIMD that the registers are held to: two; four for the Laplace
+// apply at p = 5 in FP32 and FP16, which without it takes 130 registers, two more
+// than leave room for the fourth (48^3 cells in FP32 44 us against 42).
+template <int P, typename S, int MODE> constexpr int plane_waves() {
+    return P == 5 && MODE == kApplyLaplace && (Prec<S>::id == FEM_F32 || Prec<S>::id == FEM_F16) ? 4 : 2;
+}
+
 template <int P, typename S, int MODE, bool MULTI>
-__global__ void __launch_bounds__(256, 2) k_apply_plane(LaunchTable L, PlaneMats<P, typename Prec<S>::C> R) {
+__global__ void __launch_bounds__(256, (plane_waves<P, S, MODE>())) k_apply_plane(LaunchTable L, PlaneMats<P, typename Prec<S>::C> R) {
     apply_plane_body<P, S, MODE, MULTI>(L, R, blockIdx.x, gridDim.x);
 }
 
