@@ -2675,11 +2675,13 @@ __device__ __forceinline__ void pi_combine_wr_body(const LaunchTable& L, int ite
 // 32^3 cells at p = 7, 67 MB: 109 us against 91), and so does the mixed launch,
 // which serves batches.  8-byte stores cover a line with 16 cells; there the limit
 // is the buffer, three to four times the output: once it exceeds the cache,
-// k_pi_combine_nr, whose workgroups ask for a row's runs at once, reads it faster
-// (patch inverse at p = 5 on 40^3 cells, 111 MB of output: 337 us with
+// k_pi_combine_nr, whose workgroups ask for a long row's runs at once, reads it
+// faster (patch inverse at p = 5 on 40^3 cells, 111 MB of output: 337 us with
 // k_pi_combine_wr, 325 with it; p = 6 28^3, 60 MB: 182 and 175; 24^3, 38 MB: 101
 // and 109; p = 7 24^3, 57 MB: 206 and 205, 36^3 712 and 689; p = 4 64^3 607 and 612).
-template <typename C> constexpr size_t kRowCombineBytes() { return size_t(sizeof(C) == 4 ? 128 : 56) << 20; }
+// Batches, whose rows are short, keep the wavefronts (96 problems of p = 4, 5 and 4 to
+// 24 cells an edge: 1.69 ms, with workgroups 1.89).
+constexpr size_t kRowCombineBytes = size_t(128) << 20, kRowCombineBytes64 = size_t(56) << 20;
 template <int P, typename C> constexpr bool mixed_combine_pm() { return P >= 4 && sizeof(C) == 4; }
 
 template <int P, typename S, int ACC, bool MULTI>
@@ -2728,7 +2730,8 @@ static hipError_t launch_pi_lines(int accumulate, ProbEntry* ents, int nprob, Ta
     if (cpc == 0) {
         size_t bytes = 0;
         for (int i = 0; i < nprob; ++i) bytes += ents[i].len * sizeof(S);
-        if (bytes > kRowCombineBytes<C>()) cpc = sizeof(C) == 4 ? 1 : 2;
+        if (sizeof(C) == 4 && bytes > kRowCombineBytes) cpc = 1;
+        if (sizeof(C) == 8 && nprob == 1 && bytes > kRowCombineBytes64) cpc = 2;
     }
     int tiles2 = 0;
     for (int i = 0; i < nprob; ++i) {
